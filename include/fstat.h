@@ -122,7 +122,12 @@ typedef struct {
  * PSD to device memory the plan owns, and precomputes the per-bin factors
  * that do not depend on the template (the noise weighting 1/S_n, the f^{-7/6}
  * amplitude of App. A, the bin width factor 4 df of Eq. inner_product, and the
- * template-independent part of the TDI-X transfer).  The caller keeps
+ * template-independent part of the TDI-X transfer).  For data sets of about
+ * 100,000 bins and more with T_obs df <= 1 it also lays out the data's block
+ * spectra, from which the evaluations take the N-terms of smooth templates:
+ * 512 bytes per bin and channel for FP64 and 128 for mixed (3.6 + 0.9 GB at
+ * 7.1 million bins), if that is at most a quarter of the free device memory;
+ * otherwise every bin is evaluated.  The caller keeps
  * ownership of `data`; it may be freed after this call returns.            */
 int fstat_plan_create(fstat_plan_t *plan, const fstat_data_desc *data, const fstat_opts *opts,
                       void *hip_stream);
@@ -378,8 +383,9 @@ int fstat_profile_read(fstat_plan_t plan, int reset, double *kernel_ms, double *
  * interpolation error to matter (FP64 path only).  bin_mix [14] (or NULL):
  * bins of the items by the interpolating loop's per-bin work, [0..2] phase
  * polynomial and sine at every bin, at transfer degree 5, 7, 9, [3..5] the
- * FP64 loop's difference recurrence for the template factor, at degree 5, 7,
- * 9 (on the mixed path [0] degree 4 and [2] degree 6 with the phase carried
+ * forms for smooth phases (the plan's block spectra, or the FP64 loop's
+ * difference recurrence for the template factor), at degree 5, 7,
+ * 9 (on the mixed path, without spectra [0] degree 4 and [2] degree 6 with the phase carried
  * by all nine forward differences, [3] degree 4 and [5] degree 6 with four),
  * [6] handed to the exact loop;
  * [7 + k] (k < 6) the lanes with bins (runs) of the items of kind k, each of

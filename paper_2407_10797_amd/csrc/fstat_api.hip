@@ -1,5 +1,6 @@
 // fstat_api.hip -- C ABI of libfstat (see include/fstat.h): plans, batched
 // evaluation and template generation.
+#include <algorithm>
 #include <array>
 #include <cmath>
 #include <cstdarg>
@@ -95,9 +96,9 @@ int ensure_workspace(fstat_plan_s* P, int64_t n, int32_t stride, int chunk) {
   if ((rc = ensure(&P->ws.direct, &P->cap.direct, cap_items, "alloc direct"))) return rc;
   if ((rc = ensure(&P->ws.ndirect, &P->cap.ndirect, 1, "alloc ndirect"))) return rc;
   const size_t ntiles = (size_t)((P->grid.nbins + chunk - 1) / chunk) * nch;   // all channels
-  if ((rc = ensure(&P->ws.tcnt, &P->cap.tcnt, ntiles, "alloc tcnt"))) return rc;
-  if ((rc = ensure(&P->ws.tcur, &P->cap.tcur, ntiles, "alloc tcur"))) return rc;
-  if ((rc = ensure(&P->ws.toff, &P->cap.toff, ntiles + 1, "alloc toff"))) return rc;
+  if ((rc = ensure(&P->ws.tcnt, &P->cap.tcnt, 2 * ntiles, "alloc tcnt"))) return rc;
+  if ((rc = ensure(&P->ws.tcur, &P->cap.tcur, 2 * ntiles, "alloc tcur"))) return rc;
+  if ((rc = ensure(&P->ws.toff, &P->cap.toff, 2 * ntiles + 1, "alloc toff"))) return rc;
   if ((rc = ensure(&P->ws.uoff, &P->cap.uoff, ntiles + 1, "alloc uoff"))) return rc;
   if ((rc = ensure(&P->ws.tile_items, &P->cap.tile_items, cap_items, "alloc tile items"))) return rc;
   if ((rc = ensure(&P->ws.tile_ctr, &P->cap.tile_ctr, 1, "alloc tile counter"))) return rc;
@@ -137,9 +138,9 @@ static size_t carve_workspace(const fstat_plan_s* P, int64_t n, int32_t stride, 
   take(&w.partials, cap_items * 8);
   take(&w.direct, cap_items);
   take(&w.ndirect, 1);
-  take(&w.tcnt, ntiles);
-  take(&w.tcur, ntiles);
-  take(&w.toff, ntiles + 1);
+  take(&w.tcnt, 2 * ntiles);
+  take(&w.tcur, 2 * ntiles);
+  take(&w.toff, 2 * ntiles + 1);
   take(&w.uoff, ntiles + 1);
   take(&w.tile_items, cap_items);
   take(&w.tile_ctr, 1);
@@ -163,6 +164,70 @@ static int scratch_init(int dev) {
   if (!p) return set_error(FSTAT_EDEVICE, "scratch address is null");
   g_scratch_dev[dev] = static_cast<char*>(p);
   return FSTAT_OK;
+}
+
+// Block spectra of the plan's data.  They only speed the evaluation up: where
+// the device has no room for them the per-bin loop takes every item.
+static int make_spectra(fstat_plan_s* P, hipStream_t s) {
+  const Grid& g = P->grid;
+  Spectra<double> t64{};
+  Spectra<float> t32{};
+  t64.L = (P->prec & FSTAT_FP64) ? spectra_block(false, g.nbins) : 0;
+  t32.L = (P->prec & FSTAT_MIXED) ? spectra_block(true, g.nbins) : 0;
+  if ((!t64.L && !t32.L) || !(g.T_obs * g.df <= kSpecMaxSlope)) return FSTAT_OK;
+  const bool shared = t64.L == t32.L;
+  size_t n64 = 0, n32 = 0;          // values per channel
+  if (t32.L) {
+    t32.Q = t32.L;
+    t32.nslots = spectra_slots(g, t32.Q);
+    t32.nblk = (int32_t)(g.nbins / t32.L);
+    n32 = (size_t)t32.nblk * (size_t)t32.nslots * 2 * kSpecNodes;
+  }
+  if (t64.L) {
+    t64.Q = 2 * t64.L;
+    t64.nslots = spectra_slots(g, t64.Q);
+    if (shared) t64.nslots = std::max(t64.nslots, 2 * t32.nslots - 1);
+    t64.nblk = (int32_t)(g.nbins / t64.L);
+    n64 = (size_t)t64.nblk * (size_t)t64.nslots * 2 * kSpecNodes;
+  }
+  const size_t nch = (size_t)g.chan.n;
+  // at most a quarter of the free memory, so that a plan does not crowd out its caller
+  size_t free_b = 0, total_b = 0;
+  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) { (void)hipGetLastError(); return FSTAT_OK; }
+  if (nch * (n64 * sizeof(double) + n32 * sizeof(float)) > free_b / 4) return FSTAT_OK;
+  bool have = true;
+  if (n64) have = hipMalloc((void**)&t64.S, nch * n64 * sizeof(double)) == hipSuccess;
+  if (have && n32) have = hipMalloc((void**)&t32.S, nch * n32 * sizeof(float)) == hipSuccess;
+  if (!have) {
+    (void)hipGetLastError();
+    if (t64.S) (void)hipFree(t64.S);
+    return FSTAT_OK;
+  }
+  P->s64 = t64;                     // the plan owns them from here on
+  P->s32 = t32;
+  double* lag = nullptr;
+  int rc = dev_alloc(&lag, 2 * 128 * kSpecNodes, "alloc spectra weights");
+  std::vector<double> h(2 * 128 * kSpecNodes, 0.0);
+  if (t64.L) spectra_weights(t64.L, h.data());
+  if (t32.L) spectra_weights(t32.L, h.data() + 128 * kSpecNodes);
+  if (!rc) rc = hip_check(hipMemcpyAsync(lag, h.data(), h.size() * sizeof(double),
+                                         hipMemcpyHostToDevice, s), "copy spectra weights");
+  for (size_t c = 0; c < nch && !rc; ++c) {
+    const double* wr = P->b64.wr + c * (size_t)g.nbins;
+    const double* wi = P->b64.wi + c * (size_t)g.nbins;
+    double* o64 = t64.L ? t64.S + c * n64 : nullptr;
+    float* o32 = t32.L ? t32.S + c * n32 : nullptr;
+    if (shared) {
+      launch_spectra(g, wr, wi, lag, t64, t32, o64, o32, s);
+    } else {
+      if (o64) launch_spectra(g, wr, wi, lag, t64, t32, o64, nullptr, s);
+      if (o32) launch_spectra(g, wr, wi, lag + 128 * kSpecNodes, t64, t32, nullptr, o32, s);
+    }
+    rc = hip_check(hipGetLastError(), "block spectra launch");
+  }
+  if (!rc) rc = hip_check(hipStreamSynchronize(s), "block spectra");
+  dev_free(lag);
+  return rc;
 }
 
 int eval_blocks(fstat_plan_s* P, bool mixed) {
@@ -214,7 +279,7 @@ static int eval_enqueue(fstat_plan_s* P, const WorkSpace& ws, const double* para
   um.upre = P->upre;
   launch_eval(mixed, !exact, P->refine_budget, P->grid, n, stride, chunk, ws, P->b64, P->b32,
               surrogate ? P->sur_ek : nullptr, eval_blocks(P, mixed), s,
-              prof ? &ev[1] : nullptr, um);
+              prof ? &ev[1] : nullptr, um, P->s64, P->s32);
   if (prof) {
     (void)hipEventRecord(ev[3], s);
     P->events.push_back(ev);
@@ -521,6 +586,10 @@ int fstat_plan_create(fstat_plan_t* out, const fstat_data_desc* d, const fstat_o
     fstat_plan_destroy(P);
     return rc;
   }
+  if ((rc = make_spectra(P, s))) {
+    fstat_plan_destroy(P);
+    return rc;
+  }
   if (!(prec & FSTAT_FP64)) {
     // the FP64 data are only needed to build the FP32 copies (the exact mixed
     // loop keeps sin, cos(pi f L) in FP64 for its FP64 response)
@@ -545,6 +614,7 @@ void fstat_plan_destroy(fstat_plan_t P) {
   dev_free(P->io.params); dev_free(P->io.np); dev_free(P->io.F_hat); dev_free(P->io.F_part);
   dev_free(P->io.amps); dev_free(P->umax); dev_free(P->ucoef); dev_free(P->ubad);
   dev_free(P->ures); dev_free(P->upre); dev_free(P->orb_coef);
+  dev_free(P->s64.S); dev_free(P->s32.S);
   pso_release(P);
   sur_release(P);
   for (auto& e : P->events)

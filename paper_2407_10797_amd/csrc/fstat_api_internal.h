@@ -35,6 +35,8 @@ struct fstat_plan_s {
   int32_t* ubad = nullptr;          // prefix count of u-tiles the model does not fit
   double* ures = nullptr;           // relative residual of the model per u-tile
   double* upre = nullptr;           // [channels][nbins + 1] prefix sums of u
+  fstat::Spectra<double> s64{};    // block spectra of the data (spectra.hip), L = 0: none
+  fstat::Spectra<float> s32{};
   double* orb_coef = nullptr;       // numerical orbit (fstat_plan_set_orbit)
   int32_t n_utiles = 0;
   int32_t n_ufit = 0;               // u-tiles fitted to within tolerance

@@ -48,14 +48,15 @@ struct WorkSpace {
   double* Fl;         // [n][stride]
   int32_t* direct;    // [capacity] items the interpolating kernel hands to the exact kernel
   int32_t* ndirect;   // [1]
-  int32_t* tcnt;      // [tiles] items per bin tile
-  int32_t* tcur;      // [tiles] scatter cursors
-  int32_t* toff;      // [tiles + 1] first item of each tile in tile_items
-  int32_t* uoff;      // [tiles + 1] first scheduling unit of each tile
-  int32_t* tile_items;  // [capacity] item indices grouped by bin tile
+  int32_t* tcnt;      // [2 tiles] items per bin tile: those of the block spectra, then those
+                      // of the per-bin loop
+  int32_t* tcur;      // [2 tiles] scatter cursors
+  int32_t* toff;      // [2 tiles + 1] first item of each in tile_items
+  int32_t* uoff;      // [tiles + 1] first scheduling unit of each tile (per-bin loop)
+  int32_t* tile_items;  // [capacity] item indices grouped by loop and bin tile
   int32_t* tile_ctr;  // [1] next unit to take (dynamic schedule)
-  uint8_t* xflag;     // [capacity] 1: item evaluated by the exact kernel
-  double* rec;        // [capacity][53] per-item interpolation records
+  uint8_t* xflag;     // [capacity] kItemBins, kItemExact or kItemBlocks
+  double* rec;        // [capacity][kInterpRec] per-item interpolation records
   float2* xerr;       // [capacity] interpolation error of each interpolated item:
                       // x template (norm-weighted), y M-term quadrature (absolute)
   int32_t* refine;    // [capacity] interpolated items of ill-conditioned partitions
@@ -75,7 +76,33 @@ int interp_tables_init();
 constexpr int kMaxTileFp64 = 2560;   // largest tile (bins) of the LDS-staged loops
 constexpr int kMaxTileMixed = 4608;   // FP32 w: 36 KB + 2 KB per block, four blocks per CU
 int interp_max_tile(bool mixed);   // largest tile (bins) the LDS-staged loop accepts
-constexpr int kInterpRec = 59;     // doubles per interpolation record
+constexpr int kInterpRec = 57;     // doubles per interpolation record
+// WorkSpace::xflag: which loop evaluates an item
+enum : uint8_t { kItemBins = 0, kItemExact = 1, kItemBlocks = 2 };
+
+// Block spectra of the plan's data (see spectra.hip): for every block of L
+// consecutive bins of a channel, nslots phase slopes q / Q [cycles per bin]
+// and kSpecNodes node weights per slope, real parts then imaginary parts:
+// S[channel][block][slope][2][kSpecNodes].
+constexpr int kSpecNodes = 16;
+template <typename T>
+struct Spectra {
+  T* S = nullptr;
+  int32_t L = 0;         // bins per block (a power of two); 0: no spectra
+  int32_t Q = 0;         // slopes per cycle
+  int32_t nslots = 0;    // slopes kept: 0 .. T_obs df Q
+  int32_t nblk = 0;      // whole blocks per channel
+};
+constexpr double kSpecMaxSlope = 1.001;   // largest T_obs df [cycles per bin] with spectra
+// Block size for a data set of nbins bins per channel, 0 for none.
+int spectra_block(bool mixed, int64_t nbins);
+int spectra_slots(const Grid& g, int32_t Q);
+void spectra_weights(int32_t L, double* out);   // [L / 2][kSpecNodes], host
+// Spectra of one channel (w at wr, wi) into s64 and/or s32; with both they share L and
+// t64 has the slopes of t32 at its even places.
+void launch_spectra(const Grid& g, const double* wr, const double* wi, const double* lag,
+                    const Spectra<double>& t64, const Spectra<float>& t32, double* s64, float* s32,
+                    hipStream_t s);
 
 // Smooth model of the template-independent weight u = 4 df f^{-7/3} |C|^2 / S
 // (scaled): a degree-9 Chebyshev least-squares fit per u-tile of kUTile bins,
@@ -104,7 +131,8 @@ void launch_eval(bool mixed, bool interp, double refine_budget, const Grid& g,
                  int64_t n_particles, int32_t stride, int32_t chunk,
                  const WorkSpace& ws, BinData<double> b, BinData<float> b32, const double* ek,
                  int blocks, hipStream_t s, hipEvent_t* ev_main = nullptr,
-                 const UModel& um = UModel{});
+                 const UModel& um = UModel{}, const Spectra<double>& s64 = Spectra<double>{},
+                 const Spectra<float>& s32 = Spectra<float>{});
 void launch_sur_data(uint64_t seed, int64_t n, float* X, float* T, hipStream_t s);
 void launch_sur_knots(const Grid& g, int32_t stride, int64_t n, int64_t rows, const WorkSpace& ws,
                       float* X, hipStream_t s);

@@ -25,6 +25,7 @@
 //                   item partials and the 2x2 Hermitian closed form of F_l
 //   k_mean          one wavefront per particle: F_hat = mean_l F_l, or -inf / NaN
 #include "fstat_internal.h"
+#include <algorithm>
 #include <type_traits>
 
 #include "fstat_kernels.h"
@@ -67,18 +68,20 @@ __global__ void k_prep(Grid g, const double* __restrict__ data, const double* __
   }
 }
 
-// max of u over the band (one block, grid-stride) -> *out
-__global__ void k_max(const double* __restrict__ u, int64_t n, double* __restrict__ out) {
-  __shared__ double red[1024];
+__global__ void k_zero64(unsigned long long* __restrict__ x) {
+  if (threadIdx.x == 0) x[0] = 0ull;
+}
+
+// max of u over the band -> *out (zero before): u > 0, so the order of the
+// doubles is that of their bits.
+__global__ void k_max(const double* __restrict__ u, int64_t n, unsigned long long* __restrict__ out) {
   double m = 0.0;
-  for (int64_t j = threadIdx.x; j < n; j += blockDim.x) m = fmax(m, u[j]);
-  red[threadIdx.x] = m;
-  __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + s]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[0] = red[0];
+  for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n;
+       j += (int64_t)gridDim.x * blockDim.x)
+    m = fmax(m, u[j]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
+  if ((threadIdx.x & 63) == 0) atomicMax(out, (unsigned long long)__double_as_longlong(m));
 }
 
 // Normalise so that max u = 1: F is invariant under (w, u) -> (g w, g^2 u)
@@ -796,18 +799,24 @@ __device__ __forceinline__ double estrin_d(const double* c, double s, double s2,
 
 // Per-item interpolation record: monomial coefficients of R (kCheb), then of
 // Re T''_+, Im T''_+, Re T''_x, Im T''_x (nT each: kCheb, or kDegT + 1 on the
-// mixed path), then A = frac(Phi_0), B' = B - rint(B), B, the item's state
-// (0: the exact loop takes it; 1: interpolated; the FP64 bin loop sets 2 when
-// it took the difference recurrence), the degree the FP64 loop evaluates the
-// transfer interpolants at (5, 7 or 9), the item's first bin within its tile
-// and its bin count, the step alpha = 2 / (bins - 1) of s per bin and -B / df
-// (so that the bin loop needs nothing else per item, and no division).
-constexpr int kRec = 5 * kCheb + 9;
+// mixed path), then A = frac(Phi_0), B' = B - rint(B), B, two integers (the
+// item's flags and its first bin), two more (its bin count; unused), the step
+// alpha = 2 / (bins - 1) of s per bin and -B / df (so that the bin loops need
+// nothing else per item, and no division).  Flags: the loop that takes the
+// item (kRecExact .. kRecBlocks), the degree its transfer interpolants are
+// evaluated at << 8, its channel << 16.
+constexpr int kRec = 5 * kCheb + 7;
 static_assert(kRec == kInterpRec && kRec <= 64, "record layout");
 template <bool MIXED> struct RecLayout {
   static constexpr int nT = MIXED ? kDegT + 1 : kCheb;
-  static constexpr int tail = kCheb + 4 * nT;   // A, B', B, state, degree, first bin, bins, alpha, -B/df
+  static constexpr int tail = kCheb + 4 * nT;   // A, B', B, {flags, b0}, {bins, -}, alpha, -B/df
 };
+// the per-bin loop marks the items whose lanes took its short form (the
+// difference recurrence; mixed: four phase differences) for fstat_interp_stats
+enum { kRecExact = 0, kRecBins = 1, kRecBinsShort = 2, kRecBlocks = 3 };
+__device__ __forceinline__ int rec_int(const double& x, int half) {
+  return reinterpret_cast<const int*>(&x)[half];
+}
 
 // Chebyshev series sum_k c_k T_k(x) (Clenshaw).
 __device__ __forceinline__ double cheb_eval10(const double* __restrict__ c, double x) {
@@ -915,6 +924,15 @@ constexpr double kInterpTolTMixed = 3e-8;
 // lanes active: lanes 60..63 repeat the last point of the last item).  TAB:
 // the plan has a numerical orbit (a separate instance keeps the table code
 // out of the analytic kernel's registers).
+//
+// With block spectra (sp.L > 0) an item goes to the block loop when over any
+// of its blocks the phase stays within sp.psi radians of a straight line and
+// its slope within half a slot of the spectra's range; otherwise to the
+// per-bin loop.  sup |R'| and sup |R''| are bounded by the coefficients' sums.
+struct SpecShape {
+  int32_t L, Q, nslots, nblk;
+  double psi;
+};
 template <bool MIXED, bool TAB>
 __global__ __launch_bounds__(256, 2) void k_interp_nodes(Grid g,
                                                       const PartConst* __restrict__ pc,
@@ -930,7 +948,8 @@ __global__ __launch_bounds__(256, 2) void k_interp_nodes(Grid g,
                                                       int32_t* __restrict__ direct,
                                                       int32_t* __restrict__ ndirect,
                                                       UModel um,
-                                                      double* __restrict__ partials) {
+                                                      double* __restrict__ partials,
+                                                      SpecShape sp) {
   const int lane = threadIdx.x & 63;
   const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int nwaves = (gridDim.x * blockDim.x) >> 6;
@@ -976,8 +995,7 @@ __global__ __launch_bounds__(256, 2) void k_interp_nodes(Grid g,
       // no item of this group is long enough to interpolate: all of them go
       // to the exact loop without evaluating their nodes
       if (k == kCheb && lane - base < kLanesItem && grp * kItemsWave + q < W) {
-        xflag[w] = 1;
-        rec[(int64_t)w * kRec + RecLayout<MIXED>::tail + 3] = 0.0;
+        xflag[w] = kItemExact;
         direct[atomicAdd(ndirect, 1)] = w;
       }
       continue;
@@ -1094,10 +1112,24 @@ __global__ __launch_bounds__(256, 2) void k_interp_nodes(Grid g,
 #pragma unroll
       for (int fn = 0; fn < 4; ++fn) aG[fn] = fma(gt[fn], rg, aG[fn]);
     }
-    __builtin_amdgcn_wave_barrier();   // the slots are rewritten by the next group
+    __builtin_amdgcn_wave_barrier();   // the slots are rewritten below
+    const double cR = aRs + aRx;
+    double d1 = 0.0, d2 = 0.0;         // sup |R'|, sup |R''| over the item (lane kCheb)
+    if (sp.L > 0) {
+      my_nd[0] = (double)k * fabs(cR);
+      __builtin_amdgcn_wave_barrier();
+      if (k == kCheb) {
+#pragma unroll
+        for (int kn = 1; kn < kCheb; ++kn) {
+          const double a = item_nd[kNd * kn];
+          d1 += a;
+          d2 = fma((double)(kn - 1), a, d2);
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
     const double tolP = MIXED ? kInterpTolPhaseMixed : kInterpTolPhase;
     const double tolT = MIXED ? kInterpTolTMixed : kInterpTolT;
-    const double cR = aRs + aRx;
     bool bad = false;
     double err = 0.0;           // relative template error at this end point
     double errt[2] = {0.0, 0.0};   // transfer error of the degree-5 and -7 (mixed: 4) truncations
@@ -1167,16 +1199,24 @@ __global__ __launch_bounds__(256, 2) void k_interp_nodes(Grid g,
       }
     } else if (k == kCheb) {
       FSTAT_NO_CONTRACT
-      r[L::tail + 4] = (double)degT;
+      const double alpha = nb > 1 ? 2.0 / (double)(nb - 1) : 0.0;
       r[L::tail] = (p0h - floor(p0h)) + p0l;     // fractional cycle at the first bin
       r[L::tail + 1] = B - rint(B);              // whole cycles per bin drop out (m is an integer)
       r[L::tail + 2] = B;
-      r[L::tail + 3] = rej ? 0.0 : 1.0;
-      r[L::tail + 5] = (double)(b0 % T);          // first bin within its tile
-      r[L::tail + 6] = (double)nb;
-      r[L::tail + 7] = nb > 1 ? 2.0 / (double)(nb - 1) : 0.0;
-      r[L::tail + 8] = -B / g.df;
-      xflag[w] = rej ? 1 : 0;
+      bool blocks = false;
+      if (sp.L > 0) {
+        const double half = 0.5 * (double)(sp.L - 1) * alpha;
+        const double hq = 0.5 / (double)sp.Q, sl = alpha * d1;
+        blocks = kPi * d2 * half * half <= sp.psi && B - sl >= -hq &&
+                 B + sl <= (double)(sp.nslots - 1) / (double)sp.Q + hq;
+      }
+      const int state = rej ? kRecExact : (blocks ? kRecBlocks : kRecBins);
+      int2* ri = reinterpret_cast<int2*>(r + L::tail + 3);
+      ri[0] = make_int2(state | degT << 8 | ch << 16, b0);
+      ri[1] = make_int2(nb, 0);
+      r[L::tail + 5] = alpha;
+      r[L::tail + 6] = -B / g.df;
+      xflag[w] = rej ? kItemExact : (blocks ? kItemBlocks : kItemBins);
       // the template error times the norm sqrt(sum u) max|T| of the item's
       // templates, and the M-term quadrature's error bound: its relative error
       // at the end points times max u |T|^2 times the bin count (see k_mark)
@@ -1285,25 +1325,22 @@ __global__ __launch_bounds__(256) void k_eval_interp(Grid g,
       const int idn = idx + nwv;
       wn = idn < cnt ? tile_items[i0 + idn] : 0;
       rv = (idn < cnt && lane < kRec) ? rec[(int64_t)wn * kRec + lane] : 0.0;
-      if (R[L::tail + 3] == 0.0) {                 // evaluated by the exact kernel
-        __builtin_amdgcn_wave_barrier();
-        continue;
-      }
-      const int e0 = (int)R[L::tail + 5];         // LDS offset of the item's first bin
-      const int nb = (int)R[L::tail + 6];
+      const int e0 = rec_int(R[L::tail + 3], 1) - j0;   // LDS offset of the item's first bin
+      const int nb = rec_int(R[L::tail + 4], 0);
       double cR[kCheb];
 #pragma unroll
       for (int n = 0; n < kCheb; ++n) cR[n] = R[n];
       const double A = R[L::tail];
       const double Bp = R[L::tail + 1];
-      const int degT = (int)R[L::tail + 4];      // transfer degree (FP64 loop)
-      const double alpha = R[L::tail + 7];        // 2 / (nb - 1)
+      const int flags = rec_int(R[L::tail + 3], 0);
+      const int degT = (flags >> 8) & 255;        // transfer degree
+      const double alpha = R[L::tail + 5];        // 2 / (nb - 1)
       if constexpr (!MIXED) {
         // The grid is f_j = (k_lo + j) df rounded to a double; the interpolants
         // are exact in f, so the phase moves by (dPhi/df)(f_j - exact) =
         // -(B / df) e_j, with e_j the rounding error of the product (staged
         // with the tile): up to ~1e-9 cycles at t_f ~ 1e8 s.
-        const double kB = R[L::tail + 8];           // -B / df
+        const double kB = R[L::tail + 6];           // -B / df
         // Difference recurrence for items whose lanes get runs of at least
         // kRecMinRun bins.  Lane l takes the contiguous bins m0 = l Lr ..
         // m0 + Lr - 1 (Lr odd, so that the lanes' LDS addresses fall in
@@ -1359,7 +1396,8 @@ __global__ __launch_bounds__(256) void k_eval_interp(Grid g,
           const bool ok = cnt == 0 || (phimax <= kRecPhiMax && c5 * kTwoPi * fabs(d5) <= kRecTrunc);
           use_rec = __all(ok);
         }
-        if (lane == 0 && use_rec) rec[(int64_t)w * kRec + L::tail + 3] = 2.0;   // for fstat_interp_stats
+        if (lane == 0 && use_rec)                      // for fstat_interp_stats
+          *reinterpret_cast<int*>(rec + (int64_t)w * kRec + L::tail + 3) = flags + 1;
         // DT: degree of the transfer interpolants (5, 7 or 9)
         auto loop = [&](auto dt) {
           constexpr int DT = decltype(dt)::value;
@@ -1595,7 +1633,8 @@ __global__ __launch_bounds__(256) void k_eval_interp(Grid g,
           ph = fma(Bp, (double)m0, p[0]) + A;
           ph -= rint(ph);
         }
-        if (lane == 0 && trunc) rec[(int64_t)w * kRec + L::tail + 3] = 2.0;   // for fstat_interp_stats
+        if (lane == 0 && trunc)                        // for fstat_interp_stats
+          *reinterpret_cast<int*>(rec + (int64_t)w * kRec + L::tail + 3) = flags + 1;
         // D: transfer degree; ND: forward differences carried (the last held)
         auto loop = [&](auto dt, auto ndt) {
           constexpr int D = decltype(dt)::value;
@@ -1701,6 +1740,302 @@ __global__ __launch_bounds__(256) void k_eval_interp(Grid g,
   }
 }
 
+// ---------------------------------------------------------------------------
+// the block loop: items evaluated from the plan's block spectra
+// ---------------------------------------------------------------------------
+// largest curvature over a block [rad] (see spectra.hip)
+constexpr double kSpecPsiFp64 = 0.25;
+constexpr double kSpecPsiMixed = 1.0;
+constexpr int kGrp = kSpecNodes;        // lanes per item: one per node of a block's row
+constexpr int kRecPad = 58;             // record stride in LDS: the four records of a wave
+                                        // in distinct banks
+constexpr int kBlkAhead = 2;            // rows of the spectra in flight per lane
+static_assert(kRec <= kRecPad && kGrp == 16, "group layout");
+
+// lane n of each row of 16 to the whole row
+template <int N>
+__device__ __forceinline__ double row_bcast(double x) {
+  int2 v = *reinterpret_cast<int2*>(&x);
+  v.x = __builtin_amdgcn_update_dpp(v.x, v.x, 0x150 + N, 0xf, 0xf, false);   // row_newbcast
+  v.y = __builtin_amdgcn_update_dpp(v.y, v.y, 0x150 + N, 0xf, 0xf, false);
+  return *reinterpret_cast<double*>(&v);
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double x) {
+  int2 v = *reinterpret_cast<int2*>(&x);
+  v.x = __builtin_amdgcn_update_dpp(v.x, v.x, CTRL, 0xf, 0xf, false);
+  v.y = __builtin_amdgcn_update_dpp(v.y, v.y, CTRL, 0xf, 0xf, false);
+  return x + *reinterpret_cast<double*>(&v);
+}
+// sum over each row of 16 lanes, on every lane (fixed order)
+__device__ __forceinline__ double row_sum(double x) {
+  x = dpp_add<0xB1>(x);                 // quad_perm [1, 0, 3, 2]
+  x = dpp_add<0x4E>(x);                 // quad_perm [2, 3, 0, 1]
+  x = dpp_add<0x141>(x);                // row_half_mirror
+  return dpp_add<0x140>(x);             // row_mirror
+}
+
+// An item's per-lane sums sum_j V_j s_j^k of the samples V = S e^{i Phi} that its
+// sixteen lanes take (nodes of its whole blocks, or bins of its partial ones),
+// s in [-1, 1] the item's coordinate.  DT: highest power.  FP64: even moments
+// from V, odd ones from V s, against even powers of s.
+template <bool MIXED, int DT>
+struct Moments {
+  typedef typename std::conditional<MIXED, float, double>::type T;
+  T mr[DT + 1], mm[DT + 1];
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int k = 0; k <= DT; ++k) mr[k] = mm[k] = T(0);
+  }
+  // ph: the sample's phase [turns]; (a, b): its data
+  __device__ __forceinline__ void add(double ph, double sd, T a, T b, const double2* tab) {
+    T sp, cp;
+    if constexpr (MIXED) {
+      const float rf = (float)(ph - rint(ph));
+      sp = __builtin_amdgcn_sinf(rf);
+      cp = __builtin_amdgcn_cosf(rf);
+    } else {
+      sincos_tab(ph, tab, sp, cp);
+    }
+    const T s = (T)sd, s2 = s * s;
+    const T Vr = a * cp - b * sp, Vi = a * sp + b * cp;
+    const T Ur = Vr * s, Ui = Vi * s;
+    mr[0] += Vr;
+    mm[0] += Vi;
+    mr[1] += Ur;
+    mm[1] += Ui;
+    T pw = s2;
+#pragma unroll
+    for (int k = 2; k <= DT; ++k) {
+      const T xr = (k & 1) ? Ur : Vr, xi = (k & 1) ? Ui : Vi;
+      mr[k] = fma(xr, pw, mr[k]);
+      mm[k] = fma(xi, pw, mm[k]);
+      if (k & 1) pw *= s2;
+    }
+  }
+  // The item's four N-terms from its record R, summed over the sixteen lanes
+  // (on every lane); applied in FP64.
+  __device__ __forceinline__ double total(const double* R, int m) const {
+    constexpr int nT = RecLayout<MIXED>::nT;
+    double acc[4];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int k = 0; k <= DT; ++k) {
+        const double tr = R[kCheb + 2 * h * nT + k], ti = R[kCheb + (2 * h + 1) * nT + k];
+        const double r = mr[k], q = mm[k];
+        acc[2 * h] = fma(tr, r, k ? fma(ti, q, acc[2 * h]) : ti * q);
+        acc[2 * h + 1] = fma(tr, q, k ? fma(-ti, r, acc[2 * h + 1]) : -ti * r);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[i] = row_sum(acc[i]);
+    const double lo = (m & 1) ? acc[1] : acc[0], hi = (m & 1) ? acc[3] : acc[2];
+    return (m & 2) ? hi : lo;            // lane m of the row holds term m & 3
+  }
+};
+
+// R(s) of a record's coefficients
+__device__ __forceinline__ double phase_poly(const double* cR, double s) {
+  const double s2 = s * s, s4 = s2 * s2;
+  return estrin9(cR, s, s2, s4, s4 * s4);
+}
+
+// Whole blocks of the block-loop items: sixteen lanes per item, one per node;
+// four items per wavefront, each lane looping over its item's blocks, two rows
+// of the spectra in flight.  Items come in tile order and each XCD (block
+// index mod 8) takes one contiguous eighth of them, so that the rows that many
+// particles share at a time stay in its L2.
+template <bool MIXED>
+__global__ __launch_bounds__(256, MIXED ? 4 : 3) void k_eval_blocks(
+    Spectra<typename std::conditional<MIXED, float, double>::type> sp,
+    const int32_t* __restrict__ list, const int32_t* __restrict__ nlist,
+    const double* __restrict__ rec, double* __restrict__ partials) {
+  typedef typename std::conditional<MIXED, float, double>::type DT_;
+  typedef RecLayout<MIXED> L;
+  __shared__ double2 s_tab[MIXED ? 1 : kSinTab];
+  __shared__ double s_rec[4][4][kRecPad];
+  if constexpr (!MIXED) {
+    for (int k = threadIdx.x; k < kSinTab; k += blockDim.x) s_tab[k] = c_sincos[k];
+    __syncthreads();
+  }
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int grp = lane >> 4, m = lane & 15;
+  const int n = nlist[0];
+  const int per = ((n + 7) / 8 + 15) & ~15;                 // items per XCD
+  const int lo = min(n, (int)(blockIdx.x & 7) * per), hi = min(n, lo + per);
+  const int step = (int)(gridDim.x >> 3) * 16;
+  const double c = 0.5 * (double)(sp.L - 1);                // block centre
+  double xs, xc;
+  sincospi(((double)m + 0.5) / (double)kSpecNodes, &xs, &xc);
+  const double y = c * xc;                                  // this lane's node
+  sincospi(0.5 / (double)kSpecNodes, &xs, &xc);
+  const double chord = 0.5 / (c * xc);                      // 1 / (distance of the end nodes)
+  const double invQ = 1.0 / (double)sp.Q;
+  const int lg = __builtin_ctz(sp.L);
+  int first = lo + (int)(blockIdx.x >> 3) * 16 + wv * 4;    // of this wave's four items
+  for (; first < hi; first += step) {
+    const int w = first + grp < hi ? list[first + grp] : -1;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int wi = __builtin_amdgcn_readlane(w, 16 * i);
+      if (wi >= 0 && lane < kRec) s_rec[wv][i][lane] = rec[(int64_t)wi * kRec + lane];
+    }
+    __builtin_amdgcn_wave_barrier();
+    const double* R = s_rec[wv][grp];
+    const double A = R[L::tail], Bp = R[L::tail + 1], B = R[L::tail + 2];
+    const int flags = rec_int(R[L::tail + 3], 0), b0 = rec_int(R[L::tail + 3], 1);
+    const int nb = rec_int(R[L::tail + 4], 0);
+    const double alpha = R[L::tail + 5];
+    const int degT = (flags >> 8) & 255, ch = flags >> 16;
+    const int fb = (b0 + sp.L - 1) >> lg;                   // whole blocks [fb, fb + nrow)
+    const int nrow = w >= 0 ? max(min((b0 + nb) >> lg, sp.nblk) - fb, 0) : 0;
+    const double Ac = A + (B * c - rint(B * c));            // the slope's phase at a block's centre
+    const DT_* base = sp.S + ((int64_t)ch * sp.nblk + fb) * sp.nslots * (2 * kSpecNodes) + m;
+    auto loop = [&](auto dt) {
+      Moments<MIXED, decltype(dt)::value> M;
+      M.clear();
+      for (int i0 = 0; __any(i0 < nrow); i0 += kBlkAhead) {
+        double s[kBlkAhead], ph[kBlkAhead];
+        DT_ a[kBlkAhead], b[kBlkAhead];
+#pragma unroll
+        for (int u = 0; u < kBlkAhead; ++u) {
+          const int i = i0 + u;
+          const double mb = (double)(((fb + i) << lg) - b0);
+          s[u] = fma(alpha, mb + (c + y), -1.0);
+          const double r = phase_poly(R, s[u]);   // R's head: its coefficients
+          // the chord of the block's phase chooses the slope slot
+          const double sl = fma(row_bcast<0>(r) - row_bcast<15>(r), chord, B);
+          const int q = min(max((int)rint(sl * (double)sp.Q), 0), sp.nslots - 1);
+          ph[u] = (r + Ac) + fma(Bp, mb, fma(-invQ, (double)q, B) * y);
+          a[u] = b[u] = DT_(0);
+          if (i < nrow) {
+            const DT_* row = base + ((int64_t)i * sp.nslots + q) * (2 * kSpecNodes);
+            a[u] = row[0];
+            b[u] = row[kSpecNodes];
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < kBlkAhead; ++u) M.add(ph[u], s[u], a[u], b[u], s_tab);
+      }
+      const double t = M.total(R, m);
+      if (nrow > 0 && m < 4) partials[(int64_t)w * 8 + m] = t;
+    };
+    if constexpr (MIXED) {
+      if (__any(nrow > 0 && degT > kDegTLow)) loop(std::integral_constant<int, kDegT>{});
+      else loop(std::integral_constant<int, kDegTLow>{});
+    } else {
+      if (__any(nrow > 0 && degT > 7)) loop(std::integral_constant<int, 9>{});
+      else if (__any(nrow > 0 && degT > 5)) loop(std::integral_constant<int, 7>{});
+      else loop(std::integral_constant<int, 5>{});
+    }
+    __builtin_amdgcn_wave_barrier();     // the slots are rewritten for the next items
+  }
+}
+
+// Partial blocks of the block-loop items, bin by bin.  With tiles of whole
+// blocks only a partition's first and last item of a channel have any: sixteen
+// lanes take the first item of a (partition, channel) or, in the second half
+// of the groups, the last one where that is another, and add to the sums of
+// its whole blocks.
+template <bool MIXED>
+__global__ __launch_bounds__(256, MIXED ? 4 : 3) void k_eval_edges(
+    Grid g, int32_t Lb, int32_t nblk, int64_t ngroups, const int32_t* __restrict__ cnt,
+    const int32_t* __restrict__ off, const uint8_t* __restrict__ xflag,
+    const typename std::conditional<MIXED, float, double>::type* __restrict__ wr,
+    const typename std::conditional<MIXED, float, double>::type* __restrict__ wi,
+    const double* __restrict__ rec, double* __restrict__ partials) {
+  typedef typename std::conditional<MIXED, float, double>::type DT_;
+  typedef RecLayout<MIXED> L;
+  __shared__ double2 s_tab[MIXED ? 1 : kSinTab];
+  __shared__ double s_rec[4][4][kRecPad];
+  if constexpr (!MIXED) {
+    for (int k = threadIdx.x; k < kSinTab; k += blockDim.x) s_tab[k] = c_sincos[k];
+    __syncthreads();
+  }
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int grp = lane >> 4, m = lane & 15;
+  const int lg = __builtin_ctz(Lb);
+  const int nch = g.chan.n;
+  const int64_t step = (int64_t)gridDim.x * 16;
+  for (int64_t first = (int64_t)blockIdx.x * 16 + wv * 4; first < 2 * ngroups; first += step) {
+    const int64_t id = first + grp;
+    int w = -1;
+    if (id < 2 * ngroups) {
+      const bool side = id >= ngroups;
+      const int64_t pq = side ? id - ngroups : id, q = pq / nch;
+      const int n = cnt[q];
+      if (n > (side ? nch : 0)) {
+        w = off[q] + (int)(pq - q * nch) + (side ? n - nch : 0);
+        if (xflag[w] != kItemBlocks) w = -1;
+      }
+    }
+    if (!__any(w >= 0)) continue;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int wi_ = __builtin_amdgcn_readlane(w, 16 * i);
+      if (wi_ >= 0 && lane < kRec) s_rec[wv][i][lane] = rec[(int64_t)wi_ * kRec + lane];
+    }
+    __builtin_amdgcn_wave_barrier();
+    const double* R = s_rec[wv][grp];
+    const double A = R[L::tail], Bp = R[L::tail + 1], alpha = R[L::tail + 5];
+    const double kB = R[L::tail + 6];
+    const int flags = rec_int(R[L::tail + 3], 0), b0 = rec_int(R[L::tail + 3], 1);
+    const int nb = rec_int(R[L::tail + 4], 0);
+    const int degT = (flags >> 8) & 255, ch = flags >> 16;
+    const int b1 = b0 + nb;
+    const int fb = (b0 + Lb - 1) >> lg, lb = min(b1 >> lg, nblk);
+    const int h1 = min(fb << lg, b1), t0 = max(lb << lg, h1);   // bins [b0, h1) and [t0, b1)
+    const int nh = (h1 - b0 + 15) >> 4;
+    const int nrow = w >= 0 ? nh + ((b1 - t0 + 15) >> 4) : 0;
+    const DT_* cwr = wr + (int64_t)ch * g.nbins;
+    const DT_* cwi = wi + (int64_t)ch * g.nbins;
+    auto loop = [&](auto dt) {
+      Moments<MIXED, decltype(dt)::value> M;
+      M.clear();
+      for (int i0 = 0; __any(i0 < nrow); i0 += kBlkAhead) {
+        int j[kBlkAhead];
+        DT_ a[kBlkAhead], b[kBlkAhead];
+#pragma unroll
+        for (int u = 0; u < kBlkAhead; ++u) {
+          const int i = i0 + u;
+          const bool head = i < nh;
+          j[u] = (head ? b0 + 16 * i : t0 + 16 * (i - nh)) + m;
+          a[u] = b[u] = DT_(0);
+          if (i < nrow && j[u] < (head ? h1 : b1)) { a[u] = cwr[j[u]]; b[u] = cwi[j[u]]; }
+        }
+#pragma unroll
+        for (int u = 0; u < kBlkAhead; ++u) {
+          const double mi = (double)(j[u] - b0);
+          const double s = fma(alpha, mi, -1.0);
+          double ph = fma(Bp, mi, phase_poly(R, s)) + A;
+          if constexpr (!MIXED) {
+            const double jd = (double)(g.k_lo + j[u]);      // grid rounding, as in k_eval_interp
+            ph = fma(kB, fma(jd, g.df, -(jd * g.df)), ph);
+          }
+          M.add(ph, s, a[u], b[u], s_tab);
+        }
+      }
+      const double t = M.total(R, m);
+      if (nrow > 0 && m < 4) {
+        double* o = partials + (int64_t)w * 8 + m;
+        *o = lb > fb ? *o + t : t;
+      }
+    };
+    if (__any(nrow > 0)) {
+      if constexpr (MIXED) {
+        if (__any(nrow > 0 && degT > kDegTLow)) loop(std::integral_constant<int, kDegT>{});
+        else loop(std::integral_constant<int, kDegTLow>{});
+      } else {
+        if (__any(nrow > 0 && degT > 7)) loop(std::integral_constant<int, 9>{});
+        else if (__any(nrow > 0 && degT > 5)) loop(std::integral_constant<int, 7>{});
+        else loop(std::integral_constant<int, 5>{});
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
 // Refinement of the FP64 interpolating loop's partitions.  With beta =
 // H^{-1} z the maximiser and r the data minus its projection on the template
 // span, a template error dA and an error dH_q of the quadrature M-terms move
@@ -1738,7 +2073,7 @@ __global__ void k_mark(const PartConst* __restrict__ pc, int64_t n, int32_t stri
   int ninterp = 0;
   double s2 = 0.0, mt = 0.0;
   for (int i = 0; i < c; ++i)
-    if (xflag[o + i] == 0) {
+    if (xflag[o + i] != kItemExact) {
       ++ninterp;
       const float2 x = xerr[o + i];
       s2 = fma((double)x.x, (double)x.x, s2);
@@ -1775,7 +2110,7 @@ __global__ void k_mark(const PartConst* __restrict__ pc, int64_t n, int32_t stri
     thr_m = 0.5 * tol / (km * (double)ninterp);
   }
   auto sel = [&](int i) {
-    if (xflag[o + i] != 0) return false;
+    if (xflag[o + i] == kItemExact) return false;
     const float2 x = xerr[o + i];
     return all || (double)x.x > thr_t || (double)x.y > thr_m;
   };
@@ -1818,15 +2153,18 @@ __global__ __launch_bounds__(256) void k_bin_mix(const int2* __restrict__ items,
     item_bins(bp[l], bp[l + 1], ct, T, b0, b1);
     const int nb = b1 - b0;
     int kind = 6, runs = 1;
-    if (!xflag[w]) {
+    if (xflag[w] != kItemExact) {
       const double* r = rec + (int64_t)w * kRec;
-      const int deg = (int)r[L::tail + 4];
-      const bool dr = r[L::tail + 3] == 2.0;
+      const int flags = rec_int(r[L::tail + 3], 0), state = flags & 255;
+      const int deg = (flags >> 8) & 255;
+      const bool dr = state != kRecBins;
       kind = (MIXED ? (deg == kDegTLow ? 0 : 2) : (deg == 5 ? 0 : (deg == 7 ? 1 : 2))) + (dr ? 3 : 0);
       // the recurrence's and the mixed loop's lanes take runs of Lr
       // contiguous bins, the FP64 direct form's lanes every 64th bin
+      // (a block-loop item: its sixteen lanes)
       const int Lr = ((nb + 63) >> 6) | 1;
-      runs = (MIXED || dr) ? (nb + Lr - 1) / Lr : min(nb, 64);
+      runs = state == kRecBlocks ? kSpecNodes
+                                 : ((MIXED || dr) ? (nb + Lr - 1) / Lr : min(nb, 64));
     }
     atomicAdd(&acc[kind], (unsigned long long)nb);
     atomicAdd(&acc[7 + kind], (unsigned long long)runs);
@@ -1841,87 +2179,100 @@ void launch_bin_mix(bool mixed, int32_t stride, int32_t chunk, int32_t nch, cons
                      ws.items, ws.total, ws.bounds, stride, chunk, nch, ws.rec, ws.xflag, out);
 }
 
-// ---- grouping of the work items by bin tile ---------------------------------
-__global__ void k_tile_zero(int32_t* __restrict__ tcnt, int32_t* __restrict__ tcur, int32_t ntiles,
+// ---- grouping of the work items by loop and bin tile -------------------------
+__global__ void k_tile_zero(int32_t* __restrict__ tcnt, int32_t* __restrict__ tcur, int32_t n2,
                             int32_t* __restrict__ tile_ctr) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < ntiles) { tcnt[i] = 0; tcur[i] = 0; }
+  if (i < n2) { tcnt[i] = 0; tcur[i] = 0; }
   if (i == 0) tile_ctr[0] = 0;
 }
 
-// Items per tile.  When the tiles fit in LDS the block first counts its own
+// Where item w is counted: its tile, of the block loop or (+ ntiles) of the
+// per-bin loop; -1: the exact loop takes it.
+__device__ __forceinline__ int tile_key(const int2* __restrict__ items,
+                                        const uint8_t* __restrict__ xflag,
+                                        const int32_t* __restrict__ bounds, int32_t stride,
+                                        int32_t T, int32_t ntiles, int32_t nch, int w) {
+  const uint8_t x = xflag[w];
+  if (x == kItemExact) return -1;
+  const int2 it = items[w];
+  const int p = it.x / stride, l = it.x - p * stride;
+  const int t = item_xtile(bounds[(int64_t)p * (stride + 1) + l], it.y, T, nch, ntiles);
+  return x == kItemBlocks ? t : ntiles + t;
+}
+
+// Items per key.  When the keys fit in LDS the block first counts its own
 // items there and then adds its non-zero counts to the global ones: with few
-// tiles (a narrow band) every item would otherwise hit the same few counters.
+// tiles (a narrow band) every item would otherwise hit the same few counters
+// (counting in the node kernel by global atomics cost 1.5 ms at 872,322 items
+// on 198 tiles, and 0.2 ms at 2 million on 3468).
 constexpr int kTileHist = 8192;
 
 __global__ __launch_bounds__(256) void k_tile_count(const int2* __restrict__ items,
                                                     const int32_t* __restrict__ total,
+                                                    const uint8_t* __restrict__ xflag,
                                                     const int32_t* __restrict__ bounds,
                                                     int32_t stride, int32_t T, int32_t ntiles,
                                                     int32_t nch, int32_t* __restrict__ tcnt) {
   __shared__ int32_t h[kTileHist];
-  const bool local = ntiles <= kTileHist;
+  const int nk = 2 * ntiles;
+  const bool local = nk <= kTileHist;
   const int W = total[0];
   if (local) {
-    for (int i = threadIdx.x; i < ntiles; i += blockDim.x) h[i] = 0;
+    for (int i = threadIdx.x; i < nk; i += blockDim.x) h[i] = 0;
     __syncthreads();
   }
   for (int w = blockIdx.x * blockDim.x + threadIdx.x; w < W; w += gridDim.x * blockDim.x) {
-    const int2 it = items[w];
-    const int p = it.x / stride, l = it.x - p * stride;
-    const int t = item_xtile(bounds[(int64_t)p * (stride + 1) + l], it.y, T, nch, ntiles);
+    const int t = tile_key(items, xflag, bounds, stride, T, ntiles, nch, w);
+    if (t < 0) continue;
     if (local) atomicAdd(&h[t], 1);
     else atomicAdd(&tcnt[t], 1);
   }
   if (local) {
     __syncthreads();
-    for (int i = threadIdx.x; i < ntiles; i += blockDim.x)
+    for (int i = threadIdx.x; i < nk; i += blockDim.x)
       if (h[i]) atomicAdd(&tcnt[i], h[i]);
   }
 }
 
-// Exclusive scans of the per-tile item counts into off[0..n] and of the
-// per-tile unit counts ceil(cnt / kUnitItems) into uoff[0..n] (a unit is the
-// bin loop's scheduling step: one tile, up to kUnitItems of its items).  One
-// block.
-
-__global__ void k_tile_scan(const int32_t* __restrict__ tcnt, int32_t n, int32_t* __restrict__ off,
-                            int32_t* __restrict__ uoff) {
-  __shared__ int32_t part[1024], upart[1024];
-  const int t = threadIdx.x, TB = blockDim.x;
-  const int per = (n + TB - 1) / TB;
-  const int a = t * per, b = min(n, a + per);
-  int32_t sum = 0, usum = 0;
+// Exclusive scans of the per-tile item counts into off[0..2 n] (the block
+// loop's tiles, then the per-bin loop's) and of the per-bin loop's unit counts
+// ceil(cnt / kUnitItems) into uoff[0..n] (a unit is its scheduling step: one
+// tile, up to kUnitItems of its items).  One block.
+__global__ __launch_bounds__(1024) void k_tile_scan(const int32_t* __restrict__ tcnt, int32_t n,
+                                                    int32_t* __restrict__ off,
+                                                    int32_t* __restrict__ uoff) {
+  __shared__ int32_t sh[1024];
+  const int t = threadIdx.x;
+  const int per = (2 * n + 1023) / 1024;
+  const int a = min(2 * n, t * per), b = min(2 * n, a + per);
+  int32_t sum = 0, usum = 0, tot, utot;
   for (int i = a; i < b; ++i) {
     sum += tcnt[i];
-    usum += (tcnt[i] + kUnitItems - 1) / kUnitItems;
+    if (i >= n) usum += (tcnt[i] + kUnitItems - 1) / kUnitItems;
   }
-  part[t] = sum;
-  upart[t] = usum;
-  __syncthreads();
+  int32_t run = block_excl_scan(sum, sh, tot);
+  int32_t urun = block_excl_scan(usum, sh, utot);
   if (t == 0) {
-    int32_t run = 0, urun = 0;
-    for (int i = 0; i < TB; ++i) {
-      int32_t x = part[i], y = upart[i];
-      part[i] = run; upart[i] = urun;
-      run += x; urun += y;
-    }
-    off[n] = run;
-    uoff[n] = urun;
+    off[2 * n] = tot;
+    uoff[n] = utot;
   }
-  __syncthreads();
-  int32_t run = part[t], urun = upart[t];
   for (int i = a; i < b; ++i) {
-    off[i] = run; uoff[i] = urun;
+    off[i] = run;
     run += tcnt[i];
-    urun += (tcnt[i] + kUnitItems - 1) / kUnitItems;
+    if (i >= n) {
+      uoff[i - n] = urun;
+      urun += (tcnt[i] + kUnitItems - 1) / kUnitItems;
+    }
   }
 }
 
-// Items into tile order.  With the tiles in LDS, the block ranks its items per
-// tile locally and reserves one range per tile with a single global atomic.
+// Interpolated items into (loop, tile) order.  With the keys in LDS, the block
+// ranks its items per key locally and reserves one range per key with a single
+// global atomic.
 __global__ __launch_bounds__(256) void k_tile_scatter(const int2* __restrict__ items,
                                                       const int32_t* __restrict__ total,
+                                                      const uint8_t* __restrict__ xflag,
                                                       const int32_t* __restrict__ bounds,
                                                       int32_t stride, int32_t T, int32_t ntiles,
                                                       int32_t nch,
@@ -1929,33 +2280,29 @@ __global__ __launch_bounds__(256) void k_tile_scatter(const int2* __restrict__ i
                                                       int32_t* __restrict__ tcur,
                                                       int32_t* __restrict__ tile_items) {
   __shared__ int32_t h[kTileHist];
-  const bool local = ntiles <= kTileHist;
+  const int nk = 2 * ntiles;
+  const bool local = nk <= kTileHist;
   const int W = total[0];
   if (!local) {
     for (int w = blockIdx.x * blockDim.x + threadIdx.x; w < W; w += gridDim.x * blockDim.x) {
-      const int2 it = items[w];
-      const int p = it.x / stride, l = it.x - p * stride;
-      const int t = item_xtile(bounds[(int64_t)p * (stride + 1) + l], it.y, T, nch, ntiles);
-      tile_items[off[t] + atomicAdd(&tcur[t], 1)] = w;
+      const int t = tile_key(items, xflag, bounds, stride, T, ntiles, nch, w);
+      if (t >= 0) tile_items[off[t] + atomicAdd(&tcur[t], 1)] = w;
     }
     return;
   }
-  for (int i = threadIdx.x; i < ntiles; i += blockDim.x) h[i] = 0;
+  for (int i = threadIdx.x; i < nk; i += blockDim.x) h[i] = 0;
   __syncthreads();
   for (int w = blockIdx.x * blockDim.x + threadIdx.x; w < W; w += gridDim.x * blockDim.x) {
-    const int2 it = items[w];
-    const int p = it.x / stride, l = it.x - p * stride;
-    atomicAdd(&h[item_xtile(bounds[(int64_t)p * (stride + 1) + l], it.y, T, nch, ntiles)], 1);
+    const int t = tile_key(items, xflag, bounds, stride, T, ntiles, nch, w);
+    if (t >= 0) atomicAdd(&h[t], 1);
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < ntiles; i += blockDim.x)    // counts -> reserved bases
+  for (int i = threadIdx.x; i < nk; i += blockDim.x)    // counts -> reserved bases
     if (h[i]) h[i] = off[i] + atomicAdd(&tcur[i], h[i]);
   __syncthreads();
   for (int w = blockIdx.x * blockDim.x + threadIdx.x; w < W; w += gridDim.x * blockDim.x) {
-    const int2 it = items[w];
-    const int p = it.x / stride, l = it.x - p * stride;
-    const int t = item_xtile(bounds[(int64_t)p * (stride + 1) + l], it.y, T, nch, ntiles);
-    tile_items[atomicAdd(&h[t], 1)] = w;
+    const int t = tile_key(items, xflag, bounds, stride, T, ntiles, nch, w);
+    if (t >= 0) tile_items[atomicAdd(&h[t], 1)] = w;
   }
 }
 
@@ -2466,7 +2813,9 @@ void launch_prep(const Grid& g, const double* data, const double* psd, BinData<d
 }
 
 void launch_max(const double* u, int64_t n, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_max, dim3(1), dim3(1024), 0, s, u, n, out);
+  auto* bits = reinterpret_cast<unsigned long long*>(out);
+  hipLaunchKernelGGL(k_zero64, dim3(1), dim3(64), 0, s, bits);
+  hipLaunchKernelGGL(k_max, dim3(1024), dim3(256), 0, s, u, n, bits);
 }
 
 void launch_scale(const Grid& g, const double* umax, BinData<double> b, BinData<float> b32,
@@ -2496,39 +2845,59 @@ int interp_max_tile(bool mixed) { return mixed ? kMaxTileMixed : kMaxTileFp64; }
 void launch_eval(bool mixed, bool interp, double refine_budget, const Grid& g,
                  int64_t n_particles, int32_t stride, int32_t chunk, const WorkSpace& ws,
                  BinData<double> b, BinData<float> b32, const double* ek, int blocks,
-                 hipStream_t s, hipEvent_t* ev_main, const UModel& um) {
+                 hipStream_t s, hipEvent_t* ev_main, const UModel& um,
+                 const Spectra<double>& s64, const Spectra<float>& s32) {
   const int32_t* sel = nullptr;
   const int32_t* nsel = nullptr;
   if (!interp) hipLaunchKernelGGL(k_copy_count, dim3(1), dim3(64), 0, s, ws.total, ws.ndirect);
   if (interp) {
     const int32_t ntiles = (int32_t)((g.nbins + chunk - 1) / chunk) * g.chan.n;   // all channels
-    hipLaunchKernelGGL(k_tile_zero, dim3(nblk(ntiles, 256)), dim3(256), 0, s, ws.tcnt, ws.tcur,
-                       ntiles, ws.tile_ctr);
-    hipLaunchKernelGGL(k_tile_count, dim3(1024), dim3(256), 0, s, ws.items, ws.total, ws.bounds,
-                       stride, chunk, ntiles, g.chan.n, ws.tcnt);
-    hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(1024), 0, s, ws.tcnt, ntiles, ws.toff, ws.uoff);
-    hipLaunchKernelGGL(k_tile_scatter, dim3(1024), dim3(256), 0, s, ws.items, ws.total, ws.bounds,
-                       stride, chunk, ntiles, g.chan.n, ws.toff, ws.tcur, ws.tile_items);
+    hipLaunchKernelGGL(k_tile_zero, dim3(nblk(2 * ntiles, 256)), dim3(256), 0, s, ws.tcnt, ws.tcur,
+                       2 * ntiles, ws.tile_ctr);
+    // The block loop needs tiles of whole blocks (the items inside a partition
+    // then have no partial ones).
+    SpecShape sp{};
+    const int32_t L = mixed ? s32.L : s64.L;
+    if (L > 0 && chunk % L == 0)
+      sp = mixed ? SpecShape{L, s32.Q, s32.nslots, s32.nblk, kSpecPsiMixed}
+                 : SpecShape{L, s64.Q, s64.nslots, s64.nblk, kSpecPsiFp64};
     {
       const bool tab = g.orb.coef != nullptr;
       auto nodes = mixed ? (tab ? k_interp_nodes<true, true> : k_interp_nodes<true, false>)
                          : (tab ? k_interp_nodes<false, true> : k_interp_nodes<false, false>);
       hipLaunchKernelGGL(nodes, dim3(blocks), dim3(256), 0, s, g, ws.pc, ws.bounds, stride,
                          ws.items, ws.total, chunk, ek, ws.rec, ws.xflag, ws.xerr, ws.direct,
-                         ws.ndirect, um, ws.partials);
+                         ws.ndirect, um, ws.partials, sp);
+    }
+    hipLaunchKernelGGL(k_tile_count, dim3(1024), dim3(256), 0, s, ws.items, ws.total, ws.xflag,
+                       ws.bounds, stride, chunk, ntiles, g.chan.n, ws.tcnt);
+    hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(1024), 0, s, ws.tcnt, ntiles, ws.toff, ws.uoff);
+    hipLaunchKernelGGL(k_tile_scatter, dim3(1024), dim3(256), 0, s, ws.items, ws.total, ws.xflag,
+                       ws.bounds, stride, chunk, ntiles, g.chan.n, ws.toff, ws.tcur,
+                       ws.tile_items);
+    if (ev_main) (void)hipEventRecord(ev_main[0], s);
+    if (sp.L > 0) {
+      const int64_t ng = (int64_t)n_particles * stride * g.chan.n;
+      const int eb = (int)std::min<int64_t>((2 * ng + 15) / 16, 8 * (int64_t)blocks);
+      const int bb = (8 * blocks + 7) & ~7;      // a multiple of the XCD count
+      if (mixed) {
+        hipLaunchKernelGGL(k_eval_blocks<true>, dim3(bb), dim3(256), 0, s, s32, ws.tile_items,
+                           ws.toff + ntiles, ws.rec, ws.partials);
+        hipLaunchKernelGGL(k_eval_edges<true>, dim3(eb), dim3(256), 0, s, g, sp.L, sp.nblk, ng,
+                           ws.cnt, ws.off, ws.xflag, b32.wr, b32.wi, ws.rec, ws.partials);
+      } else {
+        hipLaunchKernelGGL(k_eval_blocks<false>, dim3(bb), dim3(256), 0, s, s64, ws.tile_items,
+                           ws.toff + ntiles, ws.rec, ws.partials);
+        hipLaunchKernelGGL(k_eval_edges<false>, dim3(eb), dim3(256), 0, s, g, sp.L, sp.nblk, ng,
+                           ws.cnt, ws.off, ws.xflag, b.wr, b.wi, ws.rec, ws.partials);
+      }
     }
     // w (and e_j on the FP64 path) at the largest tile's stride
     const size_t lds = mixed ? (size_t)kMaxTileMixed * 2 * sizeof(float)
                              : (size_t)kMaxTileFp64 * (2 * sizeof(double) + sizeof(float));
-    if (ev_main) (void)hipEventRecord(ev_main[0], s);
-    if (mixed)
-      hipLaunchKernelGGL(k_eval_interp<true>, dim3(blocks), dim3(256), lds, s, g, chunk,
-                         ws.tile_items, ws.toff, ws.uoff, ntiles, ws.tile_ctr, b.wr, b.wi,
-                         b32.wr, b32.wi, ws.rec, ws.partials);
-    else
-      hipLaunchKernelGGL(k_eval_interp<false>, dim3(blocks), dim3(256), lds, s, g, chunk,
-                         ws.tile_items, ws.toff, ws.uoff, ntiles, ws.tile_ctr, b.wr, b.wi,
-                         b32.wr, b32.wi, ws.rec, ws.partials);
+    hipLaunchKernelGGL(mixed ? k_eval_interp<true> : k_eval_interp<false>, dim3(blocks), dim3(256),
+                       lds, s, g, chunk, ws.tile_items, ws.toff + ntiles, ws.uoff, ntiles,
+                       ws.tile_ctr, b.wr, b.wi, b32.wr, b32.wi, ws.rec, ws.partials);
     if (ev_main) (void)hipEventRecord(ev_main[1], s);
     sel = ws.direct;
     nsel = ws.ndirect;
