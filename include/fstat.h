@@ -105,7 +105,8 @@ typedef struct {
 typedef struct {
   int32_t precision;   /* mask of FSTAT_FP64 | FSTAT_MIXED; 0 = both           */
   uint32_t flags;      /* FSTAT_DEVICE_PTRS: data/psd are device pointers      */
-  int32_t chunk;       /* bins per work item (bin tile); 0 = 2048              */
+  int32_t chunk;       /* bins per work item (bin tile); 0 = 2048, or 2560 FP64
+                          and 5120 mixed where the plan has block spectra   */
   int32_t reserved;
   double refine_budget; /* FP64 interpolating loop: partitions where the
                            interpolation error could move F by more than this
@@ -237,7 +238,8 @@ int fstat_waveform(double T_obs, double df, int64_t k_lo, int64_t nbins, const d
  * n particles; np [n] partition counts (device) with part_stride their
  * maximum, or np NULL and np_uniform for all) for work items of 256, 512,
  * 1024, 2048, 2560, 4096, 4608 and 8192 bins (those above the interpolating
- * loop's LDS tile, 2560 bins FP64 and 4608 mixed, for the exact loop only) and
+ * loop's LDS tile, 2560 bins FP64 and 4608 mixed, for the exact loop only; on
+ * the mixed path of a plan with block spectra also 5120) and
  * persistent grids of 1, 2, 4 times the resident occupancy, keeps
  * the fastest for the precision selected by flags (FSTAT_EVAL_MIXED) in the
  * plan, and returns it.  With FSTAT_AUTOTUNE_MODE it times the exact per-bin

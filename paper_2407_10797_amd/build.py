@@ -12,7 +12,11 @@ OUT = os.path.join(HERE, "libfstat.so")
 SOURCES = ["fstat_kernels.hip", "spectra.hip", "fstat_api.hip", "pso.hip", "mlp.hip", "surrogate.hip", "search.hip", "calib.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # FP64 literals are not hoisted out of the persistent loops: hoisted, they held
+         # up to 90 registers (exact loop 236 -> 166 VGPRs, three waves per SIMD instead of
+         # two; node kernel without spills)
+         "-mllvm", "-disable-machine-licm"]
 
 
 def _compile(src: str, extra: list[str]) -> str:

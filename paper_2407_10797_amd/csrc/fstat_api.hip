@@ -244,7 +244,10 @@ int eval_blocks(fstat_plan_s* P, bool mixed) {
 
 static int check_chunk(const fstat_plan_s* P, bool mixed, bool exact) {
   const int chunk = chunk_for(P, mixed);
-  if (!exact && chunk > interp_max_tile(mixed))
+  // only a size that the caller asked for: the plan's own choices above the
+  // LDS stage go through it in parts
+  const bool given = P->chunk_given && !(mixed && P->chunk_mixed > 0);
+  if (!exact && given && chunk > interp_max_tile(mixed))
     return set_error(FSTAT_EINVAL, "work-item size %d exceeds the LDS tile limit %d (use a smaller "
                      "chunk or FSTAT_EVAL_EXACT)", chunk, interp_max_tile(mixed));
   return FSTAT_OK;
@@ -400,8 +403,10 @@ int fstat_autotune(fstat_plan_t P, const double* params, int64_t n, int32_t np_u
   if (!(flags & FSTAT_AUTOTUNE_FORCE) && tune_cache_get(key, &c, &m, &e) && c >= 64 && m >= 1) {
     // cached
   } else {
-    static const int chunks[] = {256, 512, 1024, 2048, 2560, 4096, 4608, 8192};
+    static const int chunks[] = {256, 512, 1024, 2048, 2560, 4096, 4608, 5120, 8192};
     static const int mults[] = {1, 2, 4};
+    // tiles above the per-bin loop's LDS stage only where the block loop takes the items
+    const int tile_limit = mixed && P->s32.L > 0 ? kSpecChunkMixed : interp_max_tile(mixed);
     double* F = nullptr;
     int rc = hip_check(hipMalloc(&F, sizeof(double) * n), "alloc tune out");
     hipEvent_t e0, e1;
@@ -409,14 +414,15 @@ int fstat_autotune(fstat_plan_t P, const double* params, int64_t n, int32_t np_u
     if (!rc) rc = hip_check(hipEventCreate(&e1), "event");
     const int save_c = P->chunk, save_cm = P->chunk_mixed;
     const int save_m = mixed ? P->grid_mult_mixed : P->grid_mult_fp64;
-    const bool save_p = prefer;
+    const bool save_p = prefer, save_g = P->chunk_given;
+    P->chunk_given = false;
     prefer = false;     // each candidate below runs the loop it names
     // interpolating loop (unless exact is requested), then the exact loop
     // (when requested, or when the mode is tuned as well)
     for (int ex = exact ? 1 : 0; ex <= ((exact || mode) ? 1 : 0) && !rc; ++ex)
       for (int ci = 0; ci < (int)(sizeof(chunks) / sizeof(chunks[0])) && !rc; ++ci)
         for (int mi = 0; mi < 3 && !rc; ++mi) {
-          if (!ex && chunks[ci] > interp_max_tile(mixed)) continue;
+          if (ex ? chunks[ci] == kSpecChunkMixed : chunks[ci] > tile_limit) continue;
           if (mixed) { P->chunk_mixed = chunks[ci]; P->grid_mult_mixed = mults[mi]; }
           else { P->chunk = chunks[ci]; P->grid_mult_fp64 = mults[mi]; }
           double t_min = 1e300;
@@ -437,6 +443,7 @@ int fstat_autotune(fstat_plan_t P, const double* params, int64_t n, int32_t np_u
     P->chunk = save_c; P->chunk_mixed = save_cm;
     if (mixed) P->grid_mult_mixed = save_m; else P->grid_mult_fp64 = save_m;
     prefer = save_p;
+    P->chunk_given = save_g;
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (F) (void)hipFree(F);
@@ -444,7 +451,7 @@ int fstat_autotune(fstat_plan_t P, const double* params, int64_t n, int32_t np_u
     tune_cache_put(key, c, m, e);
   }
   if (mixed) { P->chunk_mixed = c; P->grid_mult_mixed = m; }
-  else { P->chunk = c; P->grid_mult_fp64 = m; }
+  else { P->chunk = c; P->grid_mult_fp64 = m; P->chunk_given = false; }
   if (!exact) prefer = mode && e != 0;
   if (best_chunk) *best_chunk = c;
   if (best_mult) *best_mult = m;
@@ -502,6 +509,7 @@ int fstat_plan_create(fstat_plan_t* out, const fstat_data_desc* d, const fstat_o
   P->grid.chan = chan;
   P->prec = prec;
   P->chunk = chunk;
+  P->chunk_given = opts && opts->chunk > 0;
   P->refine_budget = budget;
   int rc = hip_check(hipGetDevice(&P->device), "hipGetDevice");
   if (!rc) rc = hip_check(hipDeviceGetAttribute(&P->num_cu, hipDeviceAttributeMultiprocessorCount,
@@ -590,6 +598,8 @@ int fstat_plan_create(fstat_plan_t* out, const fstat_data_desc* d, const fstat_o
     fstat_plan_destroy(P);
     return rc;
   }
+  if (!P->chunk_given && P->s64.L) P->chunk = kSpecChunkFp64;
+  if (!P->chunk_given && P->s32.L) P->chunk_mixed = kSpecChunkMixed;
   if (!(prec & FSTAT_FP64)) {
     // the FP64 data are only needed to build the FP32 copies (the exact mixed
     // loop keeps sin, cos(pi f L) in FP64 for its FP64 response)

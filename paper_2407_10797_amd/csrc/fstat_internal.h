@@ -145,6 +145,22 @@ struct PartConst {
 
 enum { kStatusOk = 0, kStatusEmpty = 1, kStatusInvalid = 2 };
 
+// The template's constants of a particle at a wave-uniform address, by scalar
+// loads (read-only memory, constant address space).
+typedef __attribute__((address_space(4))) PartConst kconst_PartConst;
+__device__ __forceinline__ PartConst load_particle(const kconst_PartConst* p) {
+  PartConst P;
+  P.tc = p->tc;
+  P.mc_hi = p->mc_hi; P.mc_lo = p->mc_lo;
+  P.cN_hi = p->cN_hi; P.cN_lo = p->cN_lo; P.c1_hi = p->c1_hi; P.c1_lo = p->c1_lo;
+  P.c15_hi = p->c15_hi; P.c15_lo = p->c15_lo; P.ce_hi = p->ce_hi; P.ce_lo = p->ce_lo;
+  P.c2 = p->c2; P.c5 = p->c5; P.c6 = p->c6; P.a6k = p->a6k; P.b6 = p->b6;
+  P.ln_vfac = p->ln_vfac; P.c5v5 = p->c5v5;
+  for (int i = 0; i < 3; ++i) { P.k[i] = p->k[i]; P.u[i] = p->u[i]; P.v[i] = p->v[i]; }
+  P.sur = p->sur;
+  return P;
+}
+
 // ---- phase and SPA time -------------------------------------------------------
 // Fractional cycle of Psi(f)/(2 pi) (constant phase offsets dropped: the
 // F-statistic absorbs them) and the SPA time t_f = (1/2 pi) dPsi/df.

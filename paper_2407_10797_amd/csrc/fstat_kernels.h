@@ -93,6 +93,12 @@ struct Spectra {
   int32_t nslots = 0;    // slopes kept: 0 .. T_obs df Q
   int32_t nblk = 0;      // whole blocks per channel
 };
+// Default work-item size of a plan with spectra.  Longer items spread a node evaluation over
+// more bins until the degree-9 interpolants miss their end points and the exact loop takes
+// the item (4096 x 64 on 7.1M bins, FP64: 4.01, 3.69, 3.73, 5.31 ms at 2048, 2560, 4096, 5120
+// bins; mixed, with its wider tolerance: 2.94, 2.61, 2.17, 2.06, 3.13 at .. 5120, 8192).
+constexpr int kSpecChunkFp64 = 2560;
+constexpr int kSpecChunkMixed = 5120;
 constexpr double kSpecMaxSlope = 1.001;   // largest T_obs df [cycles per bin] with spectra
 // Block size for a data set of nbins bins per channel, 0 for none.
 int spectra_block(bool mixed, int64_t nbins);

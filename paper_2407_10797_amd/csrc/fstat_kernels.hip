@@ -953,6 +953,9 @@ __global__ __launch_bounds__(256, 2) void k_interp_nodes(Grid g,
   const int lane = threadIdx.x & 63;
   const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int nwaves = (gridDim.x * blockDim.x) >> 6;
+  const int W = total[0];
+  const int G = (W + kItemsWave - 1) / kItemsWave;
+  if (blockIdx.x * (blockDim.x >> 6) >= G) return;   // more blocks than groups of items
   __shared__ double2 s_tab[kSinTab];              // coarse angles of the template's sin/cos
   // the row tables in LDS (the coefficient loop reads one entry of each per
   // node and lane; from the constant tables each read is a vector memory load)
@@ -974,9 +977,8 @@ __global__ __launch_bounds__(256, 2) void k_interp_nodes(Grid g,
       s_rt[0][kn][kk] = c_row4[kn][kk];
     }
   }
-  fill_sincos_table(s_tab);                       // ends with a block barrier
-  const int W = total[0];
-  const int G = (W + kItemsWave - 1) / kItemsWave;
+  for (int i = threadIdx.x; i < kSinTab; i += blockDim.x) s_tab[i] = c_sincos[i];
+  __syncthreads();
   const int q = min(lane / kLanesItem, kItemsWave - 1);
   const int k = min(lane - q * kLanesItem, kLanesItem - 1);
   const int base = q * kLanesItem;
@@ -984,7 +986,6 @@ __global__ __launch_bounds__(256, 2) void k_interp_nodes(Grid g,
     const int w = min(grp * kItemsWave + q, W - 1);
     const int2 it = items[w];
     const int p = it.x / stride, l = it.x - p * stride;
-    const PartConst& P = pc[p];
     const int32_t* bp = bounds + (int64_t)p * (stride + 1);
     int ct, ch;
     item_split(it.y, g.chan.n, ct, ch);
@@ -1000,19 +1001,31 @@ __global__ __launch_bounds__(256, 2) void k_interp_nodes(Grid g,
       }
       continue;
     }
-    const double* ekq = (ek && P.sur) ? ek + 8 * (int64_t)it.x : nullptr;
     const double sk = k < kCheb ? c_cheb_s[k] : (k == kCheb ? -1.0 : 1.0);
     const double mk = (sk + 1.0) * 0.5 * (double)(nb > 1 ? nb - 1 : 0);
     // exact frequency (k_lo + b0 + mk) df of the node, as double-double
     const dd f = dd_add(two_prod((double)(g.k_lo + b0), g.df), two_prod(mk, g.df));
     double v[5], v0lo;
     dd ph;
-    if constexpr (MIXED)
-      ph = dd{template_node_fp64(P, f.hi, ekq, v[1], v[2], v[3], v[4], g.chan.code[ch],
-                                 TAB ? &g.orb : nullptr, s_tab), 0.0};
-    else
-      ph = template_node(P, f, ekq, v[1], v[2], v[3], v[4], g.chan.code[ch],
-                         TAB ? &g.orb : nullptr, s_tab);
+    // the lanes of one particle at a time (nearly always all of them): its
+    // constants come through the scalar cache into scalar registers
+    for (uint64_t todo = __ballot(true); todo != 0;) {
+      const int pu = __builtin_amdgcn_readlane(p, __builtin_ctzll(todo));
+      int ps = pu;
+      asm("" : "+s"(ps));   // not p itself: the compiler would put it back where they are equal
+      const kconst_PartConst* kp = (const kconst_PartConst*)(uintptr_t)(pc + ps);
+      todo &= ~__ballot(p == pu);
+      if (p == pu) {
+        const PartConst P = load_particle(kp);
+        const double* ekq = (ek && P.sur) ? ek + 8 * (int64_t)it.x : nullptr;
+        if constexpr (MIXED)
+          ph = dd{template_node_fp64(P, f.hi, ekq, v[1], v[2], v[3], v[4], g.chan.code[ch],
+                                     TAB ? &g.orb : nullptr, s_tab), 0.0};
+        else
+          ph = template_node(P, f, ekq, v[1], v[2], v[3], v[4], g.chan.code[ch],
+                             TAB ? &g.orb : nullptr, s_tab);
+      }
+    }
     const double p0h = __shfl(ph.hi, base + kCheb, 64);
     const double p0l = __shfl(ph.lo, base + kCheb, 64);
     const double peh = __shfl(ph.hi, base + kCheb + 1, 64);
@@ -1270,32 +1283,42 @@ __global__ __launch_bounds__(256) void k_eval_interp(Grid g,
   const int wv = threadIdx.x >> 6;
   const int nwv = blockDim.x >> 6;
   const int nunits = unit_off[ntiles];
-  for (;;) {
-    // next unit (dynamic): up to kUnitItems items of one tile
-    if (threadIdx.x == 0) {
-      const int u = atomicAdd(tile_ctr, 1);
-      int t = -1, first = 0, count = 0;
-      if (u < nunits) {
-        int lo = 0, hi = ntiles;                     // last tile with unit_off[t] <= u
-        while (hi - lo > 1) {
-          const int mid = (lo + hi) >> 1;
-          if (unit_off[mid] <= u) lo = mid; else hi = mid;
+  // The current unit: its items, the channel's data offset, and the tile's bins
+  // not yet staged.  Tiles above the LDS stage go through it in parts; a wave
+  // takes the same items in each and adds to their sums.
+  int i0 = 0, cnt = 0, j0 = 0, j_end = 0;
+  int64_t co = 0;
+  for (;; j0 += TS) {
+    if (j0 >= j_end) {
+      // next unit (dynamic): up to kUnitItems items of one tile
+      if (threadIdx.x == 0) {
+        const int u = atomicAdd(tile_ctr, 1);
+        int t = -1, first = 0, count = 0;
+        if (u < nunits) {
+          int lo = 0, hi = ntiles;                   // last tile with unit_off[t] <= u
+          while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (unit_off[mid] <= u) lo = mid; else hi = mid;
+          }
+          t = lo;
+          first = tile_off[t] + (u - unit_off[t]) * kUnitItems;
+          count = min(kUnitItems, tile_off[t + 1] - first);
         }
-        t = lo;
-        first = tile_off[t] + (u - unit_off[t]) * kUnitItems;
-        count = min(kUnitItems, tile_off[t + 1] - first);
+        s_unit[0] = t; s_unit[1] = first; s_unit[2] = count;
       }
-      s_unit[0] = t; s_unit[1] = first; s_unit[2] = count;
+      __syncthreads();
+      const int tx = s_unit[0];
+      if (tx < 0) break;
+      // tiles of all channels are numbered channel by channel
+      const int ntpc = (int)((g.nbins + T - 1) / T);
+      const int tch = tx / ntpc, t = tx - tch * ntpc;
+      co = (int64_t)tch * g.nbins;
+      i0 = s_unit[1];
+      cnt = s_unit[2];
+      j0 = t * T;
+      j_end = (int)min((int64_t)j0 + T, g.nbins);
     }
-    __syncthreads();
-    const int tx = s_unit[0];
-    if (tx < 0) break;
-    // tiles of all channels are numbered channel by channel
-    const int ntpc = (int)((g.nbins + T - 1) / T);
-    const int tch = tx / ntpc, t = tx - tch * ntpc;
-    const int64_t co = (int64_t)tch * g.nbins;
-    const int j0 = t * T;
-    const int nt = min((int64_t)T, g.nbins - j0);
+    const int nt = min(TS, j_end - j0);
     for (int i = threadIdx.x; i < nt; i += blockDim.x) {
       s_wr[i] = gwr[co + j0 + i];
       s_wi[i] = gwi[co + j0 + i];
@@ -1307,8 +1330,6 @@ __global__ __launch_bounds__(256) void k_eval_interp(Grid g,
       }
     }
     __syncthreads();
-    const int i0 = s_unit[1];
-    const int cnt = s_unit[2];
     typedef RecLayout<MIXED> L;
     double* R = s_rec[wv];
     // Each item's record holds all the loop needs of it; a wave loads the next
@@ -1325,8 +1346,14 @@ __global__ __launch_bounds__(256) void k_eval_interp(Grid g,
       const int idn = idx + nwv;
       wn = idn < cnt ? tile_items[i0 + idn] : 0;
       rv = (idn < cnt && lane < kRec) ? rec[(int64_t)wn * kRec + lane] : 0.0;
-      const int e0 = rec_int(R[L::tail + 3], 1) - j0;   // LDS offset of the item's first bin
-      const int nb = rec_int(R[L::tail + 4], 0);
+      const int b0 = rec_int(R[L::tail + 3], 1);
+      const int e0 = max(b0 - j0, 0);             // LDS offset of the item's first bin here
+      const int mo = e0 + j0 - b0;                // that bin's number in the item
+      const int nb = min(b0 + rec_int(R[L::tail + 4], 0), j0 + nt) - (b0 + mo);   // bins here
+      if (nb <= 0) {
+        __builtin_amdgcn_wave_barrier();
+        continue;
+      }
       double cR[kCheb];
 #pragma unroll
       for (int n = 0; n < kCheb; ++n) cR[n] = R[n];
@@ -1356,8 +1383,9 @@ __global__ __launch_bounds__(256) void k_eval_interp(Grid g,
         // takes the direct loop when phi can leave the range of its series or
         // the neglected D_5 could move the phase by more than kRecTrunc.
         const int Lr = ((nb + 63) >> 6) | 1;
-        const int m0 = lane * Lr;
-        const int cnt = min(max(nb - m0, 0), Lr);
+        const int r0 = lane * Lr;                 // the run's first bin here, in the item
+        const int m0 = mo + r0;
+        const int cnt = min(max(nb - r0, 0), Lr);
         double E0r = 0.0, E0i = 0.0, E1r = 0.0, E1i = 0.0, th2 = 0.0, th3 = 0.0, th4 = 0.0;
         bool use_rec = Lr >= kRecMinRun;
         if (use_rec) {
@@ -1397,7 +1425,8 @@ __global__ __launch_bounds__(256) void k_eval_interp(Grid g,
           use_rec = __all(ok);
         }
         if (lane == 0 && use_rec)                      // for fstat_interp_stats
-          *reinterpret_cast<int*>(rec + (int64_t)w * kRec + L::tail + 3) = flags + 1;
+          *reinterpret_cast<int*>(rec + (int64_t)w * kRec + L::tail + 3) =
+              (flags & ~255) | kRecBinsShort;
         // DT: degree of the transfer interpolants (5, 7 or 9)
         auto loop = [&](auto dt) {
           constexpr int DT = decltype(dt)::value;
@@ -1453,7 +1482,7 @@ __global__ __launch_bounds__(256) void k_eval_interp(Grid g,
               };
               // the first bin sets the moments (lanes without bins take w = 0);
               // the rest of an odd run goes two bins per pass
-              const int ib = e0 + m0;
+              const int ib = e0 + r0;
               const bool any = cnt > 0;
               rec_bin(First{}, any ? s_wr[ib] : 0.0, any ? s_wi[ib] : 0.0, any ? s_e[ib] : 0.0f);
               int t = 1;
@@ -1516,7 +1545,7 @@ __global__ __launch_bounds__(256) void k_eval_interp(Grid g,
                 }
               };
               auto one_bin = [&](int mi, double a, double b, double ej) {
-                const double m = (double)mi;
+                const double m = (double)(mo + mi);
                 const double s = fma(alpha, m, -1.0);
                 const double s2 = s * s, s4 = s2 * s2, s8 = s4 * s4;
                 const double ph = fma(Bp, m, estrin9(cR, s, s2, s4, s8)) + fma(kB, ej, A);
@@ -1555,7 +1584,10 @@ __global__ __launch_bounds__(256) void k_eval_interp(Grid g,
             }
             __builtin_amdgcn_wave_barrier();   // the slot is rewritten for the next item
             const double tot = wave_sum4(acc, lane, idx);
-            if ((lane & 15) == 0) partials[(int64_t)w * 8 + idx] = tot;
+            if ((lane & 15) == 0) {
+              double* o = partials + (int64_t)w * 8 + idx;
+              *o = mo > 0 ? *o + tot : tot;
+            }
           }
         };
         using D5 = std::integral_constant<int, 5>;
@@ -1581,8 +1613,9 @@ __global__ __launch_bounds__(256) void k_eval_interp(Grid g,
         // mixed path's bar.  The transfer degree is kDegT, or kDegTLow where the
         // node kernel found it enough; the coefficients are applied in FP64.
         const int Lr = ((nb + 63) >> 6) | 1;
-        const int m0 = lane * Lr;
-        const int cnt = min(max(nb - m0, 0), Lr);
+        const int r0 = lane * Lr;                 // the run's first bin here, in the item
+        const int m0 = mo + r0;
+        const int cnt = min(max(nb - r0, 0), Lr);
         double dd[kCheb];                 // dd[j]: j-th forward difference (j >= 1)
         double ph;
         bool trunc;
@@ -1634,7 +1667,8 @@ __global__ __launch_bounds__(256) void k_eval_interp(Grid g,
           ph -= rint(ph);
         }
         if (lane == 0 && trunc)                        // for fstat_interp_stats
-          *reinterpret_cast<int*>(rec + (int64_t)w * kRec + L::tail + 3) = flags + 1;
+          *reinterpret_cast<int*>(rec + (int64_t)w * kRec + L::tail + 3) =
+              (flags & ~255) | kRecBinsShort;
         // D: transfer degree; ND: forward differences carried (the last held)
         auto loop = [&](auto dt, auto ndt) {
           constexpr int D = decltype(dt)::value;
@@ -1667,7 +1701,7 @@ __global__ __launch_bounds__(256) void k_eval_interp(Grid g,
           using Next = std::false_type;
           // the first bin sets the moments (lanes without bins take w = 0);
           // the rest of an odd run goes two bins per pass
-          const int ib = e0 + m0;
+          const int ib = e0 + r0;
           const bool any = cnt > 0;
           bin(First{}, any ? s_wr[ib] : 0.0f, any ? s_wi[ib] : 0.0f);
           int t = 1;
@@ -1721,7 +1755,10 @@ __global__ __launch_bounds__(256) void k_eval_interp(Grid g,
           }
           __builtin_amdgcn_wave_barrier();   // the slot is rewritten for the next item
           const double tot = wave_sum4(red, lane, idx);
-          if ((lane & 15) == 0) partials[(int64_t)w * 8 + idx] = tot;
+          if ((lane & 15) == 0) {
+            double* o = partials + (int64_t)w * 8 + idx;
+            *o = mo > 0 ? *o + tot : tot;
+          }
         };
         using DLow = std::integral_constant<int, kDegTLow>;
         using DHigh = std::integral_constant<int, kDegT>;
@@ -1736,7 +1773,7 @@ __global__ __launch_bounds__(256) void k_eval_interp(Grid g,
         }
       }
     }
-    __syncthreads();   // every wave is done with this unit's LDS and s_unit
+    __syncthreads();   // every wave is done with this stage's LDS and s_unit
   }
 }
 
@@ -2865,7 +2902,7 @@ void launch_eval(bool mixed, bool interp, double refine_budget, const Grid& g,
       const bool tab = g.orb.coef != nullptr;
       auto nodes = mixed ? (tab ? k_interp_nodes<true, true> : k_interp_nodes<true, false>)
                          : (tab ? k_interp_nodes<false, true> : k_interp_nodes<false, false>);
-      hipLaunchKernelGGL(nodes, dim3(blocks), dim3(256), 0, s, g, ws.pc, ws.bounds, stride,
+      hipLaunchKernelGGL(nodes, dim3(8 * blocks), dim3(256), 0, s, g, ws.pc, ws.bounds, stride,
                          ws.items, ws.total, chunk, ek, ws.rec, ws.xflag, ws.xerr, ws.direct,
                          ws.ndirect, um, ws.partials, sp);
     }
