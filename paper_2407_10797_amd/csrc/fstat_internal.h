@@ -84,11 +84,6 @@ __host__ __device__ __forceinline__ dd dd_div(dd a, dd b) {
   double q2 = r.hi / b.hi;
   return quick_two_sum(q1, q2);
 }
-// rational p/q as double-double
-__host__ __device__ __forceinline__ dd dd_ratio(double p, double q) {
-  FSTAT_NO_CONTRACT
-  return dd_div(dd{p, 0.0}, dd{q, 0.0});
-}
 // x^(1/n), x > 0, as double-double: a double estimate w0 and one Newton step
 // on w^n = x (quadratic convergence from ~1 ulp).
 __host__ __device__ __forceinline__ dd dd_root(dd x, int n, double w0) {
@@ -306,19 +301,22 @@ __host__ __device__ inline void fill_constants(PartConst& P, const double* th) {
   dd d2 = two_prod(dmu, dmu);
   dd one_m = dd_add(dd{1.0, 0.0}, dd{-d2.hi, -d2.lo});
   dd eta = dd{one_m.hi * 0.25, one_m.lo * 0.25};      // (1 - dmu^2)/4
+  // constants of the series as double-double, rounded from 400 bits
   const dd pi = {3.141592653589793116e+00, 1.2246467991473532e-16};
-  dd pi13 = dd_root(pi, 3, cbrt(pi.hi));
+  const dd pi13 = {1.46459188756152336e+00, -1.01504731086581765e-16};       // pi^{1/3}
+  const dd cN = {5.53539090143848902e-04, -4.81692159938612742e-20};         // 3 / (256 pi^{8/3})
+  const dd r2a = {4.91402116402116373e+00, 2.86660759797394900e-16};         // 3715 / 756
+  const dd r2b = {6.11111111111111072e+00, 3.94745964311166748e-16};         // 55 / 9
+  const dd rec = {-1.61080711354309170e+00, 4.00956058140959402e-17};        // -2355 / 1462
   dd ie5 = dd_root(dd_div(dd{1.0, 0.0}, eta), 5, pow(eta.hi, -0.2));   // eta^{-1/5}
   dd vfac = dd_mul(pi13, ie5);                        // v = vfac (Mc f)^{1/3}
   dd vf2 = dd_mul(vfac, vfac), vf3 = dd_mul(vf2, vfac);
-  dd pi2 = dd_mul(pi, pi);
-  dd cN = dd_div(dd{3.0, 0.0}, dd_mul_d(dd_mul(pi2, dd_mul(pi13, pi13)), 256.0));
-  dd a2 = dd_add(dd_ratio(3715.0, 756.0), dd_mul(dd_ratio(55.0, 9.0), eta));
+  dd a2 = dd_add(r2a, dd_mul(r2b, eta));
   dd c1 = dd_mul(dd_mul(cN, a2), vf2);
   dd c15 = dd_mul(dd_mul(cN, dd_mul_d(pi, -16.0)), vf3);
   dd z = dd_mul_d(m, kF0Ecc);                         // f0 Mc
   dd z19 = dd_mul(dd_mul(z, z), dd_root(z, 9, pow(z.hi, 1.0 / 9.0)));   // (f0 Mc)^{19/9}
-  dd ce = dd_mul(dd_mul(cN, dd_ratio(-2355.0, 1462.0)), dd_mul(two_prod(e0, e0), z19));
+  dd ce = dd_mul(dd_mul(cN, rec), dd_mul(two_prod(e0, e0), z19));
   P.cN_hi = cN.hi; P.cN_lo = cN.lo;
   P.c1_hi = c1.hi; P.c1_lo = c1.lo;
   P.c15_hi = c15.hi; P.c15_lo = c15.lo;
@@ -337,7 +335,7 @@ __host__ __device__ inline void fill_constants(PartConst& P, const double* th) {
   P.c5 = 3.0 * P.c5v5;
   P.c6 = K * vf6;
   P.b6 = -6848.0 / 21.0;
-  P.a6k = a6c + P.b6 * log(4.0);
+  P.a6k = a6c + P.b6 * 1.38629436111989061883;   // ln 4
   P.ln_vfac = log(vf);
   P.ecc_k = -(2355.0 / 1462.0) * e0 * e0;
   P.nn_mc = (mc - 30.0) / 20.0;
