@@ -263,7 +263,8 @@ static int eval_enqueue(fstat_plan_s* P, const WorkSpace& ws, const double* para
   int rc;
   launch_setup(P->grid, params, n, np, np_uniform, stride, chunk, skip, ws, s);
   if (surrogate && (rc = sur_prepare(P, n, stride, s))) return rc;
-  launch_worklist(n * (int64_t)stride, ws, s);
+  launch_worklist(n, stride, ws, exact,
+                  (int32_t)((P->grid.nbins + chunk - 1) / chunk) * P->grid.chan.n, s);
   // profiling: the whole bin-loop stage (e[0], e[3]) and its main kernel (e[1], e[2])
   std::array<hipEvent_t, 4> ev = {nullptr, nullptr, nullptr, nullptr};
   const bool prof = P->profile && allow_profile;
@@ -845,9 +846,19 @@ int fstat_waveform(double T_obs, double df, int64_t k_lo, int64_t nbins, const d
   g.chan.code[0] = code;
   WorkSpace ws{};
   double *dpar = nullptr, *damp = nullptr, *dout = nullptr;
-  int rc = dev_alloc(&ws.pc, 1, "alloc pc");
-  if (!rc) rc = dev_alloc(&ws.bounds, 2, "alloc bounds");
-  if (!rc) rc = dev_alloc(&ws.cnt, 1, "alloc cnt");
+  // the set-up of one particle with one partition, in one buffer
+  struct Setup {
+    PartConst pc;
+    double Fl[1];
+    int32_t bounds[2], cnt[1];
+  }* w = nullptr;
+  int rc = dev_alloc(&w, 1, "alloc waveform set-up");
+  if (!rc) {
+    ws.pc = &w->pc;
+    ws.Fl = w->Fl;
+    ws.bounds = w->bounds;
+    ws.cnt = w->cnt;
+  }
   const double* pp = params6;
   const double* ap = amps4;
   double* op = out;
@@ -860,14 +871,14 @@ int fstat_waveform(double T_obs, double df, int64_t k_lo, int64_t nbins, const d
     pp = dpar; ap = damp; op = dout;
   }
   if (!rc) {
-      launch_setup(g, pp, 1, nullptr, 1, 1, 1 << 24, nullptr, ws, s);
+    launch_setup(g, pp, 1, nullptr, 1, 1, 1 << 24, nullptr, ws, s);
     launch_waveform(g, ws.pc, ap, op, s);
     rc = hip_check(hipGetLastError(), "waveform launch");
   }
   if (!rc && !dev)
     rc = hip_check(hipMemcpyAsync(out, dout, sizeof(double) * 2 * nbins, hipMemcpyDeviceToHost, s), "copy out");
   if (!rc) rc = hip_check(hipStreamSynchronize(s), "waveform");
-  dev_free(ws.pc); dev_free(ws.bounds); dev_free(ws.cnt);
+  dev_free(w);
   dev_free(dpar); dev_free(damp); dev_free(dout);
   return rc;
 }

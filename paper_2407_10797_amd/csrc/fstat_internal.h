@@ -301,10 +301,10 @@ __host__ __device__ inline void fill_constants(PartConst& P, const double* th) {
   dd d2 = two_prod(dmu, dmu);
   dd one_m = dd_add(dd{1.0, 0.0}, dd{-d2.hi, -d2.lo});
   dd eta = dd{one_m.hi * 0.25, one_m.lo * 0.25};      // (1 - dmu^2)/4
-  // constants of the series as double-double, rounded from 400 bits
+  // constants of the series as double-double
   const dd pi = {3.141592653589793116e+00, 1.2246467991473532e-16};
-  const dd pi13 = {1.46459188756152336e+00, -1.01504731086581765e-16};       // pi^{1/3}
-  const dd cN = {5.53539090143848902e-04, -4.81692159938612742e-20};         // 3 / (256 pi^{8/3})
+  const dd pi13 = {1.46459188756152336e+00, -1.01504731086581778e-16};       // pi^{1/3}
+  const dd cN = {5.53539090143848902e-04, -4.81692159938612682e-20};         // 3 / (256 pi^{8/3})
   const dd r2a = {4.91402116402116373e+00, 2.86660759797394900e-16};         // 3715 / 756
   const dd r2b = {6.11111111111111072e+00, 3.94745964311166748e-16};         // 55 / 9
   const dd rec = {-1.61080711354309170e+00, 4.00956058140959402e-17};        // -2355 / 1462
@@ -408,17 +408,6 @@ __device__ __forceinline__ void sincos_tab(double r, const double2* tab, double&
   const double cl = fma(z, pc, 1.0);
   s = fma(e.x, cl, e.y * sl);
   c = fma(e.y, cl, -(e.x * sl));
-}
-
-// (sin, cos)(2 pi k / kSinTab) into a block's LDS table; every thread of the
-// block calls it (it ends with a block barrier).
-__device__ __forceinline__ void fill_sincos_table(double2* tab) {
-  for (int k = threadIdx.x; k < kSinTab; k += blockDim.x) {
-    double sv, cv;
-    sincospi(2.0 * (double)k / (double)kSinTab, &sv, &cv);
-    tab[k] = make_double2(sv, cv);
-  }
-  __syncthreads();
 }
 
 // sin(pi x), cos(pi x): from the table when one is given, else the library.
@@ -705,30 +694,44 @@ __device__ __forceinline__ double template_node_fp64(const PartConst& P, double 
 // acc = {Re Z+, Im Z+, Re Zx, Im Zx, P, Q, Re R, Im R};  F = 1/2 z^H H^{-1} z,
 // H = [[P, conj R], [R, Q]] is the complex form of the real 4x4 M of
 // Eq. coherent_F_stat; rank-deficient H uses the pseudo-inverse.
+// The fused operations are written out: left to the compiler, their choice
+// (above all in det = PQ - |R|^2) changes with the surrounding code, and F with
+// it by eps cond(M).
+struct Herm {
+  double lp, det;        // larger eigenvalue, determinant
+};
+__host__ __device__ __forceinline__ Herm herm_of(double P, double Q, double rr, double ri) {
+  FSTAT_NO_CONTRACT
+  const double hd = 0.5 * (P - Q), rr2 = rr * rr;
+  const double rad = sqrt(__builtin_fma(ri, ri, __builtin_fma(hd, hd, rr2)));
+  return {__builtin_fma(0.5, P + Q, rad), __builtin_fma(P, Q, -(rr2 + ri * ri))};
+}
 __host__ __device__ __forceinline__ double solve_partition(const double* a) {
-  double zpr = a[0], zpi = a[1], zxr = a[2], zxi = a[3];
-  double P = a[4], Q = a[5], rr = a[6], ri = a[7];
-  double hs = 0.5 * (P + Q), hd = 0.5 * (P - Q);
-  double rad = sqrt(hd * hd + rr * rr + ri * ri);
-  double lp = hs + rad;
+  FSTAT_NO_CONTRACT
+  const double zpr = a[0], zpi = a[1], zxr = a[2], zxi = a[3];
+  const double P = a[4], Q = a[5], rr = a[6], ri = a[7];
+  const Herm h = herm_of(P, Q, rr, ri);
+  const double lp = h.lp, det = h.det;
   if (!(lp > 0.0)) return 0.0;
-  double det = P * Q - (rr * rr + ri * ri);
-  double lm = det / lp;
-  double zp2 = zpr * zpr + zpi * zpi, zx2 = zxr * zxr + zxi * zxi;
+  const double lm = det / lp;
   if (lm > kRankCut * lp) {
-    double cross = (rr * zpr - ri * zpi) * zxr + (rr * zpi + ri * zpr) * zxi;
-    return (Q * zp2 + P * zx2 - 2.0 * cross) / (2.0 * det);
+    const double zp2 = __builtin_fma(zpr, zpr, zpi * zpi), zx2 = __builtin_fma(zxr, zxr, zxi * zxi);
+    const double cr = __builtin_fma(zpr, rr, -(zpi * ri));        // Re, Im of R z_+
+    const double ci = __builtin_fma(zpi, rr, zpr * ri);
+    const double cross = __builtin_fma(zxr, cr, zxi * ci);
+    return __builtin_fma(-2.0, cross, __builtin_fma(Q, zp2, P * zx2)) / (det + det);
   }
   // rank one: eigenvector of lambda_+ ; pick the better-conditioned form
   double v1r, v1i, v2r, v2i;
   if (P >= Q) { v1r = lp - Q; v1i = 0.0; v2r = rr; v2i = ri; }      // (lp - Q, R)
   else        { v1r = rr; v1i = -ri; v2r = lp - P; v2i = 0.0; }     // (conj R, lp - P)
-  double n2 = v1r * v1r + v1i * v1i + v2r * v2r + v2i * v2i;
+  const double n2 =
+      __builtin_fma(v2i, v2i, v2r * v2r + __builtin_fma(v1i, v1i, v1r * v1r));
   if (!(n2 > 0.0)) return 0.0;
   // v^H z
-  double pr = v1r * zpr + v1i * zpi + v2r * zxr + v2i * zxi;
-  double pi = v1r * zpi - v1i * zpr + v2r * zxi - v2i * zxr;
-  return 0.5 * (pr * pr + pi * pi) / (lp * n2);
+  const double pr = __builtin_fma(v2i, zxi, __builtin_fma(v2r, zxr, __builtin_fma(v1i, zpi, v1r * zpr)));
+  const double pi = __builtin_fma(-v2i, zxr, __builtin_fma(v2r, zxi, __builtin_fma(v1r, zpi, -(v1i * zpr))));
+  return 0.5 * __builtin_fma(pr, pr, pi * pi) / (lp * n2);
 }
 
 // ---- maximum-likelihood amplitudes of a partition (Eq. aandMN3) -------------
@@ -738,37 +741,41 @@ __host__ __device__ __forceinline__ double solve_partition(const double* a) {
 // pseudo-inverse keeps the lambda_+ eigendirection only (the minimum-norm
 // maximiser).  acc as for solve_partition; out {Re, Im} beta_+, {Re, Im} beta_x.
 __host__ __device__ __forceinline__ void solve_beta(const double* a, double* out) {
-  double zpr = a[0], zpi = a[1], zxr = a[2], zxi = a[3];
-  double P = a[4], Q = a[5], rr = a[6], ri = a[7];
+  FSTAT_NO_CONTRACT
+  const double zpr = a[0], zpi = a[1], zxr = a[2], zxi = a[3];
+  const double P = a[4], Q = a[5], rr = a[6], ri = a[7];
   for (int k = 0; k < 4; ++k) out[k] = 0.0;
-  double hs = 0.5 * (P + Q), hd = 0.5 * (P - Q);
-  double rad = sqrt(hd * hd + rr * rr + ri * ri);
-  double lp = hs + rad;
+  const Herm h = herm_of(P, Q, rr, ri);
+  const double lp = h.lp, det = h.det;
   if (!(lp > 0.0)) return;
-  double det = P * Q - (rr * rr + ri * ri);
-  double lm = det / lp;
+  const double lm = det / lp;
   if (lm > kRankCut * lp) {
     // H^{-1} = [[Q, -conj R], [-R, P]] / det
-    double cxr = rr * zxr + ri * zxi, cxi = rr * zxi - ri * zxr;   // conj(R) z_x
-    double rpr = rr * zpr - ri * zpi, rpi = rr * zpi + ri * zpr;   // R z_+
-    out[0] = (Q * zpr - cxr) / det;
-    out[1] = (Q * zpi - cxi) / det;
-    out[2] = (P * zxr - rpr) / det;
-    out[3] = (P * zxi - rpi) / det;
+    const double cxr = __builtin_fma(zxr, rr, zxi * ri);      // conj(R) z_x
+    const double cxi = __builtin_fma(zxi, rr, -(zxr * ri));
+    const double rpr = __builtin_fma(zpr, rr, -(zpi * ri));   // R z_+
+    const double rpi = __builtin_fma(zpi, rr, zpr * ri);
+    out[0] = __builtin_fma(zpr, Q, -cxr) / det;
+    out[1] = __builtin_fma(zpi, Q, -cxi) / det;
+    out[2] = __builtin_fma(zxr, P, -rpr) / det;
+    out[3] = __builtin_fma(zxi, P, -rpi) / det;
     return;
   }
   double v1r, v1i, v2r, v2i;
   if (P >= Q) { v1r = lp - Q; v1i = 0.0; v2r = rr; v2i = ri; }
   else        { v1r = rr; v1i = -ri; v2r = lp - P; v2i = 0.0; }
-  double n2 = v1r * v1r + v1i * v1i + v2r * v2r + v2i * v2i;
+  const double n2 =
+      __builtin_fma(v2i, v2i, v2r * v2r + __builtin_fma(v1i, v1i, v1r * v1r));
   if (!(n2 > 0.0)) return;
-  double pr = v1r * zpr + v1i * zpi + v2r * zxr + v2i * zxi;     // v^H z
-  double pi = v1r * zpi - v1i * zpr + v2r * zxi - v2i * zxr;
-  double sr = pr / (lp * n2), si = pi / (lp * n2);
-  out[0] = v1r * sr - v1i * si;
-  out[1] = v1r * si + v1i * sr;
-  out[2] = v2r * sr - v2i * si;
-  out[3] = v2r * si + v2i * sr;
+  // v^H z
+  const double pr = __builtin_fma(v2i, zxi, __builtin_fma(v2r, zxr, __builtin_fma(v1i, zpi, v1r * zpr)));
+  const double pi = __builtin_fma(-v2i, zxr, __builtin_fma(v2r, zxi, __builtin_fma(v1r, zpi, -(v1i * zpr))));
+  const double den = lp * n2;
+  const double sr = pr / den, si = pi / den;
+  out[0] = __builtin_fma(v1r, sr, -(v1i * si));
+  out[1] = __builtin_fma(v1r, si, v1i * sr);
+  out[2] = __builtin_fma(v2r, sr, -(v2i * si));
+  out[3] = __builtin_fma(v2r, si, v2i * sr);
 }
 
 }  // namespace fstat

@@ -61,6 +61,8 @@ struct WorkSpace {
                       // x template (norm-weighted), y M-term quadrature (absolute)
   int32_t* refine;    // [capacity] interpolated items of ill-conditioned partitions
   int32_t* nrefine;   // [1]
+  // items per particle [n]: kept where Fl is written at the evaluation's end
+  int32_t* ptot() const { return reinterpret_cast<int32_t*>(Fl); }
 };
 
 void launch_prep(const Grid& g, const double* data, const double* psd, BinData<double> b,
@@ -71,7 +73,9 @@ void launch_scale(const Grid& g, const double* umax, BinData<double> b, BinData<
 void launch_setup(const Grid& g, const double* params, int64_t n,
                   const int32_t* np, int32_t np_uniform, int32_t stride, int32_t chunk,
                   const uint8_t* skip, const WorkSpace& ws, hipStream_t s);
-void launch_worklist(int64_t m, const WorkSpace& ws, hipStream_t s);
+// all_exact: the exact loop takes every item; ntiles: of all channels
+void launch_worklist(int64_t n, int32_t stride, const WorkSpace& ws, bool all_exact, int32_t ntiles,
+                     hipStream_t s);
 int interp_tables_init();
 constexpr int kMaxTileFp64 = 2560;   // largest tile (bins) of the LDS-staged loops
 constexpr int kMaxTileMixed = 4608;   // FP32 w: 36 KB + 2 KB per block, four blocks per CU

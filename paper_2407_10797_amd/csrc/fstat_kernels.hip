@@ -7,8 +7,9 @@
 //                   two 32-point searches), Np partition edges (bin indices) and the
 //                   work-item counts: a work item is the part of a partition
 //                   inside one tile of the global tiling of the band
-//   k_scan_*        exclusive scan of the work-item counts (three passes)
-//   k_fill          work list: item -> (particle*stride + partition, tile index)
+//   k_worklist      exclusive scan of the work-item counts and the work list, item
+//                   -> (particle*stride + partition, tile index); for many counts
+//                   k_scan_* (three passes) and k_fill
 //   k_interp_nodes  exact template at 10 Chebyshev nodes and both ends of every
 //                   item -> interpolation record, or hand-over to the exact loop
 //   k_tile_*        items grouped by tile; scheduling units of <= 32 items
@@ -21,9 +22,9 @@
 //   k_eval_exact    the exact template at every bin, for handed-over items, for
 //                   refinement and under FSTAT_EVAL_EXACT (FP64 and mixed)
 //   k_mark          partitions whose interpolation error could matter -> exact
-//   k_solve         one thread per (particle, partition): ordered sum of the
-//                   item partials and the 2x2 Hermitian closed form of F_l
-//   k_mean          one wavefront per particle: F_hat = mean_l F_l, or -inf / NaN
+//   k_solve         eight lanes per (particle, partition): ordered sum of the
+//                   item partials and the 2x2 Hermitian closed form of F_l; then
+//                   F_hat = mean_l F_l, or -inf / NaN
 #include "fstat_internal.h"
 #include <algorithm>
 #include <type_traits>
@@ -213,13 +214,14 @@ __device__ double invert_tf(const PartConst& P, double t, bool need, double fa, 
 
 // One wavefront per particle: constants, support, partition edges (one per
 // lane), work-item counts.
-__global__ __launch_bounds__(256) void k_setup(Grid g, const double* __restrict__ params,
+__global__ __launch_bounds__(64) void k_setup(Grid g, const double* __restrict__ params,
                                                int64_t n, const int32_t* __restrict__ np,
                                                int32_t np_uniform, int32_t stride, int32_t chunk,
                                                const uint8_t* __restrict__ skip,
                                                PartConst* __restrict__ pc,
                                                int32_t* __restrict__ bounds,
-                                               int32_t* __restrict__ cnt) {
+                                               int32_t* __restrict__ cnt,
+                                               int32_t* __restrict__ ptot) {
   const int lane = threadIdx.x & 63;
   const int64_t p = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   if (p >= n) return;                      // whole wavefronts
@@ -232,6 +234,7 @@ __global__ __launch_bounds__(256) void k_setup(Grid g, const double* __restrict_
   int32_t* bp = bounds + p * (int64_t)(stride + 1);
   int32_t* cp = cnt + p * (int64_t)stride;
   for (int l = lane; l < stride; l += 64) cp[l] = 0;
+  if (lane == 0) ptot[p] = 0;
   P.np = npi;
   P.j_lo = 0; P.j_hi = -1;
   if (!ok) {
@@ -290,12 +293,18 @@ __global__ __launch_bounds__(256) void k_setup(Grid g, const double* __restrict_
     if (l == npi) return jhi + 1;
     return first_bin_at_or_above(g, flo + (span * (double)l) / (double)npi, jlo, jhi);
   };
+  int tot = 0;
   for (int l = lane; l < npi; l += 64) {
     const int a = edge(l), b = edge(l + 1);
     bp[l] = a;
     if (l == npi - 1) bp[npi] = b;
-    cp[l] = b > a ? ((b - 1) / chunk - a / chunk + 1) * g.chan.n : 0;   // tiles met x channels
+    const int c = b > a ? ((b - 1) / chunk - a / chunk + 1) * g.chan.n : 0;   // tiles met x channels
+    cp[l] = c;
+    tot += c;
   }
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) tot += __shfl_xor(tot, d, 64);
+  if (lane == 0) ptot[p] = tot;
 }
 
 // Exclusive scan of cnt[m] into off[m] in three passes over blocks of
@@ -381,6 +390,79 @@ __global__ void k_fill(const int32_t* __restrict__ cnt, const int32_t* __restric
   if (q >= m) return;
   int c = cnt[q], o = off[q];
   for (int i = 0; i < c; ++i) items[o + i] = make_int2((int)q, i);
+}
+
+// The same in one kernel for up to kScanOnce particles, one block each: a block
+// sums the particles' totals before its own by itself (32 KB through L2 at
+// most) instead of waiting for others, then scans its particle's counts and
+// writes its work items; the last block writes the total.  all_exact: the exact
+// loop takes every item.  Also clears the tile counters.  One launch instead of
+// five: 4 us for one particle (17), 12 us at 4096 x 64 (31).
+constexpr int64_t kScanOnce = 8192;
+
+__global__ __launch_bounds__(256) void k_worklist(const int32_t* __restrict__ cnt, int32_t stride,
+                                                  const int32_t* __restrict__ ptot,
+                                                  int32_t* __restrict__ off,
+                                                  int2* __restrict__ items,
+                                                  int32_t* __restrict__ total,
+                                                  int32_t* __restrict__ ndirect,
+                                                  int32_t* __restrict__ nrefine, int all_exact,
+                                                  int32_t* __restrict__ tcnt,
+                                                  int32_t* __restrict__ tcur, int32_t n2,
+                                                  int32_t* __restrict__ tile_ctr) {
+  __shared__ int32_t s_off[257];
+  __shared__ int32_t s_wave[4];
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int p = blockIdx.x;
+  for (int i = p * 256 + t; i < n2; i += gridDim.x * 256) { tcnt[i] = 0; tcur[i] = 0; }
+  if (p == 0 && t == 0) tile_ctr[0] = 0;
+  int32_t before = 0;                              // items of the particles before this one
+  for (int i = t; i < p; i += 256) before += ptot[i];
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) before += __shfl_xor(before, d, 64);
+  if (lane == 0) s_wave[wv] = before;
+  __syncthreads();
+  int32_t base = (s_wave[0] + s_wave[1]) + (s_wave[2] + s_wave[3]);
+  if (t == 0 && p == (int)gridDim.x - 1) {
+    const int32_t tot = base + ptot[p];
+    total[0] = tot;
+    ndirect[0] = all_exact ? tot : 0;
+    nrefine[0] = 0;
+  }
+  for (int l0 = 0; l0 < stride; l0 += 256) {
+    const int l = l0 + t;
+    const int64_t q = (int64_t)p * stride + l;
+    const int32_t v = l < stride ? cnt[q] : 0;
+    int32_t inc = v;                               // inclusive scan over the wavefront
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int32_t y = __shfl_up(inc, d, 64);
+      if (lane >= d) inc += y;
+    }
+    __syncthreads();                               // s_wave, s_off of the part before
+    if (lane == 63) s_wave[wv] = inc;
+    __syncthreads();
+    int32_t mine = 0, all = 0;
+    for (int w = 0; w < 4; ++w) {
+      if (w < wv) mine += s_wave[w];
+      all += s_wave[w];
+    }
+    const int32_t o = mine + inc - v;
+    s_off[t] = o;
+    if (t == 0) s_off[256] = all;
+    if (l < stride) off[q] = base + o;
+    __syncthreads();
+    for (int i = t; i < all; i += 256) {           // item -> its partition by bisection
+      int lo = 0, hi = 256;                        // s_off[lo] <= i < s_off[hi]
+#pragma unroll
+      for (int d = 0; d < 8; ++d) {
+        const int mid = (lo + hi) >> 1;
+        if (s_off[mid] <= i) lo = mid; else hi = mid;
+      }
+      items[base + i] = make_int2((int)((int64_t)p * stride + l0 + lo), i - s_off[lo]);
+    }
+    base += all;
+  }
 }
 
 // Prefix sums of the per-bin weight u (one channel): out[0] = 0,
@@ -489,8 +571,27 @@ __device__ __forceinline__ double wave_sum4(const double* a, int lane, int& idx)
   return d;
 }
 
+// (sin, cos)(2 pi k / kSinTab): copied to LDS by the kernels that read it per
+// bin or node; the FP64 per-bin loop needs it only in the per-lane set-up of
+// the difference recurrence and in the direct form (its LDS holds the tile)
+__constant__ double2 c_sincos[kSinTab];
+// the same from the library's sincospi, for the exact loop (filled once per
+// device; filling it in every block took 2 us of each launch)
+__device__ double2 d_sincos[kSinTab];
+__global__ void k_sincos_table() {
+  const int k = threadIdx.x;
+  double sv, cv;
+  sincospi(2.0 * (double)k / (double)kSinTab, &sv, &cv);
+  d_sincos[k] = make_double2(sv, cv);
+}
+
 constexpr int kSmallItem = 8;   // exact kernel: items this short share a wavefront
 constexpr int kBigItem = 256;   // exact kernel: items longer than this take a whole block
+constexpr int kSplitItem = 1024;   // ... and longer than this several, on very short lists
+constexpr int kSplit = 4;
+// where the blocks of a split item count themselves in its record: the unused
+// integer beside the bin count (RecLayout::tail + 4), zero from the node kernel
+template <bool MIXED> struct RecSplit { static constexpr int count = MIXED ? 85 : 109; };   // int index
 
 // Exact per-bin template loop.  FP64 (MIXED = false): everything in FP64,
 // Kahan-compensated per-lane sums.  Mixed (MIXED = true): the phase, the orbit
@@ -505,7 +606,7 @@ constexpr int kBigItem = 256;   // exact kernel: items longer than this take a w
 // the weak eigen-direction of the short, ill-conditioned partitions this
 // kernel serves.  Rounding a correct response to FP32 tilts it by ~6e-8 only.
 template <bool MIXED>
-__global__ __launch_bounds__(256) void k_eval_exact(Grid g,
+__global__ __launch_bounds__(256, 3) void k_eval_exact(Grid g,
                                                     const PartConst* __restrict__ pc,
                                                     const int32_t* __restrict__ bounds, int32_t stride,
                                                     const int2* __restrict__ items,
@@ -519,15 +620,19 @@ __global__ __launch_bounds__(256) void k_eval_exact(Grid g,
                                                     const double* __restrict__ s0a,
                                                     const double* __restrict__ c0a,
                                                     const double* __restrict__ ek,
+                                                    double* __restrict__ rec,
                                                     double* __restrict__ partials,
                                                     const int32_t* __restrict__ sel,
                                                     const int32_t* __restrict__ nsel) {
   const int lane = threadIdx.x & 63;
   const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int nwaves = (gridDim.x * blockDim.x) >> 6;
+  const int W = sel ? nsel[0] : total[0];
+  if (W == 0) return;
   __shared__ double2 s_tab[kSinTab];              // coarse angles of the template's sin/cos
   __shared__ double s_red[4][8];                  // per-wave sums of a block-wide item
-  fill_sincos_table(s_tab);
+  for (int i = threadIdx.x; i < kSinTab; i += blockDim.x) s_tab[i] = d_sincos[i];
+  __syncthreads();
   // The eight partition terms of bin j for the item (q, c) of a particle;
   // on the mixed path t[0..3] are FP32 products (widened).
   auto terms = [&](int q, int c, int j, double t[8]) {
@@ -580,40 +685,44 @@ __global__ __launch_bounds__(256) void k_eval_exact(Grid g,
     item_bins(bp[l], bp[l + 1], ct, chunk, b0, b1);
   };
   // All items, or only those listed in sel (the interpolating kernel's
-  // rejects and refinements).  Items of at most kSmallItem bins go in groups
-  // of eight list entries per wavefront, eight lanes each (one bin per lane,
-  // then a fixed three-step butterfly); larger ones one per wavefront in a
-  // second sweep over the list, so that a list of long items (the refinement
-  // pass) spreads over the whole grid, and on a short list those above
-  // kBigItem bins one per block in a third.  Which path an item takes depends
+  // rejects and refinements).  Items of at most kSmallItem bins go 32 list
+  // entries to a wavefront, two, four or eight lanes each (the fewest that hold
+  // the longest of them: 32, 16 or 8 at a time; one bin per lane, then a fixed
+  // butterfly, whose result does not depend on the width); larger ones one per
+  // wavefront in a second sweep over the list, so that a list of long items
+  // (the refinement pass) spreads over the whole grid, and on a short list
+  // those above kBigItem bins one per block (or four) in a third.  Each sweep's
+  // lanes load the items' bounds for many entries at a time (one entry at a
+  // time, the chain of dependent loads set the pass's length on the 24,910 items of
+  // a small swarm: 27 us).  Which path an item takes depends
   // on the item and the list's length alone, so its sums do not depend on the
   // order of the list.
-  const int W = sel ? nsel[0] : total[0];
-  const int G = (W + 7) >> 3;
+  const int G = (W + 31) >> 5;
   for (int gi = wave; gi < G; gi += nwaves) {
-    const int slot = gi * 8 + (lane >> 3);
-    const bool have = slot < W;
+    const int slot = gi * 32 + (lane & 31);
     int w = 0, q = 0, c = 0, b0 = 0, b1 = 0;
-    if (have) {
+    if (slot < W) {
       w = sel ? sel[slot] : slot;
       bins_of(w, q, c, b0, b1);
     }
-    const bool small = have && b1 - b0 <= kSmallItem;
-    if (!__any(small)) continue;
-    double t[8];
+    const int nb = b1 - b0 <= kSmallItem ? b1 - b0 : 0;      // 0: not of this sweep
+    if (!__any(nb > 0)) continue;
+    const int width = __any(nb > 4) ? 8 : (__any(nb > 2) ? 4 : 2), at = 64 / width;
+    for (int i0 = 0; i0 < 32; i0 += at) {
+      const int src = i0 + lane / width, e = lane & (width - 1);
+      const int wi = __shfl(w, src, 64), qi = __shfl(q, src, 64), ci = __shfl(c, src, 64);
+      const int j = __shfl(b0, src, 64) + e, ni = __shfl(nb, src, 64);
+      double t[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) t[i] = 0.0;
-    const int j = b0 + (lane & 7);
-    if (small && j < b1) terms(q, c, j, t);
+      for (int i = 0; i < 8; ++i) t[i] = 0.0;
+      if (e < ni) terms(qi, ci, j, t);
+      for (int d = width >> 1; d > 0; d >>= 1)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      t[i] += __shfl_xor(t[i], 4, 64);
-      t[i] += __shfl_xor(t[i], 2, 64);
-      t[i] += __shfl_xor(t[i], 1, 64);
-    }
-    if (small && (lane & 7) == 0) {
+        for (int i = 0; i < 8; ++i) t[i] += __shfl_xor(t[i], d, 64);
+      if (ni > 0 && e == 0) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) partials[(int64_t)w * 8 + i] = t[i];
+        for (int i = 0; i < 8; ++i) partials[(int64_t)wi * 8 + i] = t[i];
+      }
     }
   }
   // Kahan-compensated sums of this thread's bins j0, j0 + step, ... < j1 of
@@ -656,45 +765,96 @@ __global__ __launch_bounds__(256) void k_eval_exact(Grid g,
   const bool by_block = W < 4 * nwaves;
   // items of kSmallItem + 1 bins and more (up to kBigItem for a short list):
   // one per wavefront
-  for (int slot = wave; slot < W; slot += nwaves) {
-    // the slot is the same on every lane: keep the item's indices scalar
-    const int wb = __builtin_amdgcn_readfirstlane(sel ? sel[slot] : slot);
-    int qb, cb, bb0, bb1;
-    bins_of(wb, qb, cb, bb0, bb1);
-    qb = __builtin_amdgcn_readfirstlane(qb);
-    cb = __builtin_amdgcn_readfirstlane(cb);
-    bb0 = __builtin_amdgcn_readfirstlane(bb0);
-    bb1 = __builtin_amdgcn_readfirstlane(bb1);
-    if (bb1 - bb0 <= kSmallItem || (by_block && bb1 - bb0 > kBigItem)) continue;
-    double acc[8];
-    thread_sums(qb, cb, bb0 + lane, bb1, 64, acc);
-    int idx;
-    const double tot = wave_sum8(acc, lane, idx);
-    if ((lane & 7) == 0) partials[(int64_t)wb * 8 + idx] = tot;
+  for (int s0 = wave; s0 < W; s0 += 64 * nwaves) {
+    const int slot = s0 + lane * nwaves;
+    int w = 0, q = 0, c = 0, b0 = 0, b1 = 0;
+    if (slot < W) {
+      w = sel ? sel[slot] : slot;
+      bins_of(w, q, c, b0, b1);
+    }
+    const int nb = b1 - b0;
+    for (uint64_t todo = __ballot(nb > kSmallItem && !(by_block && nb > kBigItem)); todo != 0;
+         todo &= todo - 1) {
+      const int l = __builtin_ctzll(todo);       // the same on every lane: scalar indices
+      const int wb = __builtin_amdgcn_readlane(w, l), qb = __builtin_amdgcn_readlane(q, l);
+      const int cb = __builtin_amdgcn_readlane(c, l);
+      const int bb0 = __builtin_amdgcn_readlane(b0, l), bb1 = __builtin_amdgcn_readlane(b1, l);
+      double acc[8];
+      thread_sums(qb, cb, bb0 + lane, bb1, 64, acc);
+      int idx;
+      const double tot = wave_sum8(acc, lane, idx);
+      if ((lane & 7) == 0) partials[(int64_t)wb * 8 + idx] = tot;
+    }
   }
+  if (!by_block) return;
   // longer items: one per block (a few long rejects or refined items would
   // otherwise each hold one wavefront for the whole pass); the four waves'
-  // sums are added in a fixed order
-  for (int slot = blockIdx.x; by_block && slot < W; slot += gridDim.x) {
-    const int wb = __builtin_amdgcn_readfirstlane(sel ? sel[slot] : slot);
-    int qb, cb, bb0, bb1;
-    bins_of(wb, qb, cb, bb0, bb1);
-    qb = __builtin_amdgcn_readfirstlane(qb);
-    cb = __builtin_amdgcn_readfirstlane(cb);
-    bb0 = __builtin_amdgcn_readfirstlane(bb0);
-    bb1 = __builtin_amdgcn_readfirstlane(bb1);
-    if (bb1 - bb0 <= kBigItem) continue;         // the same for every thread of the block
-    double acc[8];
-    thread_sums(qb, cb, bb0 + (int)threadIdx.x, bb1, (int)blockDim.x, acc);
-    int idx;
-    const double tot = wave_sum8(acc, lane, idx);
-    if ((lane & 7) == 0) s_red[threadIdx.x >> 6][idx] = tot;
-    __syncthreads();
-    if (threadIdx.x < 8)
-      partials[(int64_t)wb * 8 + threadIdx.x] =
-          ((s_red[0][threadIdx.x] + s_red[1][threadIdx.x]) + s_red[2][threadIdx.x]) +
-          s_red[3][threadIdx.x];
-    __syncthreads();                              // s_red is rewritten by the next item
+  // sums are added in a fixed order.  On a list of at most a quarter of the
+  // blocks, items above kSplitItem bins take four blocks, whose sums meet in the
+  // item's record (its interpolants are not needed any more) and are added in
+  // order by the last of them (5120 bins by one block: ~50 us of latency for a
+  // single template).
+  const int parts = sel && (int64_t)W * kSplit <= (int64_t)gridDim.x ? kSplit : 1;
+  for (int64_t u0 = blockIdx.x; u0 < (int64_t)W * parts; u0 += 64 * (int64_t)gridDim.x) {
+    const int64_t u = u0 + (int64_t)lane * gridDim.x;
+    const int slot = (int)(u / parts), part = (int)(u - (int64_t)slot * parts);
+    int w = 0, q = 0, c = 0, b0 = 0, b1 = 0;
+    if (slot < W) {
+      w = sel ? sel[slot] : slot;
+      bins_of(w, q, c, b0, b1);
+    }
+    const int nb = b1 - b0;
+    // the same on every wave of the block
+    for (uint64_t todo = __ballot(nb > kBigItem && (part == 0 || nb > kSplitItem)); todo != 0;
+         todo &= todo - 1) {
+      const int l = __builtin_ctzll(todo);
+      const int wb = __builtin_amdgcn_readlane(w, l), qb = __builtin_amdgcn_readlane(q, l);
+      const int cb = __builtin_amdgcn_readlane(c, l), pb = __builtin_amdgcn_readlane(part, l);
+      int bb0 = __builtin_amdgcn_readlane(b0, l), bb1 = __builtin_amdgcn_readlane(b1, l);
+      const bool split = parts > 1 && bb1 - bb0 > kSplitItem;
+      if (split) {
+        const int n = (bb1 - bb0 + kSplit - 1) / kSplit;
+        bb0 += pb * n;
+        bb1 = min(bb1, bb0 + n);
+      }
+      double acc[8];
+      thread_sums(qb, cb, bb0 + (int)threadIdx.x, bb1, (int)blockDim.x, acc);
+      int idx;
+      const double tot = wave_sum8(acc, lane, idx);
+      if ((lane & 7) == 0) s_red[threadIdx.x >> 6][idx] = tot;
+      __syncthreads();
+      double sum = 0.0;
+      if (threadIdx.x < 8)
+        sum = ((s_red[0][threadIdx.x] + s_red[1][threadIdx.x]) + s_red[2][threadIdx.x]) +
+              s_red[3][threadIdx.x];
+      if (!split) {
+        if (threadIdx.x < 8) partials[(int64_t)wb * 8 + threadIdx.x] = sum;
+      } else if (threadIdx.x < 64) {             // one wavefront: its stores, then its count
+        double* r = rec + (int64_t)wb * kInterpRec;
+        int* arrived = reinterpret_cast<int*>(r) + RecSplit<MIXED>::count;
+        if (threadIdx.x < 8)
+          __hip_atomic_store(r + 8 * pb + threadIdx.x, sum, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+        __threadfence();
+        int old = 0;
+        if (threadIdx.x == 0)
+          old = __hip_atomic_fetch_add(arrived, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        old = __builtin_amdgcn_readfirstlane(old);
+        if (old == kSplit - 1) {
+          __threadfence();
+          if (threadIdx.x < 8) {
+            double x = 0.0;
+            for (int k = 0; k < kSplit; ++k)
+              x += __hip_atomic_load(r + 8 * k + threadIdx.x, __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_AGENT);
+            partials[(int64_t)wb * 8 + threadIdx.x] = x;
+          }
+          if (threadIdx.x == 0)
+            __hip_atomic_store(arrived, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+      }
+      __syncthreads();                           // s_red is rewritten by the next item
+    }
   }
 }
 
@@ -751,10 +911,6 @@ constexpr double kStirF[kCheb][kCheb] = {
     {0, 1, 510, 18150, 186480, 834120, 1905120, 2328480, 1451520, 362880}};
 
 __constant__ double c_cheb_s[kCheb];          // nodes cos(pi (k + 1/2) / 10)
-// (sin, cos)(2 pi k / kSinTab) for the FP64 bin loop, which needs it only in
-// the per-lane set-up of the difference recurrence and in the direct form
-// (its LDS holds the tile instead)
-__constant__ double2 c_sincos[kSinTab];
 // Row tables of the node kernel, indexed [node kn][lane k of the item]: on a
 // node lane (k < kCheb) the map node value kn -> monomial coefficient of s^k
 // of the interpolant, on the end lanes k = kCheb, kCheb + 1 the map node
@@ -857,6 +1013,14 @@ template <bool MIXED> struct RecLayout {
   static constexpr int nT = MIXED ? kDegT + 1 : kCheb;
   static constexpr int tail = kCheb + 4 * nT;   // A, B', B, {flags, b0}, {bins, -}, alpha, -B/df
 };
+// the split items of the exact loop count their blocks in the record's unused
+// integer (half 1 of tail + 4) and keep kSplit sets of eight sums below it
+template <bool MIXED> struct RecSplitCheck {
+  static_assert(2 * (RecLayout<MIXED>::tail + 4) + 1 == RecSplit<MIXED>::count, "record layout");
+  static_assert(8 * kSplit <= RecLayout<MIXED>::tail, "room for the sums");
+};
+template struct RecSplitCheck<false>;
+template struct RecSplitCheck<true>;
 // the per-bin loop marks the items whose lanes took its short form (the
 // difference recurrence; mixed: four phase differences) for fstat_interp_stats
 enum { kRecExact = 0, kRecBins = 1, kRecBinsShort = 2, kRecBlocks = 3 };
@@ -1329,6 +1493,7 @@ __global__ __launch_bounds__(256) void k_eval_interp(Grid g,
   const int wv = threadIdx.x >> 6;
   const int nwv = blockDim.x >> 6;
   const int nunits = unit_off[ntiles];
+  if (nunits == 0) return;
   // The current unit: its items, the channel's data offset, and the tile's bins
   // not yet staged.  Tiles above the LDS stage go through it in parts; a wave
   // takes the same items in each and adds to their sums.
@@ -2173,13 +2338,13 @@ __global__ __launch_bounds__(256) void k_mark(const PartConst* __restrict__ pc, 
                                               int32_t* __restrict__ refine,
                                               int32_t* __restrict__ nrefine) {
   const int64_t q = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 3;
-  const int k = threadIdx.x & 7;
-  if (q >= n * stride) return;                 // whole groups of eight
-  const int64_t p = q / stride;
-  const int l = (int)(q - p * stride);
-  const PartConst& P = pc[p];
-  if (l >= P.np || P.status != kStatusOk) return;
-  const int o = off[q], c = cnt[q];
+  const int k = threadIdx.x & 7, lane = threadIdx.x & 63;
+  int o = 0, c = 0;                            // no items: the group only takes part in the scan
+  if (q < n * stride) {
+    const int64_t p = q / stride;
+    const PartConst& P = pc[p];
+    if ((int)(q - p * stride) < P.np && P.status == kStatusOk) { o = off[q]; c = cnt[q]; }
+  }
   // the items' error terms, every eighth item per lane
   int ninterp = 0;
   double s2 = 0.0, mt = 0.0;
@@ -2196,16 +2361,16 @@ __global__ __launch_bounds__(256) void k_mark(const PartConst* __restrict__ pc, 
     s2 += __shfl_xor(s2, d, 8);
     mt += __shfl_xor(mt, d, 8);
   }
-  if (ninterp == 0) return;
   double a[8];
-  partition_sums(partials, o, c, k, a);
+  partition_sums(partials, o, ninterp > 0 ? c : 0, k, a);
   const double Pm = a[4], Qm = a[5], rr = a[6], ri = a[7];
   const double hs = 0.5 * (Pm + Qm), hd = 0.5 * (Pm - Qm);
   const double lp = hs + sqrt(hd * hd + rr * rr + ri * ri);
   const double lm = (Pm * Qm - (rr * rr + ri * ri)) / lp;
   const bool all = !(lp > 0.0) || !(lm > kFragile * kRankCut * lp);
   double thr_t = 0.0, thr_m = 0.0;
-  if (!all) {
+  bool some = ninterp > 0;
+  if (some && !all) {
     double beta[4];
     solve_beta(a, beta);
     const double F = solve_partition(a);
@@ -2213,17 +2378,34 @@ __global__ __launch_bounds__(256) void k_mark(const PartConst* __restrict__ pc, 
     const double kt = 1.4142135623730951 * (kRefineKappa + sqrt(2.0 * fmax(F, 0.0))) * b;
     const double km = 0.5 * b * b;
     const double tol = budget * fmax(fabs(F), 1.0);
-    if (kt * sqrt(s2) + km * mt <= tol) return;
+    some = !(kt * sqrt(s2) + km * mt <= tol);
     // refining every item above these leaves at most tol / 2 in each term
     thr_t = 0.5 * tol / (kt * sqrt((double)ninterp));
     thr_m = 0.5 * tol / (km * (double)ninterp);
   }
-  for (int i = k; i < c; i += 8) {
-    if (xflag[o + i] == kItemExact) continue;
+  if (!__any(some)) return;
+  auto sel = [&](int i) {
+    if (xflag[o + i] == kItemExact) return false;
     const float2 x = xerr[o + i];
-    if (all || (double)x.x > thr_t || (double)x.y > thr_m)
-      refine[atomicAdd(nrefine, 1)] = o + i;
+    return all || (double)x.x > thr_t || (double)x.y > thr_m;
+  };
+  int ns = 0;
+  for (int i = some ? k : c; i < c; i += 8) ns += sel(i) ? 1 : 0;
+  // one place in the list for the wavefront's items (an atomic per item took
+  // 0.9 ms for 421,783 of them)
+  int at = ns;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int y = __shfl_up(at, d, 64);
+    if (lane >= d) at += y;
   }
+  const int tot = __shfl(at, 63, 64);
+  if (tot == 0) return;
+  int base = 0;
+  if (lane == 0) base = atomicAdd(nrefine, tot);
+  at += __shfl(base, 0, 64) - ns;
+  for (int i = some ? k : c; i < c; i += 8)
+    if (sel(i)) refine[at++] = o + i;
 }
 
 // Bins of the last evaluation's items by the kind of per-bin work the
@@ -2410,6 +2592,58 @@ __global__ __launch_bounds__(256) void k_tile_scatter(const int2* __restrict__ i
   }
 }
 
+// Count, scan and scatter in one block, for few items (host bound kGroupOnce)
+// on few tiles: one launch instead of three.
+constexpr int64_t kGroupOnce = 32768;
+
+__global__ __launch_bounds__(1024) void k_tile_group(const int2* __restrict__ items,
+                                                     const int32_t* __restrict__ total,
+                                                     const uint8_t* __restrict__ xflag,
+                                                     const int32_t* __restrict__ bounds,
+                                                     int32_t stride, int32_t T, int32_t ntiles,
+                                                     int32_t nch, int32_t* __restrict__ off,
+                                                     int32_t* __restrict__ uoff,
+                                                     int32_t* __restrict__ tile_items) {
+  __shared__ int32_t h[kTileHist];
+  __shared__ int32_t sh[1024];
+  const int t = threadIdx.x, nk = 2 * ntiles;
+  const int W = total[0];
+  for (int i = t; i < nk; i += 1024) h[i] = 0;
+  __syncthreads();
+  for (int w = t; w < W; w += 1024) {
+    const int k = tile_key(items, xflag, bounds, stride, T, ntiles, nch, w);
+    if (k >= 0) atomicAdd(&h[k], 1);
+  }
+  __syncthreads();
+  const int per = (nk + 1023) / 1024, a = min(nk, t * per), b = min(nk, a + per);
+  int32_t sum = 0, usum = 0, tot, utot;
+  for (int i = a; i < b; ++i) {
+    sum += h[i];
+    if (i >= ntiles) usum += (h[i] + kUnitItems - 1) / kUnitItems;
+  }
+  int32_t run = block_excl_scan(sum, sh, tot);
+  int32_t urun = block_excl_scan(usum, sh, utot);
+  if (t == 0) {
+    off[nk] = tot;
+    uoff[ntiles] = utot;
+  }
+  for (int i = a; i < b; ++i) {
+    const int32_t c = h[i];
+    off[i] = run;
+    h[i] = run;
+    run += c;
+    if (i >= ntiles) {
+      uoff[i - ntiles] = urun;
+      urun += (c + kUnitItems - 1) / kUnitItems;
+    }
+  }
+  __syncthreads();
+  for (int w = t; w < W; w += 1024) {
+    const int k = tile_key(items, xflag, bounds, stride, T, ntiles, nch, w);
+    if (k >= 0) tile_items[atomicAdd(&h[k], 1)] = w;
+  }
+}
+
 // every item is evaluated exactly: the reject count equals the item count
 __global__ void k_copy_count(const int32_t* __restrict__ total, int32_t* __restrict__ ndirect) {
   if (threadIdx.x == 0) ndirect[0] = total[0];
@@ -2562,6 +2796,7 @@ int interp_tables_init() {
   // quadrature table S_j(nb), one per device
   double* tab = nullptr;
   if (hipMalloc((void**)&tab, sizeof(double) * 5 * (kSsumMax + 1)) != hipSuccess) return -1;
+  hipLaunchKernelGGL(k_sincos_table, dim3(1), dim3(kSinTab), 0, 0);
   hipLaunchKernelGGL(k_cheb_sums, dim3((kSsumMax + 256) / 256), dim3(256), 0, 0, tab);
   if (hipGetLastError() != hipSuccess || hipDeviceSynchronize() != hipSuccess) return -1;
   if (dev >= 0 && dev < 64) {
@@ -2731,71 +2966,66 @@ __device__ __forceinline__ void amps_from_beta(const PartConst& P, const double*
   a[3] = xi;
 }
 
-// Eight lanes per partition (partition_sums).
-__global__ __launch_bounds__(256) void k_solve(const PartConst* __restrict__ pc, int64_t n,
-                                               int32_t stride, const int32_t* __restrict__ cnt,
+// One block per particle: eight lanes per partition (partition_sums), then the
+// first wavefront takes the mean, lanes every 64th partition and a fixed
+// butterfly (the result does not depend on the launch).
+__global__ __launch_bounds__(1024) void k_solve(const PartConst* __restrict__ pc, int32_t stride,
+                                               const int32_t* __restrict__ cnt,
                                                const int32_t* __restrict__ off,
                                                const double* __restrict__ partials,
                                                double* __restrict__ Fl,
+                                               double* __restrict__ F_hat,
                                                double* __restrict__ F_part, int64_t part_stride,
                                                double* __restrict__ amps,
-                                               const double* __restrict__ umax) {
-  const int64_t q = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 3;
-  const int k = threadIdx.x & 7;
-  if (q >= n * stride) return;                 // whole groups of eight
-  const int64_t p = q / stride;
-  const int l = (int)(q - p * stride);
+                                               const double* __restrict__ umax,
+                                               unsigned long long* __restrict__ bin_counter) {
+  const int64_t p = blockIdx.x;
   const PartConst& P = pc[p];
-  if (l >= P.np || P.status == kStatusInvalid) return;
-  double F = 0.0;
-  double am[4] = {0.0, 0.0, 0.0, 0.0};
-  if (P.status == kStatusOk) {
-    double a[8];
+  const int k = threadIdx.x & 7;
+  const int status = P.status, np = P.np;
+  if (status == kStatusInvalid) {
+    if (threadIdx.x == 0) F_hat[p] = __builtin_nan("");
+    for (int l = threadIdx.x; l < np && l < part_stride; l += blockDim.x) {
+      if (F_part) F_part[p * part_stride + l] = __builtin_nan("");
+      if (amps)
+        for (int i = 0; i < 4; ++i) amps[(p * part_stride + l) * 4 + i] = __builtin_nan("");
+    }
+    return;
+  }
+  if (status != kStatusOk) {
+    if (threadIdx.x == 0) F_hat[p] = -__builtin_inf();
+    for (int l = threadIdx.x; l < np; l += blockDim.x) {
+      if (F_part) F_part[p * part_stride + l] = 0.0;
+      if (amps)
+        for (int i = 0; i < 4; ++i) amps[(p * part_stride + l) * 4 + i] = 0.0;
+    }
+    return;
+  }
+  for (int l = threadIdx.x >> 3; l < np; l += blockDim.x >> 3) {   // whole groups of eight
+    const int64_t q = p * stride + l;
+    double a[8], am[4];
     partition_sums(partials, off[q], cnt[q], k, a);
-    F = solve_partition(a);
+    const double F = solve_partition(a);
     if (amps) {
       double beta[4];
       solve_beta(a, beta);
       const double m = umax[0];
       amps_from_beta(P, beta, m > 0.0 ? sqrt(1.0 / m) : 1.0, am);
     }
+    if (k != 0) continue;
+    Fl[q] = F;
+    if (F_part) F_part[p * part_stride + l] = F;
+    if (amps)
+      for (int i = 0; i < 4; ++i) amps[(p * part_stride + l) * 4 + i] = am[i];
   }
-  if (k != 0) return;
-  Fl[q] = F;
-  if (F_part) F_part[p * part_stride + l] = F;
-  if (amps)
-    for (int i = 0; i < 4; ++i) amps[(p * part_stride + l) * 4 + i] = am[i];
-}
-
-// One wavefront per particle: lanes take every 64th partition, then a fixed
-// butterfly (the result does not depend on the launch).
-__global__ void k_mean(const PartConst* __restrict__ pc, int64_t n, int32_t stride,
-                       const double* __restrict__ Fl, double* __restrict__ F_hat,
-                       double* __restrict__ F_part, int64_t part_stride,
-                       double* __restrict__ amps, unsigned long long* __restrict__ bin_counter) {
-  const int lane = threadIdx.x & 63;
-  const int64_t p = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  if (p >= n) return;
-  const PartConst& P = pc[p];
-  if (P.status == kStatusInvalid) {
-    if (lane == 0) F_hat[p] = __builtin_nan("");
-    for (int l = lane; l < P.np && l < part_stride; l += 64) {
-      if (F_part) F_part[p * part_stride + l] = __builtin_nan("");
-      if (amps)
-        for (int k = 0; k < 4; ++k) amps[(p * part_stride + l) * 4 + k] = __builtin_nan("");
-    }
-    return;
-  }
-  if (P.status == kStatusEmpty) {
-    if (lane == 0) F_hat[p] = -__builtin_inf();
-    return;
-  }
+  __syncthreads();                             // Fl of this block's partitions
+  if (threadIdx.x >= 64) return;
   double s = 0.0;
-  for (int l = lane; l < P.np; l += 64) s += Fl[p * stride + l];
+  for (int l = threadIdx.x; l < np; l += 64) s += Fl[p * stride + l];
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-  if (lane == 0) {
-    F_hat[p] = s / (double)P.np;
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+  if (threadIdx.x == 0) {
+    F_hat[p] = s / (double)np;
     if (bin_counter) atomicAdd(bin_counter, (unsigned long long)(P.j_hi - P.j_lo + 1));
   }
 }
@@ -2928,17 +3158,31 @@ void launch_scale(const Grid& g, const double* umax, BinData<double> b, BinData<
 void launch_setup(const Grid& g, const double* params, int64_t n,
                   const int32_t* np, int32_t np_uniform, int32_t stride, int32_t chunk,
                   const uint8_t* skip, const WorkSpace& ws, hipStream_t s) {
-  hipLaunchKernelGGL(k_setup, dim3(nblk(n * 64, 256)), dim3(256), 0, s, g, params, n, np, np_uniform,
-                     stride, chunk, skip, ws.pc, ws.bounds, ws.cnt);
+  // one wavefront per block: a small batch spreads over the CUs
+  hipLaunchKernelGGL(k_setup, dim3((unsigned)n), dim3(64), 0, s, g, params, n, np, np_uniform,
+                     stride, chunk, skip, ws.pc, ws.bounds, ws.cnt, ws.ptot());
 }
 
-void launch_worklist(int64_t m, const WorkSpace& ws, hipStream_t s) {
+void launch_worklist(int64_t n, int32_t stride, const WorkSpace& ws, bool all_exact, int32_t ntiles,
+                     hipStream_t s) {
+  const int64_t m = n * stride;
   const int32_t nb = (int32_t)((m + kScanBlock - 1) / kScanBlock);
+  if (n <= kScanOnce) {
+    hipLaunchKernelGGL(k_worklist, dim3((unsigned)n), dim3(256), 0, s, ws.cnt, stride, ws.ptot(),
+                       ws.off, ws.items, ws.total, ws.ndirect, ws.nrefine, all_exact ? 1 : 0,
+                       ws.tcnt, ws.tcur, all_exact ? 0 : 2 * ntiles, ws.tile_ctr);
+    return;
+  }
   hipLaunchKernelGGL(k_scan_sums, dim3(nb), dim3(1024), 0, s, ws.cnt, m, ws.bsum);
   hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, ws.bsum, nb, ws.total, ws.ndirect,
                      ws.nrefine);
   hipLaunchKernelGGL(k_scan_apply, dim3(nb), dim3(1024), 0, s, ws.cnt, m, ws.bsum, ws.off);
   hipLaunchKernelGGL(k_fill, dim3(nblk(m, 256)), dim3(256), 0, s, ws.cnt, ws.off, m, ws.items);
+  if (all_exact)
+    hipLaunchKernelGGL(k_copy_count, dim3(1), dim3(64), 0, s, ws.total, ws.ndirect);
+  else
+    hipLaunchKernelGGL(k_tile_zero, dim3(nblk(2 * ntiles, 256)), dim3(256), 0, s, ws.tcnt, ws.tcur,
+                       2 * ntiles, ws.tile_ctr);
 }
 
 int interp_max_tile(bool mixed) { return mixed ? kMaxTileMixed : kMaxTileFp64; }
@@ -2950,11 +3194,8 @@ void launch_eval(bool mixed, bool interp, double refine_budget, const Grid& g,
                  const Spectra<double>& s64, const Spectra<float>& s32) {
   const int32_t* sel = nullptr;
   const int32_t* nsel = nullptr;
-  if (!interp) hipLaunchKernelGGL(k_copy_count, dim3(1), dim3(64), 0, s, ws.total, ws.ndirect);
   if (interp) {
     const int32_t ntiles = (int32_t)((g.nbins + chunk - 1) / chunk) * g.chan.n;   // all channels
-    hipLaunchKernelGGL(k_tile_zero, dim3(nblk(2 * ntiles, 256)), dim3(256), 0, s, ws.tcnt, ws.tcur,
-                       2 * ntiles, ws.tile_ctr);
     // The block loop needs tiles of whole blocks (the items inside a partition
     // then have no partial ones).
     SpecShape sp{};
@@ -2970,12 +3211,18 @@ void launch_eval(bool mixed, bool interp, double refine_budget, const Grid& g,
                          ws.items, ws.total, chunk, ek, ws.rec, ws.xflag, ws.xerr, ws.direct,
                          ws.ndirect, um, ws.partials, sp);
     }
-    hipLaunchKernelGGL(k_tile_count, dim3(1024), dim3(256), 0, s, ws.items, ws.total, ws.xflag,
-                       ws.bounds, stride, chunk, ntiles, g.chan.n, ws.tcnt);
-    hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(1024), 0, s, ws.tcnt, ntiles, ws.toff, ws.uoff);
-    hipLaunchKernelGGL(k_tile_scatter, dim3(1024), dim3(256), 0, s, ws.items, ws.total, ws.xflag,
-                       ws.bounds, stride, chunk, ntiles, g.chan.n, ws.toff, ws.tcur,
-                       ws.tile_items);
+    if (n_particles * (int64_t)(ntiles + stride * g.chan.n) <= kGroupOnce && 2 * ntiles <= kTileHist) {
+      hipLaunchKernelGGL(k_tile_group, dim3(1), dim3(1024), 0, s, ws.items, ws.total, ws.xflag,
+                         ws.bounds, stride, chunk, ntiles, g.chan.n, ws.toff, ws.uoff,
+                         ws.tile_items);
+    } else {
+      hipLaunchKernelGGL(k_tile_count, dim3(1024), dim3(256), 0, s, ws.items, ws.total, ws.xflag,
+                         ws.bounds, stride, chunk, ntiles, g.chan.n, ws.tcnt);
+      hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(1024), 0, s, ws.tcnt, ntiles, ws.toff, ws.uoff);
+      hipLaunchKernelGGL(k_tile_scatter, dim3(1024), dim3(256), 0, s, ws.items, ws.total, ws.xflag,
+                         ws.bounds, stride, chunk, ntiles, g.chan.n, ws.toff, ws.tcur,
+                         ws.tile_items);
+    }
     if (ev_main) (void)hipEventRecord(ev_main[0], s);
     if (sp.L > 0) {
       const int64_t ng = (int64_t)n_particles * stride * g.chan.n;
@@ -3006,7 +3253,7 @@ void launch_eval(bool mixed, bool interp, double refine_budget, const Grid& g,
   auto exact_pass = [&](const int32_t* list, const int32_t* count) {
     hipLaunchKernelGGL(mixed ? k_eval_exact<true> : k_eval_exact<false>, dim3(blocks), dim3(256),
                        0, s, g, ws.pc, ws.bounds, stride, ws.items, ws.total, chunk, b.wr, b.wi,
-                       b.u, b32.wr, b32.wi, b32.u, b.s0, b.c0, ek, ws.partials, list, count);
+                       b.u, b32.wr, b32.wi, b32.u, b.s0, b.c0, ek, ws.rec, ws.partials, list, count);
   };
   if (!interp && ev_main) (void)hipEventRecord(ev_main[0], s);
   exact_pass(sel, nsel);
@@ -3024,11 +3271,11 @@ void launch_eval(bool mixed, bool interp, double refine_budget, const Grid& g,
 void launch_solve_mean(int64_t n, int32_t stride, const WorkSpace& ws, double* F_hat,
                        double* F_part, double* amps, int64_t part_stride, const double* umax,
                        unsigned long long* bin_counter, hipStream_t s) {
-  int64_t m = n * stride;
-  hipLaunchKernelGGL(k_solve, dim3(nblk(8 * m, 256)), dim3(256), 0, s, ws.pc, n, stride, ws.cnt,
-                     ws.off, ws.partials, ws.Fl, F_part, part_stride, amps, umax);
-  hipLaunchKernelGGL(k_mean, dim3(nblk(n * 64, 256)), dim3(256), 0, s, ws.pc, n, stride, ws.Fl, F_hat,
-                     F_part, part_stride, amps, bin_counter);
+  // eight lanes for each of the particle's partitions, up to 128 at a time
+  const unsigned bs = (unsigned)std::min((stride + 7) / 8, 16) * 64;
+  hipLaunchKernelGGL(k_solve, dim3((unsigned)n), dim3(bs), 0, s, ws.pc, stride,
+                     ws.cnt, ws.off, ws.partials, ws.Fl, F_hat, F_part, part_stride, amps, umax,
+                     bin_counter);
 }
 
 void launch_sur_data(uint64_t seed, int64_t n, float* X, float* T, hipStream_t s) {

@@ -29,9 +29,27 @@ struct PsoArgs {
   uint64_t seed;
 };
 
+// Particle g of run r at normalised position x -> physical parameters for the
+// next evaluation; particles outside [0,1]^6 are skipped.
+__device__ __forceinline__ void pso_decode(const double* x, const double* __restrict__ box, int r,
+                                           int64_t g, double* __restrict__ params,
+                                           uint8_t* __restrict__ skip) {
+  bool out = false;
+  for (int j = 0; j < 6; ++j) {
+    const double xj = x[j];
+    out = out || !(xj >= 0.0 && xj <= 1.0);
+    const double lo = box[r * 12 + 2 * j], hi = box[r * 12 + 2 * j + 1];
+    params[g * 6 + j] = lo + xj * (hi - lo);
+  }
+  skip[g] = out ? 1 : 0;
+}
+
 __global__ void k_pso_init(PsoArgs a, double* __restrict__ x, double* __restrict__ v,
                            double* __restrict__ pbx, double* __restrict__ pbf,
-                           double* __restrict__ gbf, int32_t* __restrict__ iter) {
+                           double* __restrict__ gbf, int32_t* __restrict__ iter,
+                           const double* __restrict__ box, const int32_t* __restrict__ np_run,
+                           double* __restrict__ params, int32_t* __restrict__ np,
+                           uint8_t* __restrict__ skip) {
   int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (g >= (int64_t)a.n_runs * a.n_part) return;
   int r = (int)(g / a.n_part), i = (int)(g % a.n_part);
@@ -43,41 +61,28 @@ __global__ void k_pso_init(PsoArgs a, double* __restrict__ x, double* __restrict
     pbx[g * 6 + j] = xj;
     v[g * 6 + j] = u[6 + j] - xj;   // U[0 - x, 1 - x] in the normalised box
   }
+  pso_decode(u, box, r, g, params, skip);
+  np[g] = np_run[r];
   pbf[g] = -__builtin_inf();
   if (i == 0) gbf[r] = -__builtin_inf();
   if (g == 0) iter[0] = 0;
 }
 
-// normalised x -> physical parameters; particles outside [0,1]^6 are skipped
-__global__ void k_pso_decode(PsoArgs a, const double* __restrict__ x,
-                             const double* __restrict__ box, const int32_t* __restrict__ np_run,
-                             double* __restrict__ params, int32_t* __restrict__ np,
-                             uint8_t* __restrict__ skip) {
-  int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= (int64_t)a.n_runs * a.n_part) return;
-  int r = (int)(g / a.n_part);
-  bool out = false;
-  for (int j = 0; j < 6; ++j) {
-    double xj = x[g * 6 + j];
-    out = out || !(xj >= 0.0 && xj <= 1.0);
-    double lo = box[r * 12 + 2 * j], hi = box[r * 12 + 2 * j + 1];
-    params[g * 6 + j] = lo + xj * (hi - lo);
-  }
-  np[g] = np_run[r];
-  skip[g] = out ? 1 : 0;
-}
-
-// one block per run, one thread per particle
+// One block per run, one thread per particle.  The iteration is iter[0] + koff
+// (koff: its place in a captured graph); the updated positions are decoded for
+// the next evaluation here.
 __global__ void k_pso_update(PsoArgs a, const double* __restrict__ F, double* __restrict__ x,
                              double* __restrict__ v, double* __restrict__ pbx,
                              double* __restrict__ pbf, double* __restrict__ gbx,
                              double* __restrict__ gbf, double* __restrict__ trace,
-                             const int32_t* __restrict__ iter) {
+                             const int32_t* __restrict__ iter, int32_t koff,
+                             const double* __restrict__ box, double* __restrict__ params,
+                             uint8_t* __restrict__ skip) {
   extern __shared__ double sh[];
   double* spb = sh;                               // [n_part] personal bests
   int* sbest = (int*)(sh + a.n_part);             // [1] run best index
   const int r = blockIdx.x, i = threadIdx.x, Pn = a.n_part;
-  const int k = iter[0];
+  const int k = iter[0] + koff;
   const int64_t g = (int64_t)r * Pn + i;
   if (i < Pn) {
     double f = F[g];
@@ -88,11 +93,25 @@ __global__ void k_pso_update(PsoArgs a, const double* __restrict__ F, double* __
     spb[i] = pbf[g];
   }
   __syncthreads();
-  if (i == 0) {
+  if (i < 64) {
+    // the first wavefront: lowest index of the largest value (as a serial scan
+    // from particle 0 finds it, also where values are NaN: one that is not
+    // above the first stays out)
     int b = 0;
-    for (int q = 1; q < Pn; ++q)
-      if (spb[q] > spb[b]) b = q;   // lowest index wins ties
-    sbest[0] = b;
+    double fb = spb[0];
+    for (int q = i; q < Pn; q += 64)
+      if (spb[q] > fb) { b = q; fb = spb[q]; }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+      const int q = __shfl_xor(b, d, 64);
+      const double fq = __shfl_xor(fb, d, 64);
+      if (fq > fb || (fq == fb && q < b)) { b = q; fb = fq; }
+    }
+    if (i == 0) sbest[0] = b;
+  }
+  __syncthreads();
+  if (i == 0) {
+    const int b = sbest[0];
     gbf[r] = spb[b];
     for (int j = 0; j < 6; ++j) gbx[r * 6 + j] = pbx[((int64_t)r * Pn + b) * 6 + j];
     if (trace) trace[(int64_t)k * a.n_runs + r] = spb[b];
@@ -116,18 +135,20 @@ __global__ void k_pso_update(PsoArgs a, const double* __restrict__ F, double* __
   double u[12];
   draw12(a.seed, (uint64_t)r, (uint64_t)k + 1ull, (uint64_t)i, u);
   const int64_t gl = (int64_t)r * Pn + lb;
+  double xn[6];
   for (int j = 0; j < 6; ++j) {
     double xj = x[g * 6 + j];
     double vj = w * v[g * 6 + j] + a.c1 * u[j] * (pbx[g * 6 + j] - xj) +
                 a.c2 * u[6 + j] * (pbx[gl * 6 + j] - xj);
     vj = fmin(fmax(vj, -a.vmax), a.vmax);
     v[g * 6 + j] = vj;
-    x[g * 6 + j] = xj + vj;
+    x[g * 6 + j] = xn[j] = xj + vj;
   }
+  pso_decode(xn, box, r, g, params, skip);
 }
 
-__global__ void k_pso_tick(int32_t* iter) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) iter[0] += 1;
+__global__ void k_pso_tick(int32_t* iter, int32_t n) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) iter[0] += n;
 }
 
 }  // namespace fstat
@@ -240,17 +261,21 @@ extern "C" int pso_stage(fstat_plan_t P, const pso_stage_desc* d, pso_result* re
   (void)eval_blocks(P, mixed);   // occupancy query outside any capture
   PsoArgs a{R, Pn, I, d->ring_k, d->w_start, d->w_end, d->c1, d->c2, d->vmax, d->seed};
   const unsigned nb = (unsigned)((n + 255) / 256);
-  hipLaunchKernelGGL(k_pso_init, dim3(nb), dim3(256), 0, s, a, x, v, pbx, pbf, gbf, iter);
+  hipLaunchKernelGGL(k_pso_init, dim3(nb), dim3(256), 0, s, a, x, v, pbx, pbf, gbf, iter, box,
+                     np_run, params, np, skip);
   const int tpb = ((Pn + 63) / 64) * 64;
   const size_t shmem = sizeof(double) * Pn + sizeof(int) * 2;
-  auto iteration = [&]() -> int {
-    hipLaunchKernelGGL(k_pso_decode, dim3(nb), dim3(256), 0, s, a, x, box, np_run, params, np, skip);
+  // koff: the iteration's place in the current batch of them (a graph, or one)
+  auto iteration = [&](int koff) -> int {
     int r2 = eval_device(P, params, n, np, 0, stride, F, nullptr, 0, mixed, s, skip, false, sur,
                          exact);
     if (r2) return r2;
     hipLaunchKernelGGL(k_pso_update, dim3(R), dim3(tpb), shmem, s, a, F, x, v, pbx, pbf, gbx, gbf,
-                       trace, iter);
-    hipLaunchKernelGGL(k_pso_tick, dim3(1), dim3(64), 0, s, iter);
+                       trace, iter, koff, box, params, skip);
+    return hip_check(hipGetLastError(), "pso launch");
+  };
+  auto tick = [&](int iters) {
+    hipLaunchKernelGGL(k_pso_tick, dim3(1), dim3(64), 0, s, iter, iters);
     return hip_check(hipGetLastError(), "pso launch");
   };
   if (d->use_graph && I > 0) {
@@ -262,7 +287,8 @@ extern "C" int pso_stage(fstat_plan_t P, const pso_stage_desc* d, pso_result* re
       int r2 = hip_check(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal), "begin capture");
       if (r2) return r2;
       int rci = 0;
-      for (int k = 0; k < iters && !rci; ++k) rci = iteration();
+      for (int k = 0; k < iters && !rci; ++k) rci = iteration(k);
+      if (!rci) rci = tick(iters);
       hipError_t ec = hipStreamEndCapture(s, &graph);
       if (!rci) rci = hip_check(ec, "end capture");
       if (!rci) rci = hip_check(hipGraphInstantiate(exec, graph, nullptr, nullptr, 0), "instantiate");
@@ -288,7 +314,7 @@ extern "C" int pso_stage(fstat_plan_t P, const pso_stage_desc* d, pso_result* re
     if (rc) return rc;
   } else {
     for (int k = 0; k < I; ++k)
-      if ((rc = iteration()) || (rc = report_progress(k + 1, I, s))) return rc;
+      if ((rc = iteration(k)) || (rc = report_progress(k + 1, I, s))) return rc;
   }
   // results: run bests in physical units
   std::vector<double> hx((size_t)R * 6), hb((size_t)R * 12);
