@@ -25,14 +25,14 @@ struct Mlp {
   float* m2 = nullptr;
   uint16_t* wbf = nullptr;   // BF16 copies of W2..W4
   float* red = nullptr;      // partial column sums of the backward pass
-  float* splitk = nullptr;   // split-K partial weight gradients [16][256][256]
+  float* splitk = nullptr;   // split-K partial weight gradients [3][16][256][256]
+  int parts_slices = 0, parts_ks = 0;   // slices and splits of the last backward pass
   float* yinf = nullptr;     // outputs of infer()
   int64_t cap_inf = 0;
   float* z[4] = {nullptr, nullptr, nullptr, nullptr};        // pre-activations [B][256]
   uint16_t* h[4] = {nullptr, nullptr, nullptr, nullptr};     // BF16 activations
-  float* dz = nullptr;
-  uint16_t* dzb = nullptr;
-  float* dh = nullptr;
+  float* dz = nullptr;       // one FP32 dZ, where the column sums read it
+  uint16_t* dzb = nullptr;   // BF16 dZ of the three hidden layers
   float* y = nullptr;
   float* dy = nullptr;
   float* sq = nullptr;
@@ -43,7 +43,9 @@ struct Mlp {
   void release();
   void refresh_bf16(hipStream_t s);
   void forward(const float* x, const float* tgt, int B, hipStream_t s);
-  void backward(const float* x, int B, hipStream_t s);
+  static bool fused_sums(int B);
+  void backward(const float* x, int B, double* loss, hipStream_t s);
+  void gradient(hipStream_t s);
   void adam(int t, float lr, hipStream_t s);
   int infer_alloc(int64_t rows);
   void infer(const float* x, int64_t rows, hipStream_t s);   // -> yinf[rows]

@@ -27,20 +27,6 @@ __global__ void k_zero_ull(unsigned long long* p, int n) {
   if (i < n) p[i] = 0ull;
 }
 
-// mean of the per-sample squared errors of one batch -> out[0] (one block)
-__global__ void k_batch_mean(const float* __restrict__ sq, int B, double* __restrict__ out) {
-  __shared__ double red[256];
-  double s = 0.0;
-  for (int i = threadIdx.x; i < B; i += blockDim.x) s += (double)sq[i];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[0] = red[0] / (double)B;
-}
-
 // running (sum of squares, max |error|) over validation batches (one block)
 __global__ void k_val_acc(const float* __restrict__ y, const float* __restrict__ t, int B,
                           double* __restrict__ acc) {
@@ -178,8 +164,7 @@ extern "C" int fstat_surrogate_train(fstat_plan_t P, fstat_surrogate_desc* d, vo
       int64_t off = ((int64_t)st * B) % ntrain;
       float lr = (float)(d->lr * 0.5 * (1.0 + std::cos(M_PI * st / (double)d->steps)));
       net.forward(X + 3 * off, T + off, B, s);
-      hipLaunchKernelGGL(k_batch_mean, dim3(1), dim3(256), 0, s, net.sq, B, loss + st);
-      net.backward(X + 3 * off, B, s);
+      net.backward(X + 3 * off, B, loss + st, s);
       net.adam(st + 1, lr, s);
     }
     for (int64_t off = ntrain; off + B <= ntrain + nval; off += B) {
