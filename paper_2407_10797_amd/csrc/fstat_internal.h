@@ -77,6 +77,24 @@ __host__ __device__ __forceinline__ dd dd_mul_d(dd a, double b) {
   p.lo += a.lo * b;
   return quick_two_sum(p.hi, p.lo);
 }
+// The same without the closing renormalisation and with fused low-order terms,
+// for chains of a few products and sums: lo stays within a few ulp of hi, so the
+// products dropped (lo * lo) are ~1e-31 of the result, as in dd_mul; 4, 3 and 8
+// operations for 9, 7 and 11.
+__host__ __device__ __forceinline__ dd lz_mul(dd a, dd b) {
+  const double p = a.hi * b.hi;
+  return {p, __builtin_fma(a.lo, b.hi, __builtin_fma(a.hi, b.lo, __builtin_fma(a.hi, b.hi, -p)))};
+}
+__host__ __device__ __forceinline__ dd lz_mul_d(dd a, double b) {
+  const double p = a.hi * b;
+  return {p, __builtin_fma(a.lo, b, __builtin_fma(a.hi, b, -p))};
+}
+__host__ __device__ __forceinline__ dd lz_add(dd a, dd b) {
+  FSTAT_NO_CONTRACT
+  dd s = two_sum(a.hi, b.hi);
+  s.lo += a.lo + b.lo;
+  return s;
+}
 __host__ __device__ __forceinline__ dd dd_div(dd a, dd b) {
   FSTAT_NO_CONTRACT
   double q1 = a.hi / b.hi;
@@ -219,61 +237,88 @@ __host__ __device__ __forceinline__ void phase_and_tf(const PartConst& P, double
 // differences across a work item from it, at node positions between bins,
 // where rounding f to a double would move the phase by t_f * 1e-16 f
 // (~1e-9 cycles at t_f ~ 1e8 s).
-__host__ __device__ __forceinline__ dd phase_full(const PartConst& P, dd f, dd& tf,
-                                                  const double* ek = nullptr) {
+//
+// log x of a normal positive x from a table of kLogTab {1 / c, log c}: the top
+// mantissa bits pick c, log(m / c) by six terms in r = m / c - 1, |r| <= 2^-8
+// (remainder 2e-18).  log c has 40 fractional bits and ln 2 is split, so that
+// their sum is exact, and each c is one whose reciprocal rounds to less than
+// 2e-18: what is left is the last rounding, 0.5 ulp as the library's log, in 17
+// operations for its ~70.
+constexpr int kLogTab = 128;
+__device__ __forceinline__ double log_tab(double x, const double2* lt) {
+  const int hi = __double2hiint(x);
+  const double m = __hiloint2double((hi & 0xfffff) | 0x3ff00000, __double2loint(x));
+  const double e = (double)((hi >> 20) - 1023);
+  const double2 t = lt[(hi >> 13) & (kLogTab - 1)];
+  const double r = fma(m, t.x, -1.0);
+  const double q = fma(r, fma(r, fma(r, fma(r, -1.0 / 6.0, 1.0 / 5.0), -0.25), 1.0 / 3.0), -0.5);
+  return fma(e, 0x1.62e42fefa38p-1, t.y) + fma(e, 0x1.ef35793c7673p-45, fma(r * r, q, r));
+}
+// x^{-1/9} within a few ulp: an FP32 estimate (2e-7) and one third-order step
+// on x w^9 = 1 (its remainder, ~20 e^3, is below 1e-18); outside FP32's range the
+// result is not finite and the item is left to the exact loop.
+__device__ __forceinline__ double ninth_root_inv(double x) {
+  const double w = (double)__builtin_amdgcn_exp2f(__builtin_amdgcn_logf((float)x) * (-1.0f / 9.0f));
+  const double w2 = w * w, w4 = w2 * w2;
+  const double e = fma(-(w4 * w4), w * x, 1.0);
+  return fma(w * e, fma(e, 5.0 / 81.0, 1.0 / 9.0), w);
+}
+__device__ __forceinline__ dd phase_full(const PartConst& P, dd f, dd& tf, const double* ek,
+                                         const double2* lt) {
   FSTAT_NO_CONTRACT
-  dd ft = dd_mul_d(f, P.tc);
-  dd x = dd_mul(dd{P.mc_hi, P.mc_lo}, f);
-  double lx = log(x.hi);
-  const double w0 = ek ? 0.0 : exp(lx * (-1.0 / 9.0));   // as in phase_and_tf
-  double y0 = ek ? exp(lx * (-1.0 / 3.0)) : w0 * w0 * w0;
-  dd b = dd_mul(dd_mul_d(two_prod(y0, y0), y0), x);
-  double r = (1.0 - b.hi) - b.lo;
-  dd y = quick_two_sum(y0, y0 * r * (1.0 / 3.0));
-  dd y2 = dd_mul(y, y);
-  dd y3 = dd_mul(y2, y);
-  dd y5 = dd_mul(y3, y2);
-  double xy2 = x.hi * y2.hi;
-  dd tN = dd_mul(dd{P.cN_hi, P.cN_lo}, y5);
-  dd t1 = dd_mul(dd{P.c1_hi, P.c1_lo}, y3);
-  dd t15 = dd_mul(dd{P.c15_hi, P.c15_lo}, y2);
+  const dd ft = lz_mul_d(f, P.tc);
+  const dd x = lz_mul(dd{P.mc_hi, P.mc_lo}, f);
+  const double lx = log_tab(x.hi, lt);
+  const double w0 = ninth_root_inv(x.hi);
+  const double y0 = w0 * w0 * w0;
+  const dd b = lz_mul(lz_mul_d(two_prod(y0, y0), y0), x);
+  const double r = (1.0 - b.hi) - b.lo;
+  const dd y = quick_two_sum(y0, y0 * r * (1.0 / 3.0));
+  const dd y2 = lz_mul(y, y);
+  const dd y3 = lz_mul(y2, y);
+  const dd y5 = lz_mul(y3, y2);
+  const double xy2 = x.hi * y2.hi;
+  const dd tN = lz_mul(dd{P.cN_hi, P.cN_lo}, y5);
+  const dd t1 = lz_mul(dd{P.c1_hi, P.c1_lo}, y3);
+  const dd t15 = lz_mul(dd{P.c15_hi, P.c15_lo}, y2);
   dd te;
   if (ek) {
     te = dd{knot_interp(ek, f.hi), 0.0};
   } else {
-    dd w3 = dd_mul_d(two_prod(w0, w0), w0);
-    double rw = ((y.hi - w3.hi) + (y.lo - w3.lo)) * xy2;
-    dd w = quick_two_sum(w0, w0 * rw * (1.0 / 3.0));
-    te = dd_mul(dd_mul(dd{P.ce_hi, P.ce_lo}, dd_mul(dd_mul(y5, y5), y)), w);
+    const dd w3 = lz_mul_d(two_prod(w0, w0), w0);
+    const double rw = ((y.hi - w3.hi) + (y.lo - w3.lo)) * xy2;
+    const dd w = quick_two_sum(w0, w0 * rw * (1.0 / 3.0));
+    te = lz_mul(lz_mul(dd{P.ce_hi, P.ce_lo}, lz_mul(lz_mul(y5, y5), y)), w);
   }
-  double lnv = P.ln_vfac + lx * (1.0 / 3.0);
+  const double lnv = P.ln_vfac + lx * (1.0 / 3.0);
   // the alpha_4 term reaches ~1e2 cycles: double-double too, so that its
   // rounding does not add ~1e-14-cycle noise between interpolation nodes
-  dd t2d = dd_mul_d(y, P.c2);
-  double t2 = t2d.hi;
-  double t6 = P.c6 * xy2;
-  double small = P.c5 * lnv + t6 * (P.a6k + P.b6 * lnv);
-  dd ph = dd_add(dd_add(dd_add(ft, tN), dd_add(t1, t15)),
-                 dd_add(te, dd_add(t2d, dd{small, 0.0})));
+  const dd t2d = lz_mul_d(y, P.c2);
+  const double t2 = t2d.hi;
+  const double t6 = P.c6 * xy2;
+  const double small = P.c5 * lnv + t6 * (P.a6k + P.b6 * lnv);
+  const dd ph = lz_add(lz_add(lz_add(ft, tN), lz_add(t1, t15)),
+                       lz_add(te, lz_add(t2d, dd{small, 0.0})));
   // t_f in double-double as well: its rounding (1e-8 s at 1e8 s) would turn
   // the orbit angle and the 1000-s Doppler term into ~1e-13-cycle noise
-  dd D = dd_add(dd_add(dd_mul_d(tN, -5.0 / 3.0), dd{-t1.hi, -t1.lo}),
-                dd_add(dd_mul_d(t15, -2.0 / 3.0), dd_mul_d(te, -34.0 / 9.0)));
-  D = dd_add(D, dd{-(1.0 / 3.0) * t2 + P.c5v5 + t6 * (P.a6k + P.b6 + P.b6 * lnv) * (1.0 / 3.0), 0.0});
-  tf = dd_add(dd{P.tc, 0.0}, dd_mul(D, dd_mul(dd{P.mc_hi, P.mc_lo}, y3)));
-  return ph;
+  dd D = lz_add(lz_add(lz_mul_d(tN, -5.0 / 3.0), dd{-t1.hi, -t1.lo}),
+                lz_add(lz_mul_d(t15, -2.0 / 3.0), lz_mul_d(te, -34.0 / 9.0)));
+  D = lz_add(D, dd{-(1.0 / 3.0) * t2 + P.c5v5 + t6 * (P.a6k + P.b6 + P.b6 * lnv) * (1.0 / 3.0), 0.0});
+  tf = lz_add(dd{P.tc, 0.0}, lz_mul(D, lz_mul(dd{P.mc_hi, P.mc_lo}, y3)));
+  tf = quick_two_sum(tf.hi, tf.lo);
+  return quick_two_sum(ph.hi, ph.lo);
 }
 
 // The same phase and t_f in plain FP64 (whole cycles kept): at ~1e7 cycles
 // the phase rounds to ~2e-9 cycles, enough where the sine is taken in FP32
 // (~6e-8 turns).  y = x^{-1/3} from w0^3 with one Newton step, as above.
-__host__ __device__ __forceinline__ double phase_full_fp64(const PartConst& P, double f,
-                                                           double& tf,
-                                                           const double* ek = nullptr) {
+__device__ __forceinline__ double phase_full_fp64(const PartConst& P, double f,
+                                                  double& tf, const double* ek,
+                                                  const double2* lt) {
   const double x = P.mc_hi * f;
-  const double lx = log(x);
-  const double w0 = ek ? 0.0 : exp(lx * (-1.0 / 9.0));
-  const double y0 = ek ? exp(lx * (-1.0 / 3.0)) : w0 * w0 * w0;
+  const double lx = log_tab(x, lt);
+  const double w0 = ninth_root_inv(x);
+  const double y0 = w0 * w0 * w0;
   const double r = fma(-(y0 * y0) * y0, x, 1.0);
   const double y = fma(y0 * r, 1.0 / 3.0, y0);
   const double y2 = y * y, y3 = y2 * y, y5 = y3 * y2;
@@ -410,9 +455,14 @@ __device__ __forceinline__ void sincos_tab(double r, const double2* tab, double&
   c = fma(e.y, cl, -(e.x * sl));
 }
 
-// sin(pi x), cos(pi x): from the table when one is given, else the library.
+// sin(pi x), cos(pi x): from the table when one is given, else the library.  TAB:
+// one is always given; without the test the library's code and registers drop
+// out (the node kernel).  The exact loop keeps the test: its removal merges code
+// in which the compiler then fuses other products, and F of ill-conditioned
+// partitions moves by eps cond(M) with each such choice.
+template <bool TAB>
 __device__ __forceinline__ void sincospi_t(double x, const double2* tab, double* s, double* c) {
-  if (tab) sincos_tab(0.5 * x, tab, *s, *c);
+  if (TAB || tab) sincos_tab(0.5 * x, tab, *s, *c);
   else sincospi(x, s, c);
 }
 
@@ -469,6 +519,7 @@ __device__ __forceinline__ void channel_weights(int code, double w[3]) {
 // takes L n for the arm vector on the analytic (rigid) constellation, the arm
 // vector itself when `table` (a numerical orbit, whose arms need not have
 // length L).
+template <bool TAB>
 __device__ __forceinline__ void michelson_fp64(const PartConst& P, double f, double s0, double c0,
                                                const double d[3][3], int a, double& tpr,
                                                double& tpi, double& txr, double& txi,
@@ -488,7 +539,7 @@ __device__ __forceinline__ void michelson_fp64(const PartConst& P, double f, dou
     double un = P.u[0] * ax + P.u[1] * ay + P.u[2] * az;
     double vn = P.v[0] * ax + P.v[1] * ay + P.v[2] * az;
     double sq, cq;
-    sincospi_t(kLs * f * kn, tab, &sq, &cq);
+    sincospi_t<TAB>(kLs * f * kn, tab, &sq, &cq);
     double np_ = s0 * cq + c0 * sq, nm = s0 * cq - c0 * sq;   // sin(x0 (1 +- kn))
     double dp = x0 * (1.0 + kn), dm = x0 * (1.0 - kn);
     double sp, sm;
@@ -503,7 +554,7 @@ __device__ __forceinline__ void michelson_fp64(const PartConst& P, double f, dou
     double Sr = sp + zr * sm, Si = zi * sm;
     if (table) {   // link phase from the arm vector: rotate by exp(-i pi f kn (|d| - L))
       double se, ce;
-      sincospi_t(f * kn * (r2 * inv - kLs), tab, &se, &ce);
+      sincospi_t<TAB>(f * kn * (r2 * inv - kLs), tab, &se, &ce);
       const double tr = sq * ce + cq * se, tc = cq * ce - sq * se;
       sq = tr;
       cq = tc;
@@ -520,7 +571,7 @@ __device__ __forceinline__ void michelson_fp64(const PartConst& P, double f, dou
   if (a != 0) {
     const double kd = kx * (d[a][0] - d[0][0]) + ky * (d[a][1] - d[0][1]) + kz * (d[a][2] - d[0][2]);
     double sv, cv;
-    sincospi_t(2.0 * f * kd, tab, &sv, &cv);   // e^{-i 2 pi f kd} = cv - i sv
+    sincospi_t<TAB>(2.0 * f * kd, tab, &sv, &cv);   // e^{-i 2 pi f kd} = cv - i sv
     const double r0 = pr * cv + pi * sv, i0 = pi * cv - pr * sv;
     const double r1 = xr * cv + xi * sv, i1 = xi * cv - xr * sv;
     pr = r0; pi = i0; xr = r1; xi = i1;
@@ -529,10 +580,16 @@ __device__ __forceinline__ void michelson_fp64(const PartConst& P, double f, dou
 }
 
 // Transfer of channel `code` (relative to the phase reference p_1).
+template <bool TAB>
 __device__ __forceinline__ void response_ch_fp64(const PartConst& P, double f, double s0, double c0,
                                                  const double d[3][3], int code, double& tpr,
                                                  double& tpi, double& txr, double& txi,
                                                  bool table = false, const double2* tab = nullptr) {
+  // all lanes at X (the node kernel): one copy with its spacecraft known
+  if (TAB && __builtin_amdgcn_ballot_w64(code != 0) == 0) {
+    michelson_fp64<TAB>(P, f, s0, c0, d, 0, tpr, tpi, txr, txi, table, tab);
+    return;
+  }
   double w[3];
   channel_weights(code, w);
   tpr = tpi = txr = txi = 0.0;
@@ -542,7 +599,7 @@ __device__ __forceinline__ void response_ch_fp64(const PartConst& P, double f, d
   for (int a = 0; a < 3; ++a) {
     if (w[a] == 0.0) continue;
     double pr, pi, xr, xi;
-    michelson_fp64(P, f, s0, c0, d, a, pr, pi, xr, xi, table, tab);
+    michelson_fp64<TAB>(P, f, s0, c0, d, a, pr, pi, xr, xi, table, tab);
     tpr = fma(w[a], pr, tpr); tpi = fma(w[a], pi, tpi);
     txr = fma(w[a], xr, txr); txi = fma(w[a], xi, txi);
   }
@@ -629,13 +686,13 @@ __device__ __forceinline__ void template_fp64(const PartConst& P, double f, doub
     kp1 = k_dot_p1_table(P, *orb, tf, 0.0, d);
   } else {
     double sa, ca;
-    sincospi_t(2.0 * tf * (1.0 / kYear), tab, &sa, &ca);
+    sincospi_t<false>(2.0 * tf * (1.0 / kYear), tab, &sa, &ca);
     kp1 = k_dot_p1(P, ca, sa, d);
   }
   double ph = fr + f * kp1;               // Phi / (2 pi) in cycles
   ph -= rint(ph);
-  sincospi_t(2.0 * ph, tab, &sph, &cph);
-  response_ch_fp64(P, f, s0, c0, d, code, tpr, tpi, txr, txi, orb && orb->coef, tab);
+  sincospi_t<false>(2.0 * ph, tab, &sph, &cph);
+  response_ch_fp64<false>(P, f, s0, c0, d, code, tpr, tpi, txr, txi, orb && orb->coef, tab);
 }
 
 // The template at an arbitrary frequency fd (double-double; an interpolation
@@ -643,10 +700,10 @@ __device__ __forceinline__ void template_fp64(const PartConst& P, double f, doub
 // (double-double, not reduced) and the transfer without the Doppler factor.
 __device__ __forceinline__ dd template_node(const PartConst& P, dd fd, const double* ek,
                                             double& tpr, double& tpi, double& txr, double& txi,
-                                            int code = 0, const OrbitTable* orb = nullptr,
-                                            const double2* tab = nullptr) {
+                                            int code, const OrbitTable* orb, const double2* tab,
+                                            const double2* lt) {
   dd tf;
-  dd ph = phase_full(P, fd, tf, ek);
+  dd ph = phase_full(P, fd, tf, ek, lt);
   const double f = fd.hi;
   double d[3][3];
   double kp1;
@@ -657,36 +714,36 @@ __device__ __forceinline__ dd template_node(const PartConst& P, dd fd, const dou
     {
       FSTAT_NO_CONTRACT
       const dd turns = dd_mul_d(tf, 1.0 / kYear);     // orbit angle in turns, reduced exactly
-      sincospi_t(2.0 * ((turns.hi - floor(turns.hi)) + turns.lo), tab, &sa, &ca);
+      sincospi_t<true>(2.0 * ((turns.hi - floor(turns.hi)) + turns.lo), tab, &sa, &ca);
     }
     kp1 = k_dot_p1(P, ca, sa, d);
   }
   double s0, c0;
-  sincospi_t(kLs * f, tab, &s0, &c0);
-  response_ch_fp64(P, f, s0, c0, d, code, tpr, tpi, txr, txi, orb && orb->coef, tab);
+  sincospi_t<true>(kLs * f, tab, &s0, &c0);
+  response_ch_fp64<true>(P, f, s0, c0, d, code, tpr, tpi, txr, txi, orb && orb->coef, tab);
   return dd_add(ph, dd_mul_d(fd, kp1));
 }
 
 // The same node template in plain FP64 (the mixed path's interpolation nodes).
 __device__ __forceinline__ double template_node_fp64(const PartConst& P, double f, const double* ek,
                                                      double& tpr, double& tpi, double& txr,
-                                                     double& txi, int code = 0,
-                                                     const OrbitTable* orb = nullptr,
-                                                     const double2* tab = nullptr) {
+                                                     double& txi, int code,
+                                                     const OrbitTable* orb, const double2* tab,
+                                                     const double2* lt) {
   double tf;
-  const double ph = phase_full_fp64(P, f, tf, ek);
+  const double ph = phase_full_fp64(P, f, tf, ek, lt);
   double d[3][3];
   double kp1;
   if (orb && orb->coef) {
     kp1 = k_dot_p1_table(P, *orb, tf, 0.0, d);
   } else {
     double sa, ca;
-    sincospi_t(2.0 * tf * (1.0 / kYear), tab, &sa, &ca);
+    sincospi_t<true>(2.0 * tf * (1.0 / kYear), tab, &sa, &ca);
     kp1 = k_dot_p1(P, ca, sa, d);
   }
   double s0, c0;
-  sincospi_t(kLs * f, tab, &s0, &c0);
-  response_ch_fp64(P, f, s0, c0, d, code, tpr, tpi, txr, txi, orb && orb->coef, tab);
+  sincospi_t<true>(kLs * f, tab, &s0, &c0);
+  response_ch_fp64<true>(P, f, s0, c0, d, code, tpr, tpi, txr, txi, orb && orb->coef, tab);
   return fma(f, kp1, ph);
 }
 

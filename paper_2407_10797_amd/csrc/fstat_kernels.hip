@@ -575,6 +575,7 @@ __device__ __forceinline__ double wave_sum4(const double* a, int lane, int& idx)
 // bin or node; the FP64 per-bin loop needs it only in the per-lane set-up of
 // the difference recurrence and in the direct form (its LDS holds the tile)
 __constant__ double2 c_sincos[kSinTab];
+__constant__ double2 c_logtab[kLogTab];
 // the same from the library's sincospi, for the exact loop (filled once per
 // device; filling it in every block took 2 us of each launch)
 __device__ double2 d_sincos[kSinTab];
@@ -1135,6 +1136,14 @@ constexpr double kInterpTolTMixed = 3e-8;
 // the plan has a numerical orbit (a separate instance keeps the table code
 // out of the analytic kernel's registers).
 //
+// Bound by FP64 issue (~1,600 vector operations per five items, 456 B written per
+// item) and, below that, by how many waves cover its dependent chains: what kept
+// it at two waves per SIMD was values held across the per-particle loop and the
+// library's sine and logarithm, so the loop hands its results over in LDS and
+// sine, logarithm and x^{-1/9} come from tables and a third-order step; three
+// waves with numerical orbits' tables would spill (orbit batch 1.29 -> 1.48 ms).
+// 1.67 M items FP64: 1.71 -> 1.30 ms; 0.97 M mixed: 0.85 -> 0.59 ms.
+//
 // With block spectra (sp.L > 0) an item goes to the block loop when over any
 // of its blocks the phase stays within sp.psi radians of a straight line and
 // its slope within half a slot of the spectra's range; otherwise to the
@@ -1142,9 +1151,15 @@ constexpr double kInterpTolTMixed = 3e-8;
 struct SpecShape {
   int32_t L, Q, nslots, nblk;
   double psi;
+  double hq, smax;      // half a slot of the slope grid, its last slot
 };
+// a / n for 0 <= a < 2^31 and n >= 1 from rn = 1 / n: (a + 1/2) / n is at least
+// 1 / (2 n) from a whole number, the product's error below 2^-20 of that (4
+// operations; an integer division takes ~25)
+__device__ __forceinline__ int div_by(int a, double rn) { return (int)(((double)a + 0.5) * rn); }
+
 template <bool MIXED, bool TAB>
-__global__ __launch_bounds__(256, 2) void k_interp_nodes(Grid g,
+__global__ __launch_bounds__(256, TAB ? 2 : 3) void k_interp_nodes(Grid g,
                                                       const PartConst* __restrict__ pc,
                                                       const int32_t* __restrict__ bounds,
                                                       int32_t stride,
@@ -1159,7 +1174,7 @@ __global__ __launch_bounds__(256, 2) void k_interp_nodes(Grid g,
                                                       int32_t* __restrict__ ndirect,
                                                       UModel um,
                                                       double* __restrict__ partials,
-                                                      SpecShape sp) {
+                                                      SpecShape sp, double rstride, double rT) {
   const int lane = threadIdx.x & 63;
   const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int nwaves = (gridDim.x * blockDim.x) >> 6;
@@ -1187,20 +1202,35 @@ __global__ __launch_bounds__(256, 2) void k_interp_nodes(Grid g,
       s_rt[0][kn][kk] = c_row4[kn][kk];
     }
   }
+  __shared__ double2 s_log[kLogTab];
   for (int i = threadIdx.x; i < kSinTab; i += blockDim.x) s_tab[i] = c_sincos[i];
+  for (int i = threadIdx.x; i < kLogTab; i += blockDim.x) s_log[i] = c_logtab[i];
   __syncthreads();
   const int q = min(lane / kLanesItem, kItemsWave - 1);
   const int k = min(lane - q * kLanesItem, kLanesItem - 1);
   const int base = q * kLanesItem;
+  // a group's items are loaded two groups ahead and its bounds one ahead
+  auto item_of = [&](int grp) { return items[min(min(grp, G - 1) * kItemsWave + q, W - 1)]; };
+  auto bounds_of = [&](int2 it, int& p) {
+    p = div_by(it.x, rstride);
+    const int32_t* bp = bounds + (int64_t)p * (stride + 1) + (it.x - p * stride);
+    return make_int2(bp[0], bp[1]);
+  };
+  if (wave >= G) return;
+  int2 it1 = item_of(wave), it2 = item_of(wave + nwaves);
+  int p1;
+  int2 bd1 = bounds_of(it1, p1);
   for (int grp = wave; grp < G; grp += nwaves) {
     const int w = min(grp * kItemsWave + q, W - 1);
-    const int2 it = items[w];
-    const int p = it.x / stride, l = it.x - p * stride;
-    const int32_t* bp = bounds + (int64_t)p * (stride + 1);
-    int ct, ch;
-    item_split(it.y, g.chan.n, ct, ch);
-    int b0, b1;
-    item_bins(bp[l], bp[l + 1], ct, T, b0, b1);
+    const int2 it = it1, bd = bd1;
+    const int p = p1;
+    it1 = it2;
+    it2 = item_of(grp + 2 * nwaves);
+    bd1 = bounds_of(it1, p1);
+    int ct = it.y, ch = 0;
+    if (g.chan.n > 1) item_split(it.y, g.chan.n, ct, ch);
+    const int bt = (div_by(bd.x, rT) + ct) * T;                 // item_bins
+    const int b0 = max(bd.x, bt), b1 = min(bd.y, bt + T);
     const int nb = b1 - b0;
     if (!__any(nb >= kMinInterp)) {
       // no item of this group is long enough to interpolate: all of them go
@@ -1215,8 +1245,8 @@ __global__ __launch_bounds__(256, 2) void k_interp_nodes(Grid g,
     const double mk = (sk + 1.0) * 0.5 * (double)(nb > 1 ? nb - 1 : 0);
     // exact frequency (k_lo + b0 + mk) df of the node, as double-double
     const dd f = dd_add(two_prod((double)(g.k_lo + b0), g.df), two_prod(mk, g.df));
-    double v[5], v0lo;
-    dd ph;
+    // (their results go through the lane's slots: carried in registers, the
+    // earlier turns' values would be live beside those being formed)
     // the lanes of one particle at a time (nearly always all of them): its
     // constants come through the scalar cache into scalar registers
     for (uint64_t todo = __ballot(true); todo != 0;) {
@@ -1228,20 +1258,27 @@ __global__ __launch_bounds__(256, 2) void k_interp_nodes(Grid g,
       if (p == pu) {
         const PartConst P = load_particle(kp);
         const double* ekq = (ek && P.sur) ? ek + 8 * (int64_t)it.x : nullptr;
+        double t1, t2, t3, t4;
+        dd ph;
         if constexpr (MIXED)
-          ph = dd{template_node_fp64(P, f.hi, ekq, v[1], v[2], v[3], v[4], g.chan.code[ch],
-                                     TAB ? &g.orb : nullptr, s_tab), 0.0};
+          ph = dd{template_node_fp64(P, f.hi, ekq, t1, t2, t3, t4, g.chan.code[ch],
+                                     TAB ? &g.orb : nullptr, s_tab, s_log), 0.0};
         else
-          ph = template_node(P, f, ekq, v[1], v[2], v[3], v[4], g.chan.code[ch],
-                             TAB ? &g.orb : nullptr, s_tab);
+          ph = template_node(P, f, ekq, t1, t2, t3, t4, g.chan.code[ch],
+                             TAB ? &g.orb : nullptr, s_tab, s_log);
+        my_nd[0] = ph.hi; my_nd[1] = ph.lo;
+        my_nd[2] = t1; my_nd[3] = t2; my_nd[4] = t3; my_nd[5] = t4;
       }
     }
-    const double p0h = __shfl(ph.hi, base + kCheb, 64);
-    const double p0l = __shfl(ph.lo, base + kCheb, 64);
-    const double peh = __shfl(ph.hi, base + kCheb + 1, 64);
-    const double pel = __shfl(ph.lo, base + kCheb + 1, 64);
+    __builtin_amdgcn_wave_barrier();
+    const dd ph{my_nd[0], my_nd[1]};
+    double v0lo, v[5] = {0.0, my_nd[2], my_nd[3], my_nd[4], my_nd[5]};
+    const double* item_nd = s_nd[threadIdx.x >> 6][base];
+    const double p0h = item_nd[kNd * kCheb], p0l = item_nd[kNd * kCheb + 1];
+    const double peh = item_nd[kNd * (kCheb + 1)], pel = item_nd[kNd * (kCheb + 1) + 1];
     const dd span = dd_add(dd{peh, pel}, dd{-p0h, -p0l});
-    const double B = nb > 1 ? (span.hi + span.lo) / (double)(nb - 1) : 0.0;
+    const double rnb = nb > 1 ? 1.0 / (double)(nb - 1) : 0.0;
+    const double B = (span.hi + span.lo) * rnb;    // R below is relative to this very B
     {
       const dd bm = two_prod(B, mk);
       const dd r = dd_add(dd_add(ph, dd{-p0h, -p0l}), dd{-bm.hi, -bm.lo});
@@ -1259,8 +1296,8 @@ __global__ __launch_bounds__(256, 2) void k_interp_nodes(Grid g,
       const int ut0 = b0 / kUTile, ut1 = (b1 - 1) / kUTile;
       ufit = ufit && ut1 < um.ntiles &&
              (um.bad_prefix[ub + ut1 + 1] - um.bad_prefix[ub + ut0]) == 0;
-      if (ufit)   // largest fit residual over the item's u-tiles (12 lanes share the scan)
-        for (int ut = ut0 + k; ut <= ut1; ut += kLanesItem) ures = fmax(ures, um.resid[ub + ut]);
+      if (ufit && k < kCheb)   // largest fit residual over the item's u-tiles (the node lanes share the scan)
+        for (int ut = ut0 + k; ut <= ut1; ut += kCheb) ures = fmax(ures, um.resid[ub + ut]);
       const double x = (double)b0 + mk;
       const int ut = min(max((int)(x * (1.0 / kUTile)), 0), max(um.ntiles - 1, 0));
       const double loc = 2.0 * (x - (double)ut * kUTile) / (double)(kUTile - 1) - 1.0;
@@ -1284,21 +1321,20 @@ __global__ __launch_bounds__(256, 2) void k_interp_nodes(Grid g,
     // few cycles, the node-to-monomial map has entries of a few hundred, and a
     // plain double sum would leave ~1e-13 cycles of cancellation error in the
     // coefficients.  Mixed path: a plain sum (its tolerance is 1e-9 cycles).
-    double aRs = 0.0, aRx = 0.0, tmax = 0.0, gmax = 0.0;
+    double aRs = 0.0, aRx = 0.0, tmax = 0.0, gmax = 0.0, umax = 0.0;
     double aT[4], aTt[2][4], aG[4];
 #pragma unroll
     for (int fn = 0; fn < 4; ++fn) {
       aT[fn] = 0.0; aG[fn] = 0.0; aTt[0][fn] = 0.0; aTt[1][fn] = 0.0;
     }
+    __builtin_amdgcn_wave_barrier();
     my_nd[0] = v[0]; my_nd[1] = v0lo;
-    my_nd[2] = v[1]; my_nd[3] = v[2]; my_nd[4] = v[3]; my_nd[5] = v[4];
     my_nd[6] = gq[0]; my_nd[7] = gq[1]; my_nd[8] = gq[2]; my_nd[9] = gq[3];
-    my_nd[10] = wq;
+    my_nd[10] = wq; my_nd[11] = ures;
     // the node's largest transfer component and |M-term integrand|
     my_nd[12] = fmax(fmax(fabs(v[1]), fabs(v[2])), fmax(fabs(v[3]), fabs(v[4])));
     my_nd[13] = fmax(fabs(gq[0]), fabs(gq[1]));
     __builtin_amdgcn_wave_barrier();
-    const double* item_nd = s_nd[threadIdx.x >> 6][base];
     // two nodes per pass (their LDS reads overlap); unrolled fully, the loop
     // hoists every node's table loads and needs more registers than the kernel
     // can hold at a useful occupancy
@@ -1330,6 +1366,7 @@ __global__ __launch_bounds__(256, 2) void k_interp_nodes(Grid g,
       }
       tmax = fmax(tmax, ncd.x);
       gmax = fmax(gmax, ncd.y);
+      umax = fmax(umax, nab.y);
       const double rg = fma(sel0, nab.x, selE * r9);
       const double gt[4] = {n67.x, n67.y, n89.x, n89.y};
 #pragma unroll
@@ -1358,7 +1395,7 @@ __global__ __launch_bounds__(256, 2) void k_interp_nodes(Grid g,
     double errt[2] = {0.0, 0.0};   // transfer error of the degree-5 and -7 (mixed: 4) truncations
     double gerr = 0.0;          // M-term integrands' error (relative to max u |T|^2)
     if (k >= kCheb) {
-      const double itmax = 1.0 / tmax;      // the estimates below need no correct rounding
+      const double itmax = rcp_nr(tmax);      // the estimates below need no correct rounding
       // (aRs - v0 is exact wherever the interpolant is close enough to pass)
       const double dph = fabs(((aRs - v[0]) + aRx) - v0lo);
       bad = !(dph <= tolP);
@@ -1374,13 +1411,11 @@ __global__ __launch_bounds__(256, 2) void k_interp_nodes(Grid g,
       }
 #pragma unroll
       for (int fn = 0; fn < 4; ++fn) gerr = fmax(gerr, fabs(aG[fn] - gq[fn]));
-      gerr = gmax > 0.0 ? gerr / gmax : (gerr > 0.0 ? 1.0 : 0.0);
+      gerr = gmax > 0.0 ? gerr * rcp_nr(gmax) : (gerr > 0.0 ? 1.0 : 0.0);
     }
     const double tolG = MIXED ? kInterpTolTMixed : 4.0 * kInterpTolT;
     const uint64_t gbadmask = __ballot(k >= kCheb && !(gerr <= tolG));
-    gerr = fmax(gerr, __shfl(gerr, base + kCheb + 1, 64));
-#pragma unroll
-    for (int kk = 0; kk < kLanesItem; ++kk) gerr = fmax(gerr, __shfl(ures, base + kk, 64));
+    gerr = fmax(fmax(gerr, __shfl(gerr, base + kCheb + 1, 64)), umax);
     const uint64_t badmask = __ballot(bad);
     err = fmax(__shfl(err, base + kCheb, 64), __shfl(err, base + kCheb + 1, 64));
     double gsum[4];
@@ -1422,16 +1457,15 @@ __global__ __launch_bounds__(256, 2) void k_interp_nodes(Grid g,
       }
     } else if (k == kCheb) {
       FSTAT_NO_CONTRACT
-      const double alpha = nb > 1 ? 2.0 / (double)(nb - 1) : 0.0;
+      const double alpha = 2.0 * rnb;
       r[L::tail] = (p0h - floor(p0h)) + p0l;     // fractional cycle at the first bin
       r[L::tail + 1] = B - rint(B);              // whole cycles per bin drop out (m is an integer)
       r[L::tail + 2] = B;
       bool blocks = false;
       if (sp.L > 0) {
         const double half = 0.5 * (double)(sp.L - 1) * alpha;
-        const double hq = 0.5 / (double)sp.Q, sl = alpha * d1;
-        blocks = kPi * d2 * half * half <= sp.psi && B - sl >= -hq &&
-                 B + sl <= (double)(sp.nslots - 1) / (double)sp.Q + hq;
+        const double sl = alpha * d1;
+        blocks = kPi * d2 * half * half <= sp.psi && B - sl >= -sp.hq && B + sl <= sp.smax + sp.hq;
       }
       const int state = rej ? kRecExact : (blocks ? kRecBlocks : kRecBins);
       int2* ri = reinterpret_cast<int2*>(r + L::tail + 3);
@@ -1445,7 +1479,7 @@ __global__ __launch_bounds__(256, 2) void k_interp_nodes(Grid g,
       // at the end points times max u |T|^2 times the bin count (see k_mark)
       const int64_t uo = (int64_t)ch * (g.nbins + 1);
       const double U = um.upre ? fmax(um.upre[uo + b1] - um.upre[uo + b0], 0.0) : (double)nb;
-      xerr[w] = make_float2((float)(err * tmax * sqrt(U)), mq ? (float)(gerr * gmax * nb) : 0.0f);
+      xerr[w] = make_float2((float)(err * tmax * __builtin_amdgcn_sqrt(U)), mq ? (float)(gerr * gmax * nb) : 0.0f);
       if (rej) direct[atomicAdd(ndirect, 1)] = w;
     }
   }
@@ -2714,6 +2748,22 @@ int interp_tables_init() {
     }
     if (hipMemcpyToSymbol(HIP_SYMBOL(c_sincos), tab, sizeof(tab)) != hipSuccess) return -1;
   }
+  {
+    double2 tab[kLogTab];
+    for (int i = 0; i < kLogTab; ++i) {
+      const double y0 = rint((double)ldexpl(logl(1.0L + (i + 0.5L) / kLogTab), 40));
+      long double best = 1.0L;
+      for (int j = -64; j <= 64; ++j) {      // log c near the interval's middle, best 1 / c
+        const double y = ldexp(y0 + j, -40);
+        const long double rc = expl(-(long double)y), e = fabsl(rc - (long double)(double)rc);
+        if (e < best) {
+          best = e;
+          tab[i] = make_double2((double)rc, y);
+        }
+      }
+    }
+    if (hipMemcpyToSymbol(HIP_SYMBOL(c_logtab), tab, sizeof(tab)) != hipSuccess) return -1;
+  }
   if (hipMemcpyToSymbol(HIP_SYMBOL(c_row6), R6, sizeof(R6)) != hipSuccess) return -1;
   // truncations after degree 5 and 7 (FP64 loop)
   double Gt[2][kCheb][kCheb], Et[2][2][kCheb];
@@ -3201,15 +3251,17 @@ void launch_eval(bool mixed, bool interp, double refine_budget, const Grid& g,
     SpecShape sp{};
     const int32_t L = mixed ? s32.L : s64.L;
     if (L > 0 && chunk % L == 0)
-      sp = mixed ? SpecShape{L, s32.Q, s32.nslots, s32.nblk, kSpecPsiMixed}
-                 : SpecShape{L, s64.Q, s64.nslots, s64.nblk, kSpecPsiFp64};
+      sp = mixed ? SpecShape{L, s32.Q, s32.nslots, s32.nblk, kSpecPsiMixed, 0.5 / s32.Q,
+                             (double)(s32.nslots - 1) / s32.Q}
+                 : SpecShape{L, s64.Q, s64.nslots, s64.nblk, kSpecPsiFp64, 0.5 / s64.Q,
+                             (double)(s64.nslots - 1) / s64.Q};
     {
       const bool tab = g.orb.coef != nullptr;
       auto nodes = mixed ? (tab ? k_interp_nodes<true, true> : k_interp_nodes<true, false>)
                          : (tab ? k_interp_nodes<false, true> : k_interp_nodes<false, false>);
       hipLaunchKernelGGL(nodes, dim3(8 * blocks), dim3(256), 0, s, g, ws.pc, ws.bounds, stride,
                          ws.items, ws.total, chunk, ek, ws.rec, ws.xflag, ws.xerr, ws.direct,
-                         ws.ndirect, um, ws.partials, sp);
+                         ws.ndirect, um, ws.partials, sp, 1.0 / (double)stride, 1.0 / (double)chunk);
     }
     if (n_particles * (int64_t)(ntiles + stride * g.chan.n) <= kGroupOnce && 2 * ntiles <= kTileHist) {
       hipLaunchKernelGGL(k_tile_group, dim3(1), dim3(1024), 0, s, ws.items, ws.total, ws.xflag,
