@@ -105,8 +105,9 @@ typedef struct {
 typedef struct {
   int32_t precision;   /* mask of FSTAT_FP64 | FSTAT_MIXED; 0 = both           */
   uint32_t flags;      /* FSTAT_DEVICE_PTRS: data/psd are device pointers      */
-  int32_t chunk;       /* bins per work item (bin tile); 0 = 2048, or 2560 FP64
-                          and 5120 mixed where the plan has block spectra   */
+  int32_t chunk;       /* bins per work item (bin tile); 0 = 2048, or 2560 where
+                          the plan has block spectra (then an item may span
+                          several tiles)                                     */
   int32_t reserved;
   double refine_budget; /* FP64 interpolating loop: partitions where the
                            interpolation error could move F by more than this

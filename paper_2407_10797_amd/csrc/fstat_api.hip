@@ -253,18 +253,27 @@ static int check_chunk(const fstat_plan_s* P, bool mixed, bool exact) {
   return FSTAT_OK;
 }
 
+// The tiling of an evaluation.  With a size that the caller chose, without spectra
+// and in the exact loop an item is one tile's; the plan's own sizes are widened per
+// partition.
+static Tiling tiling_for(const fstat_plan_s* P, bool mixed, bool exact) {
+  const int chunk = chunk_for(P, mixed);
+  const bool given = P->chunk_given && !(mixed && P->chunk_mixed > 0);
+  const int32_t L = mixed ? P->s32.L : P->s64.L;
+  return make_tiling(P->grid, chunk, !exact && !given && L > 0 && chunk % L == 0, mixed);
+}
+
 // Enqueue the kernels of one evaluation on workspace `ws` (device pointers).
 static int eval_enqueue(fstat_plan_s* P, const WorkSpace& ws, const double* params, int64_t n,
                         const int32_t* np, int32_t np_uniform, int32_t stride, double* F_hat,
                         double* F_part, int64_t part_stride, bool mixed, hipStream_t s,
                         const uint8_t* skip, bool allow_profile, bool surrogate, bool exact,
                         double* amps) {
-  const int chunk = chunk_for(P, mixed);
+  const Tiling tl = tiling_for(P, mixed, exact);
   int rc;
-  launch_setup(P->grid, params, n, np, np_uniform, stride, chunk, skip, ws, s);
+  launch_setup(P->grid, params, n, np, np_uniform, stride, tl, skip, ws, s);
   if (surrogate && (rc = sur_prepare(P, n, stride, s))) return rc;
-  launch_worklist(n, stride, ws, exact,
-                  (int32_t)((P->grid.nbins + chunk - 1) / chunk) * P->grid.chan.n, s);
+  launch_worklist(n, stride, tl, P->grid.chan.n, ws, exact, s);
   // profiling: the whole bin-loop stage (e[0], e[3]) and its main kernel (e[1], e[2])
   std::array<hipEvent_t, 4> ev = {nullptr, nullptr, nullptr, nullptr};
   const bool prof = P->profile && allow_profile;
@@ -281,7 +290,7 @@ static int eval_enqueue(fstat_plan_s* P, const WorkSpace& ws, const double* para
   um.ssum = cheb_sums_table();
   if (!um.ssum) um.coef = nullptr;
   um.upre = P->upre;
-  launch_eval(mixed, !exact, P->refine_budget, P->grid, n, stride, chunk, ws, P->b64, P->b32,
+  launch_eval(mixed, !exact, P->refine_budget, P->grid, n, stride, tl, ws, P->b64, P->b32,
               surrogate ? P->sur_ek : nullptr, eval_blocks(P, mixed), s,
               prof ? &ev[1] : nullptr, um, P->s64, P->s32);
   if (prof) {
@@ -307,7 +316,7 @@ int eval_device(fstat_plan_s* P, const double* params, int64_t n, const int32_t*
   if (surrogate && (rc = sur_ensure(P, n, stride))) return rc;
   P->last.n = n;
   P->last.stride = stride;
-  P->last.chunk = chunk_for(P, mixed);
+  P->last.tiling = tiling_for(P, mixed, exact);
   P->last.mixed = mixed;
   P->last.exact = exact;
   return eval_enqueue(P, P->ws, params, n, np, np_uniform, stride, F_hat, F_part, part_stride,
@@ -407,7 +416,8 @@ int fstat_autotune(fstat_plan_t P, const double* params, int64_t n, int32_t np_u
     static const int chunks[] = {256, 512, 1024, 2048, 2560, 4096, 4608, 5120, 8192};
     static const int mults[] = {1, 2, 4};
     // tiles above the per-bin loop's LDS stage only where the block loop takes the items
-    const int tile_limit = mixed && P->s32.L > 0 ? kSpecChunkMixed : interp_max_tile(mixed);
+    constexpr int kTuneMixed = 5120;
+    const int tile_limit = mixed && P->s32.L > 0 ? kTuneMixed : interp_max_tile(mixed);
     double* F = nullptr;
     int rc = hip_check(hipMalloc(&F, sizeof(double) * n), "alloc tune out");
     hipEvent_t e0, e1;
@@ -423,7 +433,7 @@ int fstat_autotune(fstat_plan_t P, const double* params, int64_t n, int32_t np_u
     for (int ex = exact ? 1 : 0; ex <= ((exact || mode) ? 1 : 0) && !rc; ++ex)
       for (int ci = 0; ci < (int)(sizeof(chunks) / sizeof(chunks[0])) && !rc; ++ci)
         for (int mi = 0; mi < 3 && !rc; ++mi) {
-          if (ex ? chunks[ci] == kSpecChunkMixed : chunks[ci] > tile_limit) continue;
+          if (ex ? chunks[ci] == kTuneMixed : chunks[ci] > tile_limit) continue;
           if (mixed) { P->chunk_mixed = chunks[ci]; P->grid_mult_mixed = mults[mi]; }
           else { P->chunk = chunks[ci]; P->grid_mult_fp64 = mults[mi]; }
           double t_min = 1e300;
@@ -651,7 +661,7 @@ int fstat_interp_stats(fstat_plan_t P, int64_t* items, int64_t* rejected, int64_
       rc0 = set_error(FSTAT_EINVAL, "the last evaluation used the exact loop only");
     }
     if (!rc0) {
-      launch_bin_mix(P->last.mixed, P->last.stride, P->last.chunk, P->grid.chan.n, P->ws, d, s);
+      launch_bin_mix(P->last.mixed, P->last.stride, P->last.tiling, P->grid.chan.n, P->ws, d, s);
       rc0 = hip_check(hipGetLastError(), "bin mix launch");
     }
     if (!rc0) rc0 = hip_check(hipMemcpyAsync(h, d, sizeof(h), hipMemcpyDeviceToHost, s), "read bin mix");
@@ -871,7 +881,7 @@ int fstat_waveform(double T_obs, double df, int64_t k_lo, int64_t nbins, const d
     pp = dpar; ap = damp; op = dout;
   }
   if (!rc) {
-    launch_setup(g, pp, 1, nullptr, 1, 1, 1 << 24, nullptr, ws, s);
+    launch_setup(g, pp, 1, nullptr, 1, 1, make_tiling(g, 1 << 24, false, false), nullptr, ws, s);
     launch_waveform(g, ws.pc, ap, op, s);
     rc = hip_check(hipGetLastError(), "waveform launch");
   }

@@ -57,7 +57,8 @@ struct fstat_plan_s {
   } io;
   struct {                          // shape of the last fstat_eval (fstat_interp_stats)
     int64_t n = 0;
-    int32_t stride = 0, chunk = 0;
+    int32_t stride = 0;
+    fstat::Tiling tiling;
     bool mixed = false, exact = false;
   } last;
   PsoState* pso = nullptr;

@@ -63,7 +63,21 @@ struct WorkSpace {
   int32_t* nrefine;   // [1]
   // items per particle [n]: kept where Fl is written at the evaluation's end
   int32_t* ptot() const { return reinterpret_cast<int32_t*>(Fl); }
+  // tiles per work item of each partition [n * stride], likewise (n <= n * stride)
+  int32_t* widen(int64_t m) const { return reinterpret_cast<int32_t*>(Fl) + m; }
 };
+
+// How partitions are cut into work items: at the edges of tiles of T bins, or, where
+// mmax > 1, of m consecutive tiles with m chosen per partition (item_width).
+struct Tiling {
+  int32_t T = 0, ntiles = 0;        // bins per tile, tiles of one channel
+  double rT = 0.0;                  // 1 / T
+  int32_t mmax = 1;                 // at most kMaxWiden
+  float kt = 0.f, kf = 0.f;         // limits of m: kt Mc^{5/3} f^{11/3}, kf f
+  float kd = 0.f;                   // shortest partition that is widened (in tiles, over the first limit)
+};
+constexpr int kMaxWiden = 7;        // an item's m in three bits beside its tile
+Tiling make_tiling(const Grid& g, int32_t chunk, bool widen, bool mixed);
 
 void launch_prep(const Grid& g, const double* data, const double* psd, BinData<double> b,
                  hipStream_t s);
@@ -71,11 +85,11 @@ void launch_max(const double* u, int64_t n, double* out, hipStream_t s);
 void launch_scale(const Grid& g, const double* umax, BinData<double> b, BinData<float> b32,
                   hipStream_t s);
 void launch_setup(const Grid& g, const double* params, int64_t n,
-                  const int32_t* np, int32_t np_uniform, int32_t stride, int32_t chunk,
+                  const int32_t* np, int32_t np_uniform, int32_t stride, const Tiling& tl,
                   const uint8_t* skip, const WorkSpace& ws, hipStream_t s);
-// all_exact: the exact loop takes every item; ntiles: of all channels
-void launch_worklist(int64_t n, int32_t stride, const WorkSpace& ws, bool all_exact, int32_t ntiles,
-                     hipStream_t s);
+// all_exact: the exact loop takes every item
+void launch_worklist(int64_t n, int32_t stride, const Tiling& tl, int32_t nch, const WorkSpace& ws,
+                     bool all_exact, hipStream_t s);
 int interp_tables_init();
 constexpr int kMaxTileFp64 = 2560;   // largest tile (bins) of the LDS-staged loops
 constexpr int kMaxTileMixed = 4608;   // FP32 w: 36 KB + 2 KB per block, four blocks per CU
@@ -97,12 +111,30 @@ struct Spectra {
   int32_t nslots = 0;    // slopes kept: 0 .. T_obs df Q
   int32_t nblk = 0;      // whole blocks per channel
 };
-// Default work-item size of a plan with spectra.  Longer items spread a node evaluation over
-// more bins until the degree-9 interpolants miss their end points and the exact loop takes
-// the item (4096 x 64 on 7.1M bins, FP64: 4.01, 3.69, 3.73, 5.31 ms at 2048, 2560, 4096, 5120
-// bins; mixed, with its wider tolerance: 2.94, 2.61, 2.17, 2.06, 3.13 at .. 5120, 8192).
+// Default tile of a plan with spectra, and how far a partition's items may be
+// widened: as long as the signal's time in an item stays below kWidenTime and its
+// bandwidth below kWidenBand of the frequency, up to kWiden bins.  Longer items
+// spread a node evaluation over more bins until the degree-9 interpolants miss
+// their end points and the exact loop takes the item, and until the spectra of the
+// blocks that items of one place are at together no longer fit an L2 (7680 bins
+// FP64: 3.9 MB; block loop 1.26 -> 1.67 ms).  Np = 64 on 7.1M bins FP64, one channel,
+// three channels, orbit table, ms: one tile of 2560 each 3.17, 2.65, 1.28; 7 days 2.95,
+// 2.40, 1.29; 9 days 2.88, 2.45, 1.25; 14 days 3.85, 5.20, 1.47; 7 days and 7680 bins
+// 3.18, 2.51, 1.38.  Mixed, the same batch and the first stage's: one tile of 5120 1.69,
+// 2.61; tiles of 2560 and 12 days 1.69, 2.63; 15 days 1.62, 2.46; 20 days 1.80, 2.57.
+// FP64 partitions that the signal spends less than kWidenSpan in are not widened: over
+// so short a time the transfers T+ and Tx are nearly proportional, the partition is
+// ill-conditioned and the longer items' end points say less about it (4096 x 256:
+// 21 partitions beyond the refinement budget without this rule, 6 at two days, 1 at four
+// as with one tile per item).
 constexpr int kSpecChunkFp64 = 2560;
-constexpr int kSpecChunkMixed = 5120;
+constexpr int kSpecChunkMixed = 2560;
+constexpr int kWidenFp64 = 5120;
+constexpr int kWidenMixed = 7680;
+constexpr double kWidenTimeFp64 = 9.0 * 86400.0;     // [s]
+constexpr double kWidenTimeMixed = 15.0 * 86400.0;
+constexpr double kWidenBand = 0.01;
+constexpr double kWidenSpan = 4.0 * 86400.0;
 constexpr double kSpecMaxSlope = 1.001;   // largest T_obs df [cycles per bin] with spectra
 // Block size for a data set of nbins bins per channel, 0 for none.
 int spectra_block(bool mixed, int64_t nbins);
@@ -138,7 +170,7 @@ void launch_ufit(const double* u, int64_t nbins, int32_t ntiles, double* coef, d
 int uprefix_block_sums(int64_t n);
 void launch_uprefix(const double* u, int64_t n, double* bsum, double* out, hipStream_t s);
 void launch_eval(bool mixed, bool interp, double refine_budget, const Grid& g,
-                 int64_t n_particles, int32_t stride, int32_t chunk,
+                 int64_t n_particles, int32_t stride, const Tiling& tl,
                  const WorkSpace& ws, BinData<double> b, BinData<float> b32, const double* ek,
                  int blocks, hipStream_t s, hipEvent_t* ev_main = nullptr,
                  const UModel& um = UModel{}, const Spectra<double>& s64 = Spectra<double>{},
@@ -152,7 +184,7 @@ void launch_sur_check(const Grid& g, int32_t stride, int64_t n, const WorkSpace&
 // bins of the last evaluation by kind of interpolating-loop work, then the
 // lane runs of those items by kind (out[kBinMix] accumulated)
 constexpr int kBinMix = 14;
-void launch_bin_mix(bool mixed, int32_t stride, int32_t chunk, int32_t nch, const WorkSpace& ws,
+void launch_bin_mix(bool mixed, int32_t stride, const Tiling& tl, int32_t nch, const WorkSpace& ws,
                     unsigned long long* out, hipStream_t s);
 void launch_solve_mean(int64_t n, int32_t stride, const WorkSpace& ws, double* F_hat,
                        double* F_part, double* amps, int64_t part_stride, const double* umax,

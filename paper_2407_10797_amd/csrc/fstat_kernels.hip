@@ -114,26 +114,47 @@ __device__ __forceinline__ double bin_freq(const Grid& g, int64_t j) {
   return (double)(g.k_lo + j) * g.df;
 }
 
-// Work item c of a partition with bins [a, b): its part inside bin tile
-// a / T + c of the global tiling of the band into tiles of T bins.
-__device__ __forceinline__ int item_tile(int a, int c, int T) { return a / T + c; }
-// With several channels a partition has (tiles met) x (channels) items:
-// item c covers tile offset c / nch of channel c % nch.
-__device__ __forceinline__ void item_split(int c, int nch, int& ct, int& ch) {
-  ct = c / nch;
-  ch = c - ct * nch;
+// a / n for 0 <= a < 2^31 and n >= 1 from rn = 1 / n: (a + 1/2) / n is at least
+// 1 / (2 n) from a whole number, the product's error below 2^-20 of that (4
+// operations; an integer division takes ~25)
+__device__ __forceinline__ int div_by(int a, double rn) { return (int)(((double)a + 0.5) * rn); }
+
+// Tiles per work item of a partition that starts at frequency f.  What an
+// interpolant over an item has to follow is the detector's motion (up to four
+// turns a year of the transfer's phase pattern) over the time that the signal
+// spends in it, its width times dt/df = (5/96) pi^{-8/3} Mc^{-5/3} f^{-11/3}, and
+// the chirp's own shape over width / f.
+__device__ __forceinline__ int item_width(const Tiling& tl, float mc53, float f, int nb) {
+  if (tl.mmax == 1) return 1;
+  const float mt = tl.kt * mc53 * powf(f, 11.0f / 3.0f);
+  if ((float)nb * (float)tl.rT < tl.kd * mt) return 1;
+  return (int)fminf(fmaxf(fminf(mt, tl.kf * f), 1.0f), (float)tl.mmax);
 }
-// The item's tile in the numbering of all channels' tiles, channel by
-// channel (ntiles = nch x tiles per channel).
-__device__ __forceinline__ int item_xtile(int a, int c, int T, int nch, int ntiles) {
-  int ct, ch;
-  item_split(c, nch, ct, ch);
-  return ch * (ntiles / nch) + item_tile(a, ct, T);
+// first item of a partition with bins [a, b) and m tiles per item, in units of m
+// tiles, and the number of its items (of one channel)
+__device__ __forceinline__ int first_item(const Tiling& tl, int a, int m) {
+  const int t = div_by(a, tl.rT);
+  return m == 1 ? t : t / m;
 }
-__device__ __forceinline__ void item_bins(int a, int b, int c, int T, int& b0, int& b1) {
-  const int t = a / T + c;
-  b0 = max(a, t * T);
-  b1 = min(b, (t + 1) * T);
+__device__ __forceinline__ int item_count(const Tiling& tl, int a, int b, int m) {
+  return b > a ? first_item(tl, b - 1, m) - first_item(tl, a, m) + 1 : 0;
+}
+// A work item: partition q and, in one word, its first tile (the tiles of all
+// channels numbered channel by channel) << 3 | its tiles m.  Item i of a partition
+// whose first is u0: tile by tile, all channels of each.
+__device__ __forceinline__ int item_word(int i, int u0, int m, int nch, int ntiles) {
+  const int ct = nch == 1 ? i : i / nch;
+  return ((i - ct * nch) * ntiles + (u0 + ct) * m) << 3 | m;
+}
+__device__ __forceinline__ int item_chan(int y, const Tiling& tl, int nch) {
+  return nch > 1 ? (y >> 3) / tl.ntiles : 0;
+}
+// its bins: those of its tiles that are in the partition's [a, b)
+__device__ __forceinline__ void item_bins(int a, int b, int y, int ch, const Tiling& tl, int& b0,
+                                          int& b1) {
+  const int t = (y >> 3) - ch * tl.ntiles;
+  b0 = max(a, t * tl.T);
+  b1 = (int)min((int64_t)b, (int64_t)(t + (y & 7)) * tl.T);
 }
 
 // smallest j in [lo, hi+1] with f_j >= e
@@ -216,12 +237,13 @@ __device__ double invert_tf(const PartConst& P, double t, bool need, double fa, 
 // lane), work-item counts.
 __global__ __launch_bounds__(64) void k_setup(Grid g, const double* __restrict__ params,
                                                int64_t n, const int32_t* __restrict__ np,
-                                               int32_t np_uniform, int32_t stride, int32_t chunk,
+                                               int32_t np_uniform, int32_t stride, Tiling tl,
                                                const uint8_t* __restrict__ skip,
                                                PartConst* __restrict__ pc,
                                                int32_t* __restrict__ bounds,
                                                int32_t* __restrict__ cnt,
-                                               int32_t* __restrict__ ptot) {
+                                               int32_t* __restrict__ ptot,
+                                               int32_t* __restrict__ widen) {
   const int lane = threadIdx.x & 63;
   const int64_t p = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   if (p >= n) return;                      // whole wavefronts
@@ -287,6 +309,7 @@ __global__ __launch_bounds__(64) void k_setup(Grid g, const double* __restrict__
   if (lane == 0) pc[p] = P;
   // edges e_l = flo + span l / Np: bin bp[l] is the first at or above e_l; each
   // lane computes both edges of its partitions (no exchange between lanes)
+  const float mc53 = tl.mmax > 1 ? powf((float)P.mc_hi, 5.0f / 3.0f) : 0.f;
   const double span = fhi - flo;
   auto edge = [&](int l) -> int {
     if (l == 0) return jlo;
@@ -298,7 +321,9 @@ __global__ __launch_bounds__(64) void k_setup(Grid g, const double* __restrict__
     const int a = edge(l), b = edge(l + 1);
     bp[l] = a;
     if (l == npi - 1) bp[npi] = b;
-    const int c = b > a ? ((b - 1) / chunk - a / chunk + 1) * g.chan.n : 0;   // tiles met x channels
+    const int m = item_width(tl, mc53, (float)bin_freq(g, a), b - a);
+    if (tl.mmax > 1) widen[(int64_t)p * stride + l] = m;
+    const int c = item_count(tl, a, b, m) * g.chan.n;
     cp[l] = c;
     tot += c;
   }
@@ -385,11 +410,15 @@ __global__ __launch_bounds__(1024) void k_scan_apply(const int32_t* __restrict__
 }
 
 __global__ void k_fill(const int32_t* __restrict__ cnt, const int32_t* __restrict__ off, int64_t m,
-                       int2* __restrict__ items) {
+                       const int32_t* __restrict__ bounds, const int32_t* __restrict__ widen,
+                       int32_t stride, Tiling tl, int32_t nch, int2* __restrict__ items) {
   int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= m) return;
   int c = cnt[q], o = off[q];
-  for (int i = 0; i < c; ++i) items[o + i] = make_int2((int)q, i);
+  if (c == 0) return;
+  const int64_t p = q / stride;
+  const int m_ = tl.mmax > 1 ? widen[q] : 1, u0 = first_item(tl, bounds[p * (stride + 1) + (q - p * stride)], m_);
+  for (int i = 0; i < c; ++i) items[o + i] = make_int2((int)q, item_word(i, u0, m_, nch, tl.ntiles));
 }
 
 // The same in one kernel for up to kScanOnce particles, one block each: a block
@@ -400,7 +429,10 @@ __global__ void k_fill(const int32_t* __restrict__ cnt, const int32_t* __restric
 // five: 4 us for one particle (17), 12 us at 4096 x 64 (31).
 constexpr int64_t kScanOnce = 8192;
 
-__global__ __launch_bounds__(256) void k_worklist(const int32_t* __restrict__ cnt, int32_t stride,
+__global__ __launch_bounds__(256) void k_worklist(const int32_t* __restrict__ cnt,
+                                                  const int32_t* __restrict__ bounds,
+                                                  const int32_t* __restrict__ widen,
+                                                  int32_t stride, Tiling tl, int32_t nch,
                                                   const int32_t* __restrict__ ptot,
                                                   int32_t* __restrict__ off,
                                                   int2* __restrict__ items,
@@ -410,7 +442,7 @@ __global__ __launch_bounds__(256) void k_worklist(const int32_t* __restrict__ cn
                                                   int32_t* __restrict__ tcnt,
                                                   int32_t* __restrict__ tcur, int32_t n2,
                                                   int32_t* __restrict__ tile_ctr) {
-  __shared__ int32_t s_off[257];
+  __shared__ int32_t s_off[257], s_u0[256], s_m[256];
   __shared__ int32_t s_wave[4];
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int p = blockIdx.x;
@@ -450,6 +482,11 @@ __global__ __launch_bounds__(256) void k_worklist(const int32_t* __restrict__ cn
     const int32_t o = mine + inc - v;
     s_off[t] = o;
     if (t == 0) s_off[256] = all;
+    if (v > 0) {
+      const int m = tl.mmax > 1 ? widen[q] : 1;
+      s_m[t] = m;
+      s_u0[t] = first_item(tl, bounds[(int64_t)p * (stride + 1) + l], m);
+    }
     if (l < stride) off[q] = base + o;
     __syncthreads();
     for (int i = t; i < all; i += 256) {           // item -> its partition by bisection
@@ -459,7 +496,8 @@ __global__ __launch_bounds__(256) void k_worklist(const int32_t* __restrict__ cn
         const int mid = (lo + hi) >> 1;
         if (s_off[mid] <= i) lo = mid; else hi = mid;
       }
-      items[base + i] = make_int2((int)((int64_t)p * stride + l0 + lo), i - s_off[lo]);
+      items[base + i] = make_int2((int)((int64_t)p * stride + l0 + lo),
+                                  item_word(i - s_off[lo], s_u0[lo], s_m[lo], nch, tl.ntiles));
     }
     base += all;
   }
@@ -611,7 +649,7 @@ __global__ __launch_bounds__(256, 3) void k_eval_exact(Grid g,
                                                     const PartConst* __restrict__ pc,
                                                     const int32_t* __restrict__ bounds, int32_t stride,
                                                     const int2* __restrict__ items,
-                                                    const int32_t* __restrict__ total, int32_t chunk,
+                                                    const int32_t* __restrict__ total, Tiling tl,
                                                     const double* __restrict__ wr,
                                                     const double* __restrict__ wi,
                                                     const double* __restrict__ u,
@@ -639,8 +677,7 @@ __global__ __launch_bounds__(256, 3) void k_eval_exact(Grid g,
   auto terms = [&](int q, int c, int j, double t[8]) {
     const int p = q / stride;
     const PartConst& P = pc[p];
-    int ct, ch;
-    item_split(c, g.chan.n, ct, ch);
+    const int ch = item_chan(c, tl, g.chan.n);
     const int64_t co = (int64_t)ch * g.nbins;   // the channel's data
     const double* ekq = (ek && P.sur) ? ek + 8 * (int64_t)q : nullptr;
     double f = bin_freq(g, j);
@@ -681,9 +718,7 @@ __global__ __launch_bounds__(256, 3) void k_eval_exact(Grid g,
     c = it.y;
     const int p = q / stride, l = q - p * stride;
     const int32_t* bp = bounds + (int64_t)p * (stride + 1);
-    int ct, ch;
-    item_split(c, g.chan.n, ct, ch);
-    item_bins(bp[l], bp[l + 1], ct, chunk, b0, b1);
+    item_bins(bp[l], bp[l + 1], c, item_chan(c, tl, g.chan.n), tl, b0, b1);
   };
   // All items, or only those listed in sel (the interpolating kernel's
   // rejects and refinements).  Items of at most kSmallItem bins go 32 list
@@ -862,7 +897,7 @@ __global__ __launch_bounds__(256, 3) void k_eval_exact(Grid g,
 // ---------------------------------------------------------------------------
 // the hot loop, interpolating form (default)
 // ---------------------------------------------------------------------------
-// Within one work item (at most `chunk` consecutive bins of one partition)
+// Within one work item (at most a tile of consecutive bins of one partition)
 // every factor of the template except the fast phase is smooth in f, and the
 // phase is smooth once a linear term is taken out.  Per item, with m = j - b0
 // and s = 2 m / (nb - 1) - 1 in [-1, 1]:
@@ -1153,11 +1188,6 @@ struct SpecShape {
   double psi;
   double hq, smax;      // half a slot of the slope grid, its last slot
 };
-// a / n for 0 <= a < 2^31 and n >= 1 from rn = 1 / n: (a + 1/2) / n is at least
-// 1 / (2 n) from a whole number, the product's error below 2^-20 of that (4
-// operations; an integer division takes ~25)
-__device__ __forceinline__ int div_by(int a, double rn) { return (int)(((double)a + 0.5) * rn); }
-
 template <bool MIXED, bool TAB>
 __global__ __launch_bounds__(256, TAB ? 2 : 3) void k_interp_nodes(Grid g,
                                                       const PartConst* __restrict__ pc,
@@ -1165,7 +1195,7 @@ __global__ __launch_bounds__(256, TAB ? 2 : 3) void k_interp_nodes(Grid g,
                                                       int32_t stride,
                                                       const int2* __restrict__ items,
                                                       const int32_t* __restrict__ total,
-                                                      int32_t T,
+                                                      Tiling tl,
                                                       const double* __restrict__ ek,
                                                       double* __restrict__ rec,
                                                       uint8_t* __restrict__ xflag,
@@ -1174,7 +1204,7 @@ __global__ __launch_bounds__(256, TAB ? 2 : 3) void k_interp_nodes(Grid g,
                                                       int32_t* __restrict__ ndirect,
                                                       UModel um,
                                                       double* __restrict__ partials,
-                                                      SpecShape sp, double rstride, double rT) {
+                                                      SpecShape sp, double rstride) {
   const int lane = threadIdx.x & 63;
   const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int nwaves = (gridDim.x * blockDim.x) >> 6;
@@ -1210,14 +1240,14 @@ __global__ __launch_bounds__(256, TAB ? 2 : 3) void k_interp_nodes(Grid g,
   const int k = min(lane - q * kLanesItem, kLanesItem - 1);
   const int base = q * kLanesItem;
   // a group's items are loaded two groups ahead and its bounds one ahead
-  auto item_of = [&](int grp) { return items[min(min(grp, G - 1) * kItemsWave + q, W - 1)]; };
+  auto load_item = [&](int grp) { return items[min(min(grp, G - 1) * kItemsWave + q, W - 1)]; };
   auto bounds_of = [&](int2 it, int& p) {
     p = div_by(it.x, rstride);
     const int32_t* bp = bounds + (int64_t)p * (stride + 1) + (it.x - p * stride);
     return make_int2(bp[0], bp[1]);
   };
   if (wave >= G) return;
-  int2 it1 = item_of(wave), it2 = item_of(wave + nwaves);
+  int2 it1 = load_item(wave), it2 = load_item(wave + nwaves);
   int p1;
   int2 bd1 = bounds_of(it1, p1);
   for (int grp = wave; grp < G; grp += nwaves) {
@@ -1225,12 +1255,11 @@ __global__ __launch_bounds__(256, TAB ? 2 : 3) void k_interp_nodes(Grid g,
     const int2 it = it1, bd = bd1;
     const int p = p1;
     it1 = it2;
-    it2 = item_of(grp + 2 * nwaves);
+    it2 = load_item(grp + 2 * nwaves);
     bd1 = bounds_of(it1, p1);
-    int ct = it.y, ch = 0;
-    if (g.chan.n > 1) item_split(it.y, g.chan.n, ct, ch);
-    const int bt = (div_by(bd.x, rT) + ct) * T;                 // item_bins
-    const int b0 = max(bd.x, bt), b1 = min(bd.y, bt + T);
+    const int ch = item_chan(it.y, tl, g.chan.n);
+    int b0, b1;
+    item_bins(bd.x, bd.y, it.y, ch, tl, b0, b1);
     const int nb = b1 - b0;
     if (!__any(nb >= kMinInterp)) {
       // no item of this group is long enough to interpolate: all of them go
@@ -1490,7 +1519,7 @@ __global__ __launch_bounds__(256, TAB ? 2 : 3) void k_interp_nodes(Grid g,
 // registers and runs the per-bin loop from LDS.
 template <bool MIXED>
 __global__ __launch_bounds__(256) void k_eval_interp(Grid g,
-                                                     int32_t T,
+                                                     Tiling tl,
                                                      const int32_t* __restrict__ tile_items,
                                                      const int32_t* __restrict__ tile_off,
                                                      const int32_t* __restrict__ unit_off,
@@ -1528,8 +1557,8 @@ __global__ __launch_bounds__(256) void k_eval_interp(Grid g,
   const int nwv = blockDim.x >> 6;
   const int nunits = unit_off[ntiles];
   if (nunits == 0) return;
-  // The current unit: its items, the channel's data offset, and the tile's bins
-  // not yet staged.  Tiles above the LDS stage go through it in parts; a wave
+  // The current unit: its items, the channel's data offset, and the bins of its
+  // tile (of all tiles its items may reach) not yet staged.  More than the LDS stage go through it in parts; a wave
   // takes the same items in each and adds to their sums.
   int i0 = 0, cnt = 0, j0 = 0, j_end = 0;
   int64_t co = 0;
@@ -1555,13 +1584,12 @@ __global__ __launch_bounds__(256) void k_eval_interp(Grid g,
       const int tx = s_unit[0];
       if (tx < 0) break;
       // tiles of all channels are numbered channel by channel
-      const int ntpc = (int)((g.nbins + T - 1) / T);
-      const int tch = tx / ntpc, t = tx - tch * ntpc;
+      const int tch = tx / tl.ntiles;
       co = (int64_t)tch * g.nbins;
       i0 = s_unit[1];
       cnt = s_unit[2];
-      j0 = t * T;
-      j_end = (int)min((int64_t)j0 + T, g.nbins);
+      j0 = (tx - tch * tl.ntiles) * tl.T;
+      j_end = (int)min((int64_t)j0 + (int64_t)tl.mmax * tl.T, g.nbins);
     }
     const int nt = min(TS, j_end - j0);
     for (int i = threadIdx.x; i < nt; i += blockDim.x) {
@@ -2455,7 +2483,7 @@ template <bool MIXED>
 __global__ __launch_bounds__(256) void k_bin_mix(const int2* __restrict__ items,
                                                  const int32_t* __restrict__ total,
                                                  const int32_t* __restrict__ bounds,
-                                                 int32_t stride, int32_t T, int32_t nch,
+                                                 int32_t stride, Tiling tl, int32_t nch,
                                                  const double* __restrict__ rec,
                                                  const uint8_t* __restrict__ xflag,
                                                  unsigned long long* __restrict__ out) {
@@ -2468,9 +2496,8 @@ __global__ __launch_bounds__(256) void k_bin_mix(const int2* __restrict__ items,
     const int2 it = items[w];
     const int p = it.x / stride, l = it.x - p * stride;
     const int32_t* bp = bounds + (int64_t)p * (stride + 1);
-    int ct, ch, b0, b1;
-    item_split(it.y, nch, ct, ch);
-    item_bins(bp[l], bp[l + 1], ct, T, b0, b1);
+    int b0, b1;
+    item_bins(bp[l], bp[l + 1], it.y, item_chan(it.y, tl, nch), tl, b0, b1);
     const int nb = b1 - b0;
     int kind = 6, runs = 1;
     if (xflag[w] != kItemExact) {
@@ -2493,10 +2520,10 @@ __global__ __launch_bounds__(256) void k_bin_mix(const int2* __restrict__ items,
   if (threadIdx.x < kBinMix && acc[threadIdx.x]) atomicAdd(&out[threadIdx.x], acc[threadIdx.x]);
 }
 
-void launch_bin_mix(bool mixed, int32_t stride, int32_t chunk, int32_t nch, const WorkSpace& ws,
+void launch_bin_mix(bool mixed, int32_t stride, const Tiling& tl, int32_t nch, const WorkSpace& ws,
                     unsigned long long* out, hipStream_t s) {
   hipLaunchKernelGGL(mixed ? k_bin_mix<true> : k_bin_mix<false>, dim3(1024), dim3(256), 0, s,
-                     ws.items, ws.total, ws.bounds, stride, chunk, nch, ws.rec, ws.xflag, out);
+                     ws.items, ws.total, ws.bounds, stride, tl, nch, ws.rec, ws.xflag, out);
 }
 
 // ---- grouping of the work items by loop and bin tile -------------------------
@@ -2510,14 +2537,10 @@ __global__ void k_tile_zero(int32_t* __restrict__ tcnt, int32_t* __restrict__ tc
 // Where item w is counted: its tile, of the block loop or (+ ntiles) of the
 // per-bin loop; -1: the exact loop takes it.
 __device__ __forceinline__ int tile_key(const int2* __restrict__ items,
-                                        const uint8_t* __restrict__ xflag,
-                                        const int32_t* __restrict__ bounds, int32_t stride,
-                                        int32_t T, int32_t ntiles, int32_t nch, int w) {
+                                        const uint8_t* __restrict__ xflag, int32_t ntiles, int w) {
   const uint8_t x = xflag[w];
   if (x == kItemExact) return -1;
-  const int2 it = items[w];
-  const int p = it.x / stride, l = it.x - p * stride;
-  const int t = item_xtile(bounds[(int64_t)p * (stride + 1) + l], it.y, T, nch, ntiles);
+  const int t = items[w].y >> 3;
   return x == kItemBlocks ? t : ntiles + t;
 }
 
@@ -2531,9 +2554,7 @@ constexpr int kTileHist = 8192;
 __global__ __launch_bounds__(256) void k_tile_count(const int2* __restrict__ items,
                                                     const int32_t* __restrict__ total,
                                                     const uint8_t* __restrict__ xflag,
-                                                    const int32_t* __restrict__ bounds,
-                                                    int32_t stride, int32_t T, int32_t ntiles,
-                                                    int32_t nch, int32_t* __restrict__ tcnt) {
+                                                    int32_t ntiles, int32_t* __restrict__ tcnt) {
   __shared__ int32_t h[kTileHist];
   const int nk = 2 * ntiles;
   const bool local = nk <= kTileHist;
@@ -2543,7 +2564,7 @@ __global__ __launch_bounds__(256) void k_tile_count(const int2* __restrict__ ite
     __syncthreads();
   }
   for (int w = blockIdx.x * blockDim.x + threadIdx.x; w < W; w += gridDim.x * blockDim.x) {
-    const int t = tile_key(items, xflag, bounds, stride, T, ntiles, nch, w);
+    const int t = tile_key(items, xflag, ntiles, w);
     if (t < 0) continue;
     if (local) atomicAdd(&h[t], 1);
     else atomicAdd(&tcnt[t], 1);
@@ -2593,9 +2614,7 @@ __global__ __launch_bounds__(1024) void k_tile_scan(const int32_t* __restrict__ 
 __global__ __launch_bounds__(256) void k_tile_scatter(const int2* __restrict__ items,
                                                       const int32_t* __restrict__ total,
                                                       const uint8_t* __restrict__ xflag,
-                                                      const int32_t* __restrict__ bounds,
-                                                      int32_t stride, int32_t T, int32_t ntiles,
-                                                      int32_t nch,
+                                                      int32_t ntiles,
                                                       const int32_t* __restrict__ off,
                                                       int32_t* __restrict__ tcur,
                                                       int32_t* __restrict__ tile_items) {
@@ -2605,7 +2624,7 @@ __global__ __launch_bounds__(256) void k_tile_scatter(const int2* __restrict__ i
   const int W = total[0];
   if (!local) {
     for (int w = blockIdx.x * blockDim.x + threadIdx.x; w < W; w += gridDim.x * blockDim.x) {
-      const int t = tile_key(items, xflag, bounds, stride, T, ntiles, nch, w);
+      const int t = tile_key(items, xflag, ntiles, w);
       if (t >= 0) tile_items[off[t] + atomicAdd(&tcur[t], 1)] = w;
     }
     return;
@@ -2613,7 +2632,7 @@ __global__ __launch_bounds__(256) void k_tile_scatter(const int2* __restrict__ i
   for (int i = threadIdx.x; i < nk; i += blockDim.x) h[i] = 0;
   __syncthreads();
   for (int w = blockIdx.x * blockDim.x + threadIdx.x; w < W; w += gridDim.x * blockDim.x) {
-    const int t = tile_key(items, xflag, bounds, stride, T, ntiles, nch, w);
+    const int t = tile_key(items, xflag, ntiles, w);
     if (t >= 0) atomicAdd(&h[t], 1);
   }
   __syncthreads();
@@ -2621,7 +2640,7 @@ __global__ __launch_bounds__(256) void k_tile_scatter(const int2* __restrict__ i
     if (h[i]) h[i] = off[i] + atomicAdd(&tcur[i], h[i]);
   __syncthreads();
   for (int w = blockIdx.x * blockDim.x + threadIdx.x; w < W; w += gridDim.x * blockDim.x) {
-    const int t = tile_key(items, xflag, bounds, stride, T, ntiles, nch, w);
+    const int t = tile_key(items, xflag, ntiles, w);
     if (t >= 0) tile_items[atomicAdd(&h[t], 1)] = w;
   }
 }
@@ -2633,9 +2652,7 @@ constexpr int64_t kGroupOnce = 32768;
 __global__ __launch_bounds__(1024) void k_tile_group(const int2* __restrict__ items,
                                                      const int32_t* __restrict__ total,
                                                      const uint8_t* __restrict__ xflag,
-                                                     const int32_t* __restrict__ bounds,
-                                                     int32_t stride, int32_t T, int32_t ntiles,
-                                                     int32_t nch, int32_t* __restrict__ off,
+                                                     int32_t ntiles, int32_t* __restrict__ off,
                                                      int32_t* __restrict__ uoff,
                                                      int32_t* __restrict__ tile_items) {
   __shared__ int32_t h[kTileHist];
@@ -2645,7 +2662,7 @@ __global__ __launch_bounds__(1024) void k_tile_group(const int2* __restrict__ it
   for (int i = t; i < nk; i += 1024) h[i] = 0;
   __syncthreads();
   for (int w = t; w < W; w += 1024) {
-    const int k = tile_key(items, xflag, bounds, stride, T, ntiles, nch, w);
+    const int k = tile_key(items, xflag, ntiles, w);
     if (k >= 0) atomicAdd(&h[k], 1);
   }
   __syncthreads();
@@ -2673,7 +2690,7 @@ __global__ __launch_bounds__(1024) void k_tile_group(const int2* __restrict__ it
   }
   __syncthreads();
   for (int w = t; w < W; w += 1024) {
-    const int k = tile_key(items, xflag, bounds, stride, T, ntiles, nch, w);
+    const int k = tile_key(items, xflag, ntiles, w);
     if (k >= 0) tile_items[atomicAdd(&h[k], 1)] = w;
   }
 }
@@ -3206,20 +3223,21 @@ void launch_scale(const Grid& g, const double* umax, BinData<double> b, BinData<
 }
 
 void launch_setup(const Grid& g, const double* params, int64_t n,
-                  const int32_t* np, int32_t np_uniform, int32_t stride, int32_t chunk,
+                  const int32_t* np, int32_t np_uniform, int32_t stride, const Tiling& tl,
                   const uint8_t* skip, const WorkSpace& ws, hipStream_t s) {
   // one wavefront per block: a small batch spreads over the CUs
   hipLaunchKernelGGL(k_setup, dim3((unsigned)n), dim3(64), 0, s, g, params, n, np, np_uniform,
-                     stride, chunk, skip, ws.pc, ws.bounds, ws.cnt, ws.ptot());
+                     stride, tl, skip, ws.pc, ws.bounds, ws.cnt, ws.ptot(), ws.widen(n * stride));
 }
 
-void launch_worklist(int64_t n, int32_t stride, const WorkSpace& ws, bool all_exact, int32_t ntiles,
-                     hipStream_t s) {
+void launch_worklist(int64_t n, int32_t stride, const Tiling& tl, int32_t nch, const WorkSpace& ws,
+                     bool all_exact, hipStream_t s) {
+  const int32_t ntiles = tl.ntiles * nch;
   const int64_t m = n * stride;
   const int32_t nb = (int32_t)((m + kScanBlock - 1) / kScanBlock);
   if (n <= kScanOnce) {
-    hipLaunchKernelGGL(k_worklist, dim3((unsigned)n), dim3(256), 0, s, ws.cnt, stride, ws.ptot(),
-                       ws.off, ws.items, ws.total, ws.ndirect, ws.nrefine, all_exact ? 1 : 0,
+    hipLaunchKernelGGL(k_worklist, dim3((unsigned)n), dim3(256), 0, s, ws.cnt, ws.bounds,
+                       ws.widen(m), stride, tl, nch, ws.ptot(), ws.off, ws.items, ws.total, ws.ndirect, ws.nrefine, all_exact ? 1 : 0,
                        ws.tcnt, ws.tcur, all_exact ? 0 : 2 * ntiles, ws.tile_ctr);
     return;
   }
@@ -3227,7 +3245,8 @@ void launch_worklist(int64_t n, int32_t stride, const WorkSpace& ws, bool all_ex
   hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, ws.bsum, nb, ws.total, ws.ndirect,
                      ws.nrefine);
   hipLaunchKernelGGL(k_scan_apply, dim3(nb), dim3(1024), 0, s, ws.cnt, m, ws.bsum, ws.off);
-  hipLaunchKernelGGL(k_fill, dim3(nblk(m, 256)), dim3(256), 0, s, ws.cnt, ws.off, m, ws.items);
+  hipLaunchKernelGGL(k_fill, dim3(nblk(m, 256)), dim3(256), 0, s, ws.cnt, ws.off, m, ws.bounds,
+                     ws.widen(m), stride, tl, nch, ws.items);
   if (all_exact)
     hipLaunchKernelGGL(k_copy_count, dim3(1), dim3(64), 0, s, ws.total, ws.ndirect);
   else
@@ -3235,22 +3254,38 @@ void launch_worklist(int64_t n, int32_t stride, const WorkSpace& ws, bool all_ex
                        2 * ntiles, ws.tile_ctr);
 }
 
+Tiling make_tiling(const Grid& g, int32_t chunk, bool widen, bool mixed) {
+  Tiling tl;
+  tl.T = chunk;
+  tl.rT = 1.0 / (double)chunk;
+  tl.ntiles = (int32_t)((g.nbins + chunk - 1) / chunk);
+  if (widen) {
+    tl.mmax = std::max(1, std::min(kMaxWiden, (mixed ? kWidenMixed : kWidenFp64) / chunk));
+    const double w = (double)chunk * g.df;          // [Hz] per tile
+    tl.kt = (float)((mixed ? kWidenTimeMixed : kWidenTimeFp64) /
+                    (w * (5.0 / 96.0) * pow(kPi, -8.0 / 3.0)));
+    tl.kf = (float)(kWidenBand / w);
+    tl.kd = mixed ? 0.f : (float)(kWidenSpan / kWidenTimeFp64);
+  }
+  return tl;
+}
+
 int interp_max_tile(bool mixed) { return mixed ? kMaxTileMixed : kMaxTileFp64; }
 
 void launch_eval(bool mixed, bool interp, double refine_budget, const Grid& g,
-                 int64_t n_particles, int32_t stride, int32_t chunk, const WorkSpace& ws,
+                 int64_t n_particles, int32_t stride, const Tiling& tl, const WorkSpace& ws,
                  BinData<double> b, BinData<float> b32, const double* ek, int blocks,
                  hipStream_t s, hipEvent_t* ev_main, const UModel& um,
                  const Spectra<double>& s64, const Spectra<float>& s32) {
   const int32_t* sel = nullptr;
   const int32_t* nsel = nullptr;
   if (interp) {
-    const int32_t ntiles = (int32_t)((g.nbins + chunk - 1) / chunk) * g.chan.n;   // all channels
+    const int32_t ntiles = tl.ntiles * g.chan.n;   // all channels
     // The block loop needs tiles of whole blocks (the items inside a partition
     // then have no partial ones).
     SpecShape sp{};
     const int32_t L = mixed ? s32.L : s64.L;
-    if (L > 0 && chunk % L == 0)
+    if (L > 0 && tl.T % L == 0)
       sp = mixed ? SpecShape{L, s32.Q, s32.nslots, s32.nblk, kSpecPsiMixed, 0.5 / s32.Q,
                              (double)(s32.nslots - 1) / s32.Q}
                  : SpecShape{L, s64.Q, s64.nslots, s64.nblk, kSpecPsiFp64, 0.5 / s64.Q,
@@ -3260,19 +3295,19 @@ void launch_eval(bool mixed, bool interp, double refine_budget, const Grid& g,
       auto nodes = mixed ? (tab ? k_interp_nodes<true, true> : k_interp_nodes<true, false>)
                          : (tab ? k_interp_nodes<false, true> : k_interp_nodes<false, false>);
       hipLaunchKernelGGL(nodes, dim3(8 * blocks), dim3(256), 0, s, g, ws.pc, ws.bounds, stride,
-                         ws.items, ws.total, chunk, ek, ws.rec, ws.xflag, ws.xerr, ws.direct,
-                         ws.ndirect, um, ws.partials, sp, 1.0 / (double)stride, 1.0 / (double)chunk);
+                         ws.items, ws.total, tl, ek, ws.rec, ws.xflag, ws.xerr, ws.direct,
+                         ws.ndirect, um, ws.partials, sp, 1.0 / (double)stride);
     }
     if (n_particles * (int64_t)(ntiles + stride * g.chan.n) <= kGroupOnce && 2 * ntiles <= kTileHist) {
       hipLaunchKernelGGL(k_tile_group, dim3(1), dim3(1024), 0, s, ws.items, ws.total, ws.xflag,
-                         ws.bounds, stride, chunk, ntiles, g.chan.n, ws.toff, ws.uoff,
+                         ntiles, ws.toff, ws.uoff,
                          ws.tile_items);
     } else {
       hipLaunchKernelGGL(k_tile_count, dim3(1024), dim3(256), 0, s, ws.items, ws.total, ws.xflag,
-                         ws.bounds, stride, chunk, ntiles, g.chan.n, ws.tcnt);
+                         ntiles, ws.tcnt);
       hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(1024), 0, s, ws.tcnt, ntiles, ws.toff, ws.uoff);
       hipLaunchKernelGGL(k_tile_scatter, dim3(1024), dim3(256), 0, s, ws.items, ws.total, ws.xflag,
-                         ws.bounds, stride, chunk, ntiles, g.chan.n, ws.toff, ws.tcur,
+                         ntiles, ws.toff, ws.tcur,
                          ws.tile_items);
     }
     if (ev_main) (void)hipEventRecord(ev_main[0], s);
@@ -3296,7 +3331,7 @@ void launch_eval(bool mixed, bool interp, double refine_budget, const Grid& g,
     const size_t lds = mixed ? (size_t)kMaxTileMixed * 2 * sizeof(float)
                              : (size_t)kMaxTileFp64 * (2 * sizeof(double) + sizeof(float));
     hipLaunchKernelGGL(mixed ? k_eval_interp<true> : k_eval_interp<false>, dim3(blocks), dim3(256),
-                       lds, s, g, chunk, ws.tile_items, ws.toff + ntiles, ws.uoff, ntiles,
+                       lds, s, g, tl, ws.tile_items, ws.toff + ntiles, ws.uoff, ntiles,
                        ws.tile_ctr, b.wr, b.wi, b32.wr, b32.wi, ws.rec, ws.partials);
     if (ev_main) (void)hipEventRecord(ev_main[1], s);
     sel = ws.direct;
@@ -3304,7 +3339,7 @@ void launch_eval(bool mixed, bool interp, double refine_budget, const Grid& g,
   }
   auto exact_pass = [&](const int32_t* list, const int32_t* count) {
     hipLaunchKernelGGL(mixed ? k_eval_exact<true> : k_eval_exact<false>, dim3(blocks), dim3(256),
-                       0, s, g, ws.pc, ws.bounds, stride, ws.items, ws.total, chunk, b.wr, b.wi,
+                       0, s, g, ws.pc, ws.bounds, stride, ws.items, ws.total, tl, b.wr, b.wi,
                        b.u, b32.wr, b32.wi, b32.u, b.s0, b.c0, ek, ws.rec, ws.partials, list, count);
   };
   if (!interp && ev_main) (void)hipEventRecord(ev_main[0], s);
