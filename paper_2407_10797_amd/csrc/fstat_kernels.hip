@@ -119,32 +119,53 @@ __device__ __forceinline__ double bin_freq(const Grid& g, int64_t j) {
 // operations; an integer division takes ~25)
 __device__ __forceinline__ int div_by(int a, double rn) { return (int)(((double)a + 0.5) * rn); }
 
-// Tiles per work item of a partition that starts at frequency f.  What an
-// interpolant over an item has to follow is the detector's motion (up to four
-// turns a year of the transfer's phase pattern) over the time that the signal
-// spends in it, its width times dt/df = (5/96) pi^{-8/3} Mc^{-5/3} f^{-11/3}, and
-// the chirp's own shape over width / f.
-__device__ __forceinline__ int item_width(const Tiling& tl, float mc53, float f, int nb) {
-  if (tl.mmax == 1) return 1;
+// Tiles per work item in a partition.  What an interpolant over an item has to follow
+// is the detector's motion (up to four turns a year of the transfer's phase pattern)
+// over the time that the signal spends in it, its width times dt/df =
+// (5/96) pi^{-8/3} Mc^{-5/3} f^{-11/3}, and the chirp's own shape over width / f.  Both
+// fall with f: from tile z on mmax tiles keep the limits, before it the m1 that do at
+// the partition's start.  (The first limit with a fifth to spare: 4096 whole-band
+// partitions, two swarm iterations, 5.56 ms without z, 4.75, 4.91 and 5.17 with
+// factors 1.15, 1.3 and 1.5, but 6.00 with 1, where 6,949 items miss.)  The
+// partition's word: z << 3 | m1.
+constexpr int kWholeBand = 1 << 27;      // no tile z: beyond any plan's tiles
+__device__ __forceinline__ int item_width(const Grid& g, const Tiling& tl, float mc53, int a,
+                                          int b) {
+  const float f = (float)((double)(g.k_lo + a) * g.df), mx = (float)tl.mmax;
   const float mt = tl.kt * mc53 * powf(f, 11.0f / 3.0f);
-  if ((float)nb * (float)tl.rT < tl.kd * mt) return 1;
-  return (int)fminf(fmaxf(fminf(mt, tl.kf * f), 1.0f), (float)tl.mmax);
+  if ((float)(b - a) * (float)tl.rT < tl.kd * mt) return kWholeBand << 3 | 1;
+  const int m1 = (int)fminf(fmaxf(fminf(mt, tl.kf * f), 1.0f), mx);
+  const double fz = fmaxf(powf(1.2f * mx / (tl.kt * mc53), 3.0f / 11.0f), mx / tl.kf);
+  const double z = fmin(fmax(ceil((fz / g.df - (double)g.k_lo) * tl.rT), 0.0), (double)tl.ntiles);
+  return ((int)z + tl.mmax - 1) / tl.mmax * tl.mmax << 3 | m1;
 }
-// first item of a partition with bins [a, b) and m tiles per item, in units of m
-// tiles, and the number of its items (of one channel)
-__device__ __forceinline__ int first_item(const Tiling& tl, int a, int m) {
-  const int t = div_by(a, tl.rT);
-  return m == 1 ? t : t / m;
-}
-__device__ __forceinline__ int item_count(const Tiling& tl, int a, int b, int m) {
-  return b > a ? first_item(tl, b - 1, m) - first_item(tl, a, m) + 1 : 0;
+// Items i of a partition with bins [a, b): n1 of m1 tiles from unit u0 (cut at tile
+// z), then those of mmax tiles from unit v0.
+struct ItemCut {
+  int m1, z, u0, n1, v0;
+};
+__device__ __forceinline__ int item_count(const Tiling& tl, int a, int b, int word, ItemCut& c) {
+  c = ItemCut{1, INT32_MAX, 0, 0, 0};
+  if (b <= a) return 0;
+  const int ta = div_by(a, tl.rT), tb = div_by(b - 1, tl.rT);
+  c.u0 = ta;
+  if (tl.mmax == 1) return c.n1 = tb - ta + 1;
+  c.m1 = word & 7;
+  c.z = word >> 3;
+  c.u0 = ta / c.m1;
+  c.n1 = ta < c.z ? min(tb, c.z - 1) / c.m1 - c.u0 + 1 : 0;
+  c.v0 = max(ta, c.z) / tl.mmax;
+  return c.n1 + (tb >= c.z ? tb / tl.mmax - c.v0 + 1 : 0);
 }
 // A work item: partition q and, in one word, its first tile (the tiles of all
-// channels numbered channel by channel) << 3 | its tiles m.  Item i of a partition
-// whose first is u0: tile by tile, all channels of each.
-__device__ __forceinline__ int item_word(int i, int u0, int m, int nch, int ntiles) {
-  const int ct = nch == 1 ? i : i / nch;
-  return ((i - ct * nch) * ntiles + (u0 + ct) * m) << 3 | m;
+// channels numbered channel by channel) << 3 | its tiles m.  Items of several
+// channels: tile by tile, all channels of each.
+__device__ __forceinline__ int item_word(int i, const ItemCut& c, const Tiling& tl, int nch) {
+  const int ct = nch == 1 ? i : i / nch, ch = i - ct * nch;
+  const bool head = ct < c.n1;
+  const int t = head ? (c.u0 + ct) * c.m1 : (c.v0 + ct - c.n1) * tl.mmax;
+  const int m = head ? min(c.m1, c.z - t) : tl.mmax;
+  return (ch * tl.ntiles + t) << 3 | m;
 }
 __device__ __forceinline__ int item_chan(int y, const Tiling& tl, int nch) {
   return nch > 1 ? (y >> 3) / tl.ntiles : 0;
@@ -321,9 +342,10 @@ __global__ __launch_bounds__(64) void k_setup(Grid g, const double* __restrict__
     const int a = edge(l), b = edge(l + 1);
     bp[l] = a;
     if (l == npi - 1) bp[npi] = b;
-    const int m = item_width(tl, mc53, (float)bin_freq(g, a), b - a);
-    if (tl.mmax > 1) widen[(int64_t)p * stride + l] = m;
-    const int c = item_count(tl, a, b, m) * g.chan.n;
+    int word = 1;
+    if (tl.mmax > 1) widen[(int64_t)p * stride + l] = word = item_width(g, tl, mc53, a, b);
+    ItemCut ic;
+    const int c = item_count(tl, a, b, word, ic) * g.chan.n;
     cp[l] = c;
     tot += c;
   }
@@ -417,8 +439,10 @@ __global__ void k_fill(const int32_t* __restrict__ cnt, const int32_t* __restric
   int c = cnt[q], o = off[q];
   if (c == 0) return;
   const int64_t p = q / stride;
-  const int m_ = tl.mmax > 1 ? widen[q] : 1, u0 = first_item(tl, bounds[p * (stride + 1) + (q - p * stride)], m_);
-  for (int i = 0; i < c; ++i) items[o + i] = make_int2((int)q, item_word(i, u0, m_, nch, tl.ntiles));
+  const int32_t* bp = bounds + p * (stride + 1) + (q - p * stride);
+  ItemCut ic;
+  item_count(tl, bp[0], bp[1], tl.mmax > 1 ? widen[q] : 1, ic);
+  for (int i = 0; i < c; ++i) items[o + i] = make_int2((int)q, item_word(i, ic, tl, nch));
 }
 
 // The same in one kernel for up to kScanOnce particles, one block each: a block
@@ -442,7 +466,8 @@ __global__ __launch_bounds__(256) void k_worklist(const int32_t* __restrict__ cn
                                                   int32_t* __restrict__ tcnt,
                                                   int32_t* __restrict__ tcur, int32_t n2,
                                                   int32_t* __restrict__ tile_ctr) {
-  __shared__ int32_t s_off[257], s_u0[256], s_m[256];
+  __shared__ int32_t s_off[257];
+  __shared__ ItemCut s_cut[256];
   __shared__ int32_t s_wave[4];
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int p = blockIdx.x;
@@ -483,9 +508,8 @@ __global__ __launch_bounds__(256) void k_worklist(const int32_t* __restrict__ cn
     s_off[t] = o;
     if (t == 0) s_off[256] = all;
     if (v > 0) {
-      const int m = tl.mmax > 1 ? widen[q] : 1;
-      s_m[t] = m;
-      s_u0[t] = first_item(tl, bounds[(int64_t)p * (stride + 1) + l], m);
+      const int32_t* bp = bounds + (int64_t)p * (stride + 1) + l;
+      item_count(tl, bp[0], bp[1], tl.mmax > 1 ? widen[q] : 1, s_cut[t]);
     }
     if (l < stride) off[q] = base + o;
     __syncthreads();
@@ -497,7 +521,7 @@ __global__ __launch_bounds__(256) void k_worklist(const int32_t* __restrict__ cn
         if (s_off[mid] <= i) lo = mid; else hi = mid;
       }
       items[base + i] = make_int2((int)((int64_t)p * stride + l0 + lo),
-                                  item_word(i - s_off[lo], s_u0[lo], s_m[lo], nch, tl.ntiles));
+                                  item_word(i - s_off[lo], s_cut[lo], tl, nch));
     }
     base += all;
   }
