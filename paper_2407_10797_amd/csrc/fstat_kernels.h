@@ -100,8 +100,8 @@ enum : uint8_t { kItemBins = 0, kItemExact = 1, kItemBlocks = 2 };
 
 // Block spectra of the plan's data (see spectra.hip): for every block of L
 // consecutive bins of a channel, nslots phase slopes q / Q [cycles per bin]
-// and kSpecNodes node weights per slope, real parts then imaginary parts:
-// S[channel][block][slope][2][kSpecNodes].
+// and kSpecNodes complex node weights per slope:
+// S[channel][block][slope][kSpecNodes][re, im].
 constexpr int kSpecNodes = 16;
 template <typename T>
 struct Spectra {

@@ -2090,15 +2090,15 @@ static_assert(kRec <= kRecPad && kGrp == 16, "group layout");
 template <int N>
 __device__ __forceinline__ double row_bcast(double x) {
   int2 v = *reinterpret_cast<int2*>(&x);
-  v.x = __builtin_amdgcn_update_dpp(v.x, v.x, 0x150 + N, 0xf, 0xf, false);   // row_newbcast
-  v.y = __builtin_amdgcn_update_dpp(v.y, v.y, 0x150 + N, 0xf, 0xf, false);
+  v.x = __builtin_amdgcn_mov_dpp(v.x, 0x150 + N, 0xf, 0xf, true);   // row_newbcast
+  v.y = __builtin_amdgcn_mov_dpp(v.y, 0x150 + N, 0xf, 0xf, true);
   return *reinterpret_cast<double*>(&v);
 }
 template <int CTRL>
 __device__ __forceinline__ double dpp_add(double x) {
   int2 v = *reinterpret_cast<int2*>(&x);
-  v.x = __builtin_amdgcn_update_dpp(v.x, v.x, CTRL, 0xf, 0xf, false);
-  v.y = __builtin_amdgcn_update_dpp(v.y, v.y, CTRL, 0xf, 0xf, false);
+  v.x = __builtin_amdgcn_mov_dpp(v.x, CTRL, 0xf, 0xf, true);
+  v.y = __builtin_amdgcn_mov_dpp(v.y, CTRL, 0xf, 0xf, true);
   return x + *reinterpret_cast<double*>(&v);
 }
 // sum over each row of 16 lanes, on every lane (fixed order)
@@ -2107,6 +2107,20 @@ __device__ __forceinline__ double row_sum(double x) {
   x = dpp_add<0x4E>(x);                 // quad_perm [2, 3, 0, 1]
   x = dpp_add<0x141>(x);                // row_half_mirror
   return dpp_add<0x140>(x);             // row_mirror
+}
+
+// largest of a value that is the same in each row of 16 lanes, for the whole wave
+__device__ __forceinline__ int row_max(int x) {
+  return max(max(__builtin_amdgcn_readlane(x, 0), __builtin_amdgcn_readlane(x, 16)),
+             max(__builtin_amdgcn_readlane(x, 32), __builtin_amdgcn_readlane(x, 48)));
+}
+// x (|x| < 2^31) rounded to a whole number, as a double and an integer, by an addition
+// that leaves the number in the low bits
+__device__ __forceinline__ double round_int(double x, double scale, int& n) {
+  const double big = 6755399441055744.0;                 // 1.5 2^52
+  const double t = fma(x, scale, big);
+  n = __double2loint(t);
+  return t - big;
 }
 
 // An item's per-lane sums sum_j V_j s_j^k of the samples V = S e^{i Phi} that its
@@ -2129,7 +2143,17 @@ struct Moments {
       sp = __builtin_amdgcn_sinf(rf);
       cp = __builtin_amdgcn_cosf(rf);
     } else {
-      sincos_tab(ph, tab, sp, cp);
+      // sincos_tab with the rounding of round_int
+      int n;
+      const double nd = round_int(ph, (double)kSinTab, n);
+      const double2 e = tab[n & (kSinTab - 1)];
+      const double th = fma(-1.0 / (double)kSinTab, nd, ph) * 6.283185307179586477;
+      const double z = th * th;
+      const double ps = fma3(1.0 / 120.0, z, -1.0 / 6.0);
+      const double pc = fma(fma3(-1.0 / 720.0, z, 1.0 / 24.0), z, -0.5);
+      const double sl = fma(th * z, ps, th), cl = fma(z, pc, 1.0);
+      sp = fma(e.x, cl, e.y * sl);
+      cp = fma(e.y, cl, -(e.x * sl));
     }
     const T s = (T)sd, s2 = s * s;
     const T Vr = a * cp - b * sp, Vi = a * sp + b * cp;
@@ -2179,13 +2203,19 @@ __device__ __forceinline__ double phase_poly(const double* cR, double s) {
 // four items per wavefront, each lane looping over its item's blocks, two rows
 // of the spectra in flight.  Items come in tile order and each XCD (block
 // index mod 8) takes one contiguous eighth of them, so that the rows that many
-// particles share at a time stay in its L2.
+// particles share at a time stay in its L2.  Bound by FP64 issue (about 75 vector
+// operations per row and lane, 30 of them the phase and the row's choice, 20 the
+// sine) at the three waves per SIMD that its registers allow.  A wave-uniform trip
+// count, roundings by addition and DPP moves without an old value took 26 of 175
+// operations per pair of rows, real and imaginary parts side by side one of two loads:
+// 3.57e9 bins in 1.07 M items FP64 1.31 -> 1.16 ms, partial blocks 0.53 -> 0.49 ms.
 template <bool MIXED>
 __global__ __launch_bounds__(256, MIXED ? 4 : 3) void k_eval_blocks(
     Spectra<typename std::conditional<MIXED, float, double>::type> sp,
     const int32_t* __restrict__ list, const int32_t* __restrict__ nlist,
     const double* __restrict__ rec, double* __restrict__ partials) {
   typedef typename std::conditional<MIXED, float, double>::type DT_;
+  typedef typename std::conditional<MIXED, float2, double2>::type DT2;
   typedef RecLayout<MIXED> L;
   __shared__ double2 s_tab[MIXED ? 1 : kSinTab];
   __shared__ double s_rec[4][4][kRecPad];
@@ -2205,7 +2235,7 @@ __global__ __launch_bounds__(256, MIXED ? 4 : 3) void k_eval_blocks(
   const double y = c * xc;                                  // this lane's node
   sincospi(0.5 / (double)kSpecNodes, &xs, &xc);
   const double chord = 0.5 / (c * xc);                      // 1 / (distance of the end nodes)
-  const double invQ = 1.0 / (double)sp.Q;
+  const double invQ = 1.0 / (double)sp.Q, slmax = (double)(sp.nslots - 1) * invQ;
   const int lg = __builtin_ctz(sp.L);
   int first = lo + (int)(blockIdx.x >> 3) * 16 + wv * 4;    // of this wave's four items
   for (; first < hi; first += step) {
@@ -2225,28 +2255,33 @@ __global__ __launch_bounds__(256, MIXED ? 4 : 3) void k_eval_blocks(
     const int fb = (b0 + sp.L - 1) >> lg;                   // whole blocks [fb, fb + nrow)
     const int nrow = w >= 0 ? max(min((b0 + nb) >> lg, sp.nblk) - fb, 0) : 0;
     const double Ac = A + (B * c - rint(B * c));            // the slope's phase at a block's centre
-    const DT_* base = sp.S + ((int64_t)ch * sp.nblk + fb) * sp.nslots * (2 * kSpecNodes) + m;
+    const int rows = row_max(nrow);
+    const DT2* base = reinterpret_cast<const DT2*>(sp.S) +
+                      ((int64_t)ch * sp.nblk + fb) * sp.nslots * kSpecNodes + m;
     auto loop = [&](auto dt) {
       Moments<MIXED, decltype(dt)::value> M;
       M.clear();
-      for (int i0 = 0; __any(i0 < nrow); i0 += kBlkAhead) {
+      const double row0 = (double)((fb << lg) - b0);
+      for (int i0 = 0; i0 < rows; i0 += kBlkAhead) {
         double s[kBlkAhead], ph[kBlkAhead];
+        const double mb0 = fma((double)i0, (double)sp.L, row0);
         DT_ a[kBlkAhead], b[kBlkAhead];
 #pragma unroll
         for (int u = 0; u < kBlkAhead; ++u) {
           const int i = i0 + u;
-          const double mb = (double)(((fb + i) << lg) - b0);
+          const double mb = mb0 + (double)(u * sp.L);
           s[u] = fma(alpha, mb + (c + y), -1.0);
           const double r = phase_poly(R, s[u]);   // R's head: its coefficients
           // the chord of the block's phase chooses the slope slot
           const double sl = fma(row_bcast<0>(r) - row_bcast<15>(r), chord, B);
-          const int q = min(max((int)rint(sl * (double)sp.Q), 0), sp.nslots - 1);
-          ph[u] = (r + Ac) + fma(Bp, mb, fma(-invQ, (double)q, B) * y);
+          int q;
+          const double qd = round_int(fmin(fmax(sl, 0.0), slmax), (double)sp.Q, q);
+          ph[u] = (r + Ac) + fma(Bp, mb, fma(-invQ, qd, B) * y);
           a[u] = b[u] = DT_(0);
           if (i < nrow) {
-            const DT_* row = base + ((int64_t)i * sp.nslots + q) * (2 * kSpecNodes);
-            a[u] = row[0];
-            b[u] = row[kSpecNodes];
+            const DT2 v = base[((int64_t)i * sp.nslots + q) * kSpecNodes];
+            a[u] = v.x;
+            b[u] = v.y;
           }
         }
 #pragma unroll
@@ -2324,10 +2359,11 @@ __global__ __launch_bounds__(256, MIXED ? 4 : 3) void k_eval_edges(
     const int nrow = w >= 0 ? nh + ((b1 - t0 + 15) >> 4) : 0;
     const DT_* cwr = wr + (int64_t)ch * g.nbins;
     const DT_* cwi = wi + (int64_t)ch * g.nbins;
+    const int rows = row_max(nrow);
     auto loop = [&](auto dt) {
       Moments<MIXED, decltype(dt)::value> M;
       M.clear();
-      for (int i0 = 0; __any(i0 < nrow); i0 += kBlkAhead) {
+      for (int i0 = 0; i0 < rows; i0 += kBlkAhead) {
         int j[kBlkAhead];
         DT_ a[kBlkAhead], b[kBlkAhead];
 #pragma unroll
@@ -2572,10 +2608,12 @@ __device__ __forceinline__ int tile_key(const int2* __restrict__ items,
 // items there and then adds its non-zero counts to the global ones: with few
 // tiles (a narrow band) every item would otherwise hit the same few counters
 // (counting in the node kernel by global atomics cost 1.5 ms at 872,322 items
-// on 198 tiles, and 0.2 ms at 2 million on 3468).
+// on 198 tiles, and 0.2 ms at 2 million on 3468).  One large block per CU: a block clears
+// and adds up all its counters (1.07 M items on 2774 tiles, both kernels: 63 us with
+// 1024 blocks of 256, 47 with 512, 26 with 256 of 1024).
 constexpr int kTileHist = 8192;
 
-__global__ __launch_bounds__(256) void k_tile_count(const int2* __restrict__ items,
+__global__ __launch_bounds__(1024) void k_tile_count(const int2* __restrict__ items,
                                                     const int32_t* __restrict__ total,
                                                     const uint8_t* __restrict__ xflag,
                                                     int32_t ntiles, int32_t* __restrict__ tcnt) {
@@ -2635,7 +2673,7 @@ __global__ __launch_bounds__(1024) void k_tile_scan(const int32_t* __restrict__ 
 // Interpolated items into (loop, tile) order.  With the keys in LDS, the block
 // ranks its items per key locally and reserves one range per key with a single
 // global atomic.
-__global__ __launch_bounds__(256) void k_tile_scatter(const int2* __restrict__ items,
+__global__ __launch_bounds__(1024) void k_tile_scatter(const int2* __restrict__ items,
                                                       const int32_t* __restrict__ total,
                                                       const uint8_t* __restrict__ xflag,
                                                       int32_t ntiles,
@@ -3327,10 +3365,10 @@ void launch_eval(bool mixed, bool interp, double refine_budget, const Grid& g,
                          ntiles, ws.toff, ws.uoff,
                          ws.tile_items);
     } else {
-      hipLaunchKernelGGL(k_tile_count, dim3(1024), dim3(256), 0, s, ws.items, ws.total, ws.xflag,
+      hipLaunchKernelGGL(k_tile_count, dim3(256), dim3(1024), 0, s, ws.items, ws.total, ws.xflag,
                          ntiles, ws.tcnt);
       hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(1024), 0, s, ws.tcnt, ntiles, ws.toff, ws.uoff);
-      hipLaunchKernelGGL(k_tile_scatter, dim3(1024), dim3(256), 0, s, ws.items, ws.total, ws.xflag,
+      hipLaunchKernelGGL(k_tile_scatter, dim3(256), dim3(1024), 0, s, ws.items, ws.total, ws.xflag,
                          ntiles, ws.toff, ws.tcur,
                          ws.tile_items);
     }

@@ -20,11 +20,12 @@
 // g by at most pi / 4 (Q = 2 L) and the curvature by kSpecPsi64 = 0.25 rad; the Chebyshev
 // coefficients of e^{i (0.785 x + 0.25 x^2)} fall below 1e-13 at degree 16.  With Q = L the
 // slope turns it by pi / 2 and the curvature may reach 1 rad before the sixteenth coefficient
-// passes 1e-8, the mixed path's FP32 resolution.  16 nodes of 8 + 8 bytes are two whole
-// 128-byte lines per (block, slope) row.
+// passes 1e-8, the mixed path's FP32 resolution.  16 nodes of 8 + 8 bytes (real and
+// imaginary part side by side: one load per lane) are two whole 128-byte lines per
+// (block, slope) row.
 //
-// Measured at 4096 particles x 64 partitions on 7,101,001 bins: the bin sums take 1.31 ms
-// (whole blocks) + 0.50 ms (partial ones) instead of 6.8 ms in FP64, 0.82 + 0.30 instead of
+// Measured at 4096 particles x 64 partitions on 7,101,001 bins: the bin sums take 1.16 ms
+// (whole blocks) + 0.49 ms (partial ones) instead of 6.8 ms in FP64, 0.80 + 0.30 instead of
 // 3.3 ms mixed; the largest partition error against the exact loop is unchanged
 // (2.6e-12, 2.1e-11, 2.3e-10 at Np = 1, 64, 256).
 #include <cmath>
@@ -126,26 +127,22 @@ __global__ __launch_bounds__(64) void k_spectra(Grid g, const double* __restrict
     er = nr;
   }
   if constexpr (D64) {
-    double* o = s64 + ((int64_t)b * nslots + q) * (2 * kSpecNodes);
+    double2* o = reinterpret_cast<double2*>(s64) + ((int64_t)b * nslots + q) * kSpecNodes;
 #pragma unroll
     for (int m = 0; m < kHalf; ++m) {
-      o[m] = Er[m] + Or[m];
-      o[kSpecNodes - 1 - m] = Er[m] - Or[m];
-      o[kSpecNodes + m] = Ei[m] + Oi[m];
-      o[2 * kSpecNodes - 1 - m] = Ei[m] - Oi[m];
+      o[m] = double2{Er[m] + Or[m], Ei[m] + Oi[m]};
+      o[kSpecNodes - 1 - m] = double2{Er[m] - Or[m], Ei[m] - Oi[m]};
     }
   }
   if constexpr (D32) {
     // with both tables the FP32 one keeps every second slope (Q = L beside Q = 2 L)
     const int q32 = D64 ? q >> 1 : q;
     if (!D64 || ((q & 1) == 0 && q32 < n32)) {
-      float* o = s32 + ((int64_t)b * n32 + q32) * (2 * kSpecNodes);
+      float2* o = reinterpret_cast<float2*>(s32) + ((int64_t)b * n32 + q32) * kSpecNodes;
 #pragma unroll
       for (int m = 0; m < kHalf; ++m) {
-        o[m] = (float)(Er[m] + Or[m]);
-        o[kSpecNodes - 1 - m] = (float)(Er[m] - Or[m]);
-        o[kSpecNodes + m] = (float)(Ei[m] + Oi[m]);
-        o[2 * kSpecNodes - 1 - m] = (float)(Ei[m] - Oi[m]);
+        o[m] = float2{(float)(Er[m] + Or[m]), (float)(Ei[m] + Oi[m])};
+        o[kSpecNodes - 1 - m] = float2{(float)(Er[m] - Or[m]), (float)(Ei[m] - Oi[m])};
       }
     }
   }
@@ -158,7 +155,7 @@ __global__ __launch_bounds__(64) void k_spectra(Grid g, const double* __restrict
 // of 512 threads takes eight nodes of a block (sixteen in 1024 threads would leave 128
 // registers for the ~220 in use): thread (j, m) has eight of node m's values in each of
 // three radix-8 stages, which exchange through LDS as [value][node], so that LDS accesses
-// and the rows' stores are whole 64-byte segments.  Twiddles come from a table of 1024 roots in LDS; a
+// and the rows' stores are whole 128-byte lines (64 in FP32).  Twiddles come from a table of 1024 roots in LDS; a
 // thread's four weights l_m stay in its registers over the blocks that its group takes.
 // About 1/6 of the direct sums' operations: 6.3 -> 1.83 ms on 7,101,001 bins, both tables
 // (4.5 GB, so 2.5 TB/s; the barriers between the stages keep it from the rate of a copy).
@@ -283,18 +280,16 @@ __global__ __launch_bounds__(kFftThreads) void k_spectra_fft(Grid g, const doubl
       y[a + 4] = zero;
     }
     fft512(y, j, m, buf, root);
-    double* o64 = s64 + (int64_t)b * nslots * (2 * kSpecNodes) + node;
-    float* o32 = D32 ? s32 + (int64_t)b * n32 * (2 * kSpecNodes) + node : nullptr;
+    double2* o64 = reinterpret_cast<double2*>(s64) + (int64_t)b * nslots * kSpecNodes + node;
+    float2* o32 = reinterpret_cast<float2*>(s32) + (int64_t)b * n32 * kSpecNodes + node;
     auto put = [&](int q, Cplx f, Cplx fe) {
       if (q >= nslots) return;
       const double k = kap * (double)q;
       const Cplx v = cmul(Cplx{fma(k, fe.i, f.r), fma(-k, fe.r, f.i)},
                           root[(2 * kFftQ - (2 * (L / 2) - 1) * q) & (2 * kFftQ - 1)]);
-      o64[(int64_t)q * (2 * kSpecNodes)] = v.r;
-      o64[(int64_t)q * (2 * kSpecNodes) + kSpecNodes] = v.i;
+      o64[(int64_t)q * kSpecNodes] = double2{v.r, v.i};
       if (D32 && !(q & 1) && (q >> 1) < n32) {
-        o32[(int64_t)(q >> 1) * (2 * kSpecNodes)] = (float)v.r;
-        o32[(int64_t)(q >> 1) * (2 * kSpecNodes) + kSpecNodes] = (float)v.i;
+        o32[(int64_t)(q >> 1) * kSpecNodes] = float2{(float)v.r, (float)v.i};
       }
     };
 #pragma unroll
