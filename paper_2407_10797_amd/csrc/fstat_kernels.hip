@@ -3162,41 +3162,71 @@ __global__ __launch_bounds__(1024) void k_solve(const PartConst* __restrict__ pc
 // ---------------------------------------------------------------------------
 // template signal (for injections): sum_i a_i A^i with the full transfer
 // ---------------------------------------------------------------------------
-__global__ void k_waveform(Grid g, const PartConst* __restrict__ pc,
-                           const double* __restrict__ amps, double* __restrict__ out) {
-  int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= g.nbins) return;
+// f^{-7/6} = f^{-1/6} / f, the root from an FP32 estimate and one third-order step on
+// f w^6 = 1 (its remainder, ~10 e^3, is below 1e-19), within two ulp
+__device__ __forceinline__ double pow_m7_6(double f) {
+  const double w = (double)__builtin_amdgcn_exp2f(__builtin_amdgcn_logf((float)f) * (-1.0f / 6.0f));
+  const double w2 = w * w;
+  const double e = fma(-(w2 * w2), w2 * f, 1.0);
+  return fma(w * e, fma(e, 7.0 / 72.0, 1.0 / 6.0), w) / f;
+}
+
+// One bin per thread and turn; 2048 blocks, so that the sine table and the particle's
+// dropped phase are set up once per block.  Bound by FP64 issue (the template's phase in
+// double-double): 7,101,001 bins 52 -> 30 us with the library's sines and power taken
+// out (the stores alone need 24).
+constexpr int kWaveBlocks = 2048;
+__global__ __launch_bounds__(256) void k_waveform(Grid g, const PartConst* __restrict__ pc,
+                                                  const double* __restrict__ amps,
+                                                  double2* __restrict__ out) {
+  __shared__ double2 s_tab[kSinTab];
+  __shared__ double2 s_drop;
   const PartConst& P = pc[0];
-  if (P.status != kStatusOk || j < P.j_lo || j > P.j_hi) {
-    out[2 * j] = 0.0;
-    out[2 * j + 1] = 0.0;
-    return;
+  const bool ok = P.status == kStatusOk;
+  if (ok) {
+    // (formed here: a call needs no plan, whose creation fills the constant table)
+    for (int i = threadIdx.x; i < kSinTab; i += blockDim.x) {
+      double sv, cv;
+      sincospi((double)i * (2.0 / (double)kSinTab), &sv, &cv);
+      s_tab[i] = double2{sv, cv};
+    }
+    if (threadIdx.x == 0) {
+      double sc, cc;
+      sincospi(2.0 * dropped_phase(P), &sc, &cc);
+      s_drop = double2{sc, cc};
+    }
   }
-  double f = bin_freq(g, j);
-  double s0, c0;
-  sincospi(kLs * f, &s0, &c0);
-  double cph, sph, tpr, tpi, txr, txi;
-  template_fp64(P, f, s0, c0, cph, sph, tpr, tpi, txr, txi, nullptr, g.chan.code[0], &g.orb);
-  // restore the constant phase the statistic drops
-  double sc, cc;
-  sincospi(2.0 * dropped_phase(P), &sc, &cc);
-  double cps = cph * cc - sph * sc, sps = sph * cc + cph * sc;   // e^{i Phi_full}
-  // full transfer: C(f) times the particle part T''
-  double x0 = kPi * kLs * f;
-  double zr = c0 * c0 - s0 * s0, zi = -2.0 * s0 * c0;
-  double omr = 1.0 - (zr * zr - zi * zi), omi = -2.0 * zr * zi;
-  double er = -x0 * s0, ei = -x0 * c0;
-  double Cr = omr * er - omi * ei, Ci = omr * ei + omi * er;
-  double Tpr = Cr * tpr - Ci * tpi, Tpi = Cr * tpi + Ci * tpr;
-  double Txr = Cr * txr - Ci * txi, Txi = Cr * txi + Ci * txr;
-  // h = f^{-7/6} e^{-i Phi} [(a1 - i a3) T+ + (-a2 + i a4) Tx]  (App. B basis)
-  double a1 = amps[0], a2 = amps[1], a3 = amps[2], a4 = amps[3];
-  double hr = (a1 * Tpr + a3 * Tpi) + (-a2 * Txr - a4 * Txi);
-  double hi = (a1 * Tpi - a3 * Tpr) + (-a2 * Txi + a4 * Txr);
-  double amp = pow(f, -7.0 / 6.0);
-  // multiply by e^{-i Phi} = cps - i sps
-  out[2 * j] = amp * (hr * cps + hi * sps);
-  out[2 * j + 1] = amp * (hi * cps - hr * sps);
+  __syncthreads();
+  const double sc = s_drop.x, cc = s_drop.y;
+  for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < g.nbins;
+       j += (int64_t)gridDim.x * blockDim.x) {
+    if (!ok || j < P.j_lo || j > P.j_hi) {
+      out[j] = double2{0.0, 0.0};
+      continue;
+    }
+    double f = bin_freq(g, j);
+    double s0, c0;
+    sincos_tab(0.5 * kLs * f, s_tab, s0, c0);
+    double cph, sph, tpr, tpi, txr, txi;
+    template_fp64(P, f, s0, c0, cph, sph, tpr, tpi, txr, txi, nullptr, g.chan.code[0], &g.orb, s_tab);
+    // restore the constant phase the statistic drops
+    double cps = cph * cc - sph * sc, sps = sph * cc + cph * sc;   // e^{i Phi_full}
+    // full transfer: C(f) times the particle part T''
+    double x0 = kPi * kLs * f;
+    double zr = c0 * c0 - s0 * s0, zi = -2.0 * s0 * c0;
+    double omr = 1.0 - (zr * zr - zi * zi), omi = -2.0 * zr * zi;
+    double er = -x0 * s0, ei = -x0 * c0;
+    double Cr = omr * er - omi * ei, Ci = omr * ei + omi * er;
+    double Tpr = Cr * tpr - Ci * tpi, Tpi = Cr * tpi + Ci * tpr;
+    double Txr = Cr * txr - Ci * txi, Txi = Cr * txi + Ci * txr;
+    // h = f^{-7/6} e^{-i Phi} [(a1 - i a3) T+ + (-a2 + i a4) Tx]  (App. B basis)
+    double a1 = amps[0], a2 = amps[1], a3 = amps[2], a4 = amps[3];
+    double hr = (a1 * Tpr + a3 * Tpi) + (-a2 * Txr - a4 * Txi);
+    double hi = (a1 * Tpi - a3 * Tpr) + (-a2 * Txi + a4 * Txr);
+    const double amp = pow_m7_6(f);
+    // multiply by e^{-i Phi} = cps - i sps
+    out[j] = double2{amp * (hr * cps + hi * sps), amp * (hi * cps - hr * sps)};
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -3468,7 +3498,8 @@ void launch_extrinsic(const double* amps, const double* params, int64_t n, doubl
 
 void launch_waveform(const Grid& g, const PartConst* pc, const double* amps,
                      double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_waveform, dim3(nblk(g.nbins, 256)), dim3(256), 0, s, g, pc, amps, out);
+  hipLaunchKernelGGL(k_waveform, dim3(std::min<unsigned>(nblk(g.nbins, 256), kWaveBlocks)), dim3(256),
+                     0, s, g, pc, amps, reinterpret_cast<double2*>(out));
 }
 
 }  // namespace fstat
