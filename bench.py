@@ -35,9 +35,9 @@ PEAK_F32_TFLOPS = 157.3
 PEAK_HBM_GBPS = 8000.0
 PEAK_LANE_INSTR = 256 * 64 * 2.4e9
 
-# Algorithmic FLOPs of the interpolating loop (FMA = 2), derived from its
-# arithmetic (see the repository documentation), per bin-template and per lane
-# run (the lanes of an item that hold bins, each of which does its per-lane
+# Algorithmic FLOPs of the per-bin interpolating loop k_eval_interp (FMA = 2),
+# derived from its arithmetic (see the repository documentation), per
+# bin-template and per lane run (the lanes of an item that hold bins, each of which does its per-lane
 # work once).  Direct loop, per bin: the item coordinate s and s^2, s^4, s^8
 # (5), the phase polynomial in Estrin form (18) plus the linear and grid terms
 # (5), sin/cos by table and Taylor series (22), w e^{i Phi} (6), and the
@@ -86,9 +86,10 @@ def bin_mix_dict(mixed, mix):
 
 
 def alg_flops(kind, mix, runs=True):
-    """Algorithmic FLOPs of the main kernel over one launch, from the launch's
+    """Algorithmic FLOPs of the per-bin loop over one launch, from the launch's
     bins and lane runs by kind of work (fstat_interp_stats bin_mix), as (FP64,
-    FP32); runs=False: the per-bin work alone."""
+    FP32); runs=False: the per-bin work alone.  On plans with block spectra the
+    block loop does the same bins' sums with about a fifth of that work."""
     r = 1.0 if runs else 0.0
     if kind == "fp64":
         k = BIN_MIX_KEYS
@@ -121,22 +122,22 @@ def calibrate(reps=10):
                           "hbm_GBps": PEAK_HBM_GBPS}}
 
 
-# Per bin-template figures of the main bin-loop kernel of each path counted
-# by rocprofv3 (the interpolating loop k_eval_interp;
-# profiles/k_eval_interp_paper_4096x64_counters.md): floating-point operations
-# executed (FP64 + FP32, FMA = 2, x64 lanes), VALU instructions, HBM bytes read
-# per bin-template (FETCH_SIZE x 2, calibrated on a plain copy) and bytes
-# written per launch (WRITE_SIZE).
-MAIN_KERNEL = {"fp64": "k_eval_interp<false>", "mixed": "k_eval_interp<true>"}
-FLOP_PER_BIN = {"fp64": 69.19, "mixed": 30.90}      # FP64 + FP32
-FLOP32_PER_BIN = {"fp64": 0.00, "mixed": 20.69}      # of which FP32
-VALU_PER_BIN = {"fp64": 56.42, "mixed": 30.55}
-VALU32_PER_BIN = {"fp64": 0.00, "mixed": 16.01}      # of which FP32 arithmetic
-TRAFFIC = {"fp64": (0.3551, 1.046e+08), "mixed": (0.2081, 6.732e+07)}
+# Per bin-template figures of the bin sums of each path counted by rocprofv3 (the
+# kernels between the main-kernel events: the block loop's whole and partial
+# blocks; profiles/bin_loops_paper_4096x64_counters.md): floating-point
+# operations executed (FP64 + FP32, FMA = 2, x64 lanes), VALU instructions, HBM
+# bytes read per bin-template (FETCH_SIZE x 2, calibrated on a plain copy) and
+# bytes written per launch (WRITE_SIZE).
+MAIN_KERNEL = {"fp64": "k_eval_blocks<false> + k_eval_edges<false>",
+               "mixed": "k_eval_blocks<true> + k_eval_edges<true>"}
+FLOP_PER_BIN = {"fp64": 13.09, "mixed": 9.65}      # FP64 + FP32
+FLOP32_PER_BIN = {"fp64": 0.01, "mixed": 4.39}      # of which FP32
+VALU_PER_BIN = {"fp64": 11.51, "mixed": 9.38}
+TRAFFIC = {"fp64": (1.1750, 4.983e+07), "mixed": (0.4828, 4.096e+07)}
 # sha256 of the bin-loop kernels' code (fstat_kernels.hip and the two headers
 # it builds on, comments removed) when those counters were taken; the figures
 # are reported as null once it differs.
-COUNTERS_SRC_SHA = "e8889c6449f65bacb229c420ddea1065f83206feb718405fdafe89e2bf523b38"
+COUNTERS_SRC_SHA = "4592f8b8ab4c9e0a24e15bd35874727aebfa4bdc1865e08d82ee6fd98e43d232"
 KERNEL_HEADERS = ("fstat_internal.h", "fstat_kernels.h")
 
 
@@ -521,22 +522,26 @@ def main():
         kind = "mixed" if mixed else "fp64"
         secs = r["main_ms"] * 1e-3          # the main kernel alone (HIP events)
         bins = r["bins_per_launch"]
-        # algorithmic FLOPs of the main kernel per launch, from its bin and run mix
-        a64, a32 = alg_flops(kind, mix)
-        alg = a64 + a32
-        peak = floor_peak(a64, a32, PEAK_VALU_TFLOPS, PEAK_F32_TFLOPS)
-        achieved = alg / secs / 1e12
+        # FLOPs that the bin sums execute per launch (counted): their algorithm's
+        # own, samples per block and not bins
+        f32 = FLOP32_PER_BIN[kind] * bins
+        f64 = FLOP_PER_BIN[kind] * bins - f32
         step_secs = r["seconds"] / args.steps
-        b64, b32 = alg_flops(kind, mix, runs=False)
-        roof = dict(bound="alu", achieved=achieved, peak=round(peak, 1), unit="TFLOP/s",
-                    frac=achieved / peak, flop_per_launch=alg, flop_fp32_per_launch=a32,
-                    frac_step=alg / step_secs / 1e12 / peak,
-                    flop_bins_per_launch=b64 + b32,
-                    frac_bins=(b64 + b32) / secs / 1e12 / floor_peak(b64, b32, PEAK_VALU_TFLOPS,
-                                                                     PEAK_F32_TFLOPS))
-        if calib:
-            pm = floor_peak(a64, a32, calib["fp64_fma_tflops"], calib["fp32_fma_unpacked_tflops"])
-            roof.update(peak_measured=round(pm, 1), frac_measured=achieved / pm)
+        roof = dict(bound="alu", unit="TFLOP/s", flop_source="counters")
+        if same_src:
+            peak = floor_peak(f64, f32, PEAK_VALU_TFLOPS, PEAK_F32_TFLOPS)
+            achieved = (f64 + f32) / secs / 1e12
+            roof.update(achieved=achieved, peak=round(peak, 1), frac=achieved / peak,
+                        flop_per_launch=f64 + f32, flop_fp32_per_launch=f32,
+                        frac_step=(f64 + f32) / step_secs / 1e12 / peak)
+            if calib:
+                pm = floor_peak(f64, f32, calib["fp64_fma_tflops"],
+                                calib["fp32_fma_unpacked_tflops"])
+                roof.update(peak_measured=round(pm, 1), frac_measured=achieved / pm)
+        else:
+            roof.update(achieved=None, peak=None, frac=None)
+        # what the same bins would cost one by one
+        roof["per_bin_loop_flop_per_launch"] = sum(alg_flops(kind, mix))
         # the counted figures belong to the kernel sources they were counted on
         rd, wr = TRAFFIC[kind]
         traffic = rd * bins + wr if same_src else None

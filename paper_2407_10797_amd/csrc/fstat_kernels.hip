@@ -1,24 +1,28 @@
 // fstat_kernels.hip -- gfx950 kernels of the batched semi-coherent F-statistic.
 //
 // One evaluation (Sec. II.B, Eq. semi-cohF of arXiv:2407.10797) is a chain of
-// small kernels around one heavy one:
+// kernels:
 //   k_setup         one wavefront per particle: intrinsic parameters -> PN
 //                   constants, sky frame, support [f_lo, f_hi] (t_f inverted by
-//                   two 32-point searches), Np partition edges (bin indices) and the
-//                   work-item counts: a work item is the part of a partition
-//                   inside one tile of the global tiling of the band
+//                   two clustered searches), Np partition edges (bin indices) and the
+//                   work-item counts: a work item is the part of a partition inside
+//                   one tile of the global tiling of the band, or a few tiles
 //   k_worklist      exclusive scan of the work-item counts and the work list, item
-//                   -> (particle*stride + partition, tile index); for many counts
-//                   k_scan_* (three passes) and k_fill
+//                   -> (particle*stride + partition, tile and tiles); for many
+//                   particles k_scan_* (three passes) and k_fill
 //   k_interp_nodes  exact template at 10 Chebyshev nodes and both ends of every
-//                   item -> interpolation record, or hand-over to the exact loop
-//   k_tile_*        items grouped by tile; scheduling units of <= 32 items
-//   k_eval_interp   persistent blocks take units dynamically, stage the tile's
-//                   data in LDS, and evaluate the interpolated template at every
-//                   bin of each item (FP64: advanced by a difference recurrence
-//                   along each lane's run of bins): the N-term sums per item
-//                   (deterministic, no float atomics); the M-terms come from the
-//                   node kernel's quadrature
+//                   item -> interpolation record, or hand-over to the exact loop;
+//                   the M-terms by quadrature
+//   k_tile_*        items grouped by tile, the block loop's and the per-bin loop's
+//                   (k_tile_group: small calls, in one block)
+//   k_eval_blocks   N-terms of whole blocks from the plan's block spectra
+//                   (spectra.hip): sixteen samples per block
+//   k_eval_edges    N-terms of the partial blocks at a partition's ends, bin by bin
+//   k_eval_interp   the per-bin loop, for items without block spectra: persistent
+//                   blocks take scheduling units of <= 64 items of a tile, stage the
+//                   tile's data in LDS, and evaluate the interpolated template at
+//                   every bin (FP64: advanced by a difference recurrence along each
+//                   lane's run of bins); deterministic sums, no float atomics
 //   k_eval_exact    the exact template at every bin, for handed-over items, for
 //                   refinement and under FSTAT_EVAL_EXACT (FP64 and mixed)
 //   k_mark          partitions whose interpolation error could matter -> exact
