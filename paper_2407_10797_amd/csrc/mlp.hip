@@ -32,13 +32,18 @@ __device__ __forceinline__ v4f mfma32(v8s a, v8s b, v4f c) {
 }
 
 __device__ __forceinline__ uint16_t f2bf(float f) {   // round to nearest even
-  uint32_t u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
+  return __builtin_bit_cast(uint16_t, (__bf16)f);       // v_cvt_pk_bf16_f32
 }
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 __device__ __forceinline__ float sigm(float z) { return 1.0f / (1.0f + __expf(-z)); }
 __device__ __forceinline__ float silu(float z) { return z * sigm(z); }
+// SiLU for the inference kernel: the reciprocal by the hardware's estimate and one
+// Newton step, within 0.51 ulp, in 3 operations for the division's ~10
+__device__ __forceinline__ float silu_nr(float z) {
+  const float d = 1.0f + __expf(-z), r = __builtin_amdgcn_rcpf(d);
+  const float q = fmaf(fmaf(-d, r, 1.0f), r, r);
+  return z * (d < 3.0e38f ? q : 0.0f);                  // e^-z past FP32: 1 / inf
+}
 __device__ __forceinline__ float dsilu(float z) {
   float s = sigm(z);
   return s * (1.0f + z * (1.0f - s));
@@ -522,9 +527,14 @@ __global__ void k_grad(GradParts p, int64_t n, float* __restrict__ g) {
 }
 
 // Inference-only forward of the whole network on R rows, keeping no
-// activations (knot evaluation).  One wavefront per 16 rows, four per block;
-// the weights pass through LDS in 16 KB k-slabs of 32 shared by the four
-// waves.  Layer 1 runs on the VALU straight into the MFMA A-operand layout
+// activations (knot evaluation).  One wavefront per 32 rows (two MFMA tiles), four
+// per block; the weights pass through LDS in 16 KB k-slabs of 32 shared by the four
+// waves, and a fragment that a wave reads serves both of its tiles (with one tile
+// the fragment reads, 64 KB per slab and CU, bounded the kernel: 1.05 M rows
+// 1.38 -> 1.18 ms; three and four tiles at one wave per SIMD 1.55 and 2.06).  Then
+// bound by the activations' VALU work: with the reciprocal of silu_nr in place of a
+// division and the hardware's BF16 rounding 0.98 ms.
+// Layer 1 runs on the VALU straight into the MFMA A-operand layout
 // (lane l: row l % 16, k = 32 kb + 8 (l / 16) + j); layers 2-4 are 16x16x32
 // BF16 MFMA tiles over all 256 outputs with the weights' BF16 copies read from
 // the LDS slabs in the B-operand layout (col l % 16, same k); between layers
@@ -532,32 +542,37 @@ __global__ void k_grad(GradParts p, int64_t n, float* __restrict__ g) {
 // (row 4 (l / 16) + r, col l % 16) back into the A layout.  The output unit
 // is a lane reduction.  Same operand rounding as the training forward: BF16
 // hidden activations, FP32 last pre-activation, FP32 output layer.
+constexpr int kInferTiles = 2;
 __global__ __launch_bounds__(256, 2) void k_mlp_infer(const float* __restrict__ x, int64_t R,
                                                    const float* __restrict__ P,
                                                    const uint16_t* __restrict__ wbf,
                                                    float* __restrict__ y) {
+  constexpr int MT = kInferTiles;
   __shared__ __align__(16) uint16_t T[4][16][kHid + 8];
   __shared__ __align__(16) uint16_t Ws[2][kHid][kGemmK + 8];   // two k-slabs of W (rows n, 32 k)
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int c16 = lane & 15, g4 = lane >> 4;
-  const int64_t r0 = ((int64_t)blockIdx.x * 4 + w) * 16;
-  const int64_t row = r0 + c16 < R ? r0 + c16 : R - 1;
-  const float x0 = x[row * 3 + 0], x1 = x[row * 3 + 1], x2 = x[row * 3 + 2];
+  const int64_t r0 = ((int64_t)blockIdx.x * 4 + w) * (16 * MT);
   constexpr int NK = kHid / kGemmK;
-  v8s a[NK];
+  v8s a[MT][NK];
   {
     const float* W1 = P + mlp_off_w(0);
     const float* b1 = P + mlp_off_b(0);
 #pragma unroll
-    for (int kb = 0; kb < NK; ++kb)
+    for (int t = 0; t < MT; ++t) {
+      const int64_t row = r0 + 16 * t + c16 < R ? r0 + 16 * t + c16 : R - 1;
+      const float x0 = x[row * 3 + 0], x1 = x[row * 3 + 1], x2 = x[row * 3 + 2];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int k = kGemmK * kb + 8 * g4 + j;
-        float z = b1[k] + W1[3 * k] * x0 + W1[3 * k + 1] * x1 + W1[3 * k + 2] * x2;
-        a[kb][j] = (short)f2bf(silu(z));
-      }
+      for (int kb = 0; kb < NK; ++kb)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const int k = kGemmK * kb + 8 * g4 + j;
+          float z = b1[k] + W1[3 * k] * x0 + W1[3 * k + 1] * x1 + W1[3 * k + 2] * x2;
+          a[t][kb][j] = (short)f2bf(silu_nr(z));
+        }
+    }
   }
-  v4f acc[16];
+  v4f acc[MT][16];
   // W_l[n][k] in k-slabs of 32 (16 KB), staged in LDS once for the block's four
   // waves and double-buffered: slab kb + 1 is fetched while slab kb is used
   const int tid = threadIdx.x;                      // row n of W that this thread stages
@@ -565,7 +580,9 @@ __global__ __launch_bounds__(256, 2) void k_mlp_infer(const float* __restrict__ 
     const uint16_t* W = wbf + (size_t)L * kHid * kHid;
     const float* bias = P + mlp_off_b(L + 1);
 #pragma unroll
-    for (int nt = 0; nt < 16; ++nt) acc[nt] = v4f{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+      for (int nt = 0; nt < 16; ++nt) acc[t][nt] = v4f{0.f, 0.f, 0.f, 0.f};
     {
       const uint4* src = reinterpret_cast<const uint4*>(W + (size_t)tid * kHid);
 #pragma unroll
@@ -584,7 +601,8 @@ __global__ __launch_bounds__(256, 2) void k_mlp_infer(const float* __restrict__ 
 #pragma unroll
       for (int nt = 0; nt < 16; ++nt) {
         const v8s b = *reinterpret_cast<const v8s*>(&Ws[kb & 1][16 * nt + c16][8 * g4]);
-        acc[nt] = mfma32(a[kb], b, acc[nt]);
+#pragma unroll
+        for (int t = 0; t < MT; ++t) acc[t][nt] = mfma32(a[t][kb], b, acc[t][nt]);
       }
       if (kb + 1 < NK) {
 #pragma unroll
@@ -593,39 +611,47 @@ __global__ __launch_bounds__(256, 2) void k_mlp_infer(const float* __restrict__ 
       __syncthreads();
     }
     if (L < 2) {
+      // the wave's own rows of T, one tile after the other
 #pragma unroll
-      for (int nt = 0; nt < 16; ++nt) {
-        const float bn = bias[16 * nt + c16];
+      for (int t = 0; t < MT; ++t) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) T[w][4 * g4 + r][16 * nt + c16] = f2bf(silu(acc[nt][r] + bn));
+        for (int nt = 0; nt < 16; ++nt) {
+          const float bn = bias[16 * nt + c16];
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            T[w][4 * g4 + r][16 * nt + c16] = f2bf(silu_nr(acc[t][nt][r] + bn));
+        }
+        __builtin_amdgcn_wave_barrier();      // LDS operations of a wave complete in order
+#pragma unroll
+        for (int kb = 0; kb < NK; ++kb)
+          a[t][kb] = *reinterpret_cast<const v8s*>(&T[w][c16][kGemmK * kb + 8 * g4]);
+        __builtin_amdgcn_wave_barrier();
       }
-      __syncthreads();
-#pragma unroll
-      for (int kb = 0; kb < NK; ++kb)
-        a[kb] = *reinterpret_cast<const v8s*>(&T[w][c16][kGemmK * kb + 8 * g4]);
-      __syncthreads();
     }
   }
   const float* w5 = P + mlp_off_w(4);
   const float* b4 = P + mlp_off_b(3);
-  float s[4] = {0.f, 0.f, 0.f, 0.f};
+  const float b5 = P[mlp_off_b(4)];
 #pragma unroll
-  for (int nt = 0; nt < 16; ++nt) {
-    const int n = 16 * nt + c16;
-    const float wn = w5[n], bn = b4[n];
+  for (int t = 0; t < MT; ++t) {
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int r = 0; r < 4; ++r) s[r] += wn * silu(acc[nt][r] + bn);
-  }
+    for (int nt = 0; nt < 16; ++nt) {
+      const int n = 16 * nt + c16;
+      const float wn = w5[n], bn = b4[n];
 #pragma unroll
-  for (int r = 0; r < 4; ++r)
+      for (int r = 0; r < 4; ++r) s[r] += wn * silu_nr(acc[t][nt][r] + bn);
+    }
 #pragma unroll
-    for (int o = 1; o < 16; o <<= 1) s[r] += __shfl_xor(s[r], o, 64);
-  if (c16 == 0) {
-    const float b5 = P[mlp_off_b(4)];
+    for (int r = 0; r < 4; ++r)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t m = r0 + 4 * g4 + r;
-      if (m < R) y[m] = s[r] + b5;
+      for (int o = 1; o < 16; o <<= 1) s[r] += __shfl_xor(s[r], o, 64);
+    if (c16 == 0) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t m = r0 + 16 * t + 4 * g4 + r;
+        if (m < R) y[m] = s[r] + b5;
+      }
     }
   }
 }
@@ -730,7 +756,7 @@ int Mlp::infer_alloc(int64_t rows) {
 
 void Mlp::infer(const float* x, int64_t rows, hipStream_t s) {
   if (rows <= 0) return;
-  hipLaunchKernelGGL(k_mlp_infer, dim3(nb(rows, 64)), dim3(256), 0, s, x, rows, params, wbf, yinf);
+  hipLaunchKernelGGL(k_mlp_infer, dim3(nb(rows, 64 * kInferTiles)), dim3(256), 0, s, x, rows, params, wbf, yinf);
 }
 
 void Mlp::refresh_bf16(hipStream_t s) {
