@@ -416,7 +416,7 @@ int fstat_autotune(fstat_plan_t P, const double* params, int64_t n, int32_t np_u
     static const int chunks[] = {256, 512, 1024, 2048, 2560, 4096, 4608, 5120, 8192};
     static const int mults[] = {1, 2, 4};
     // tiles above the per-bin loop's LDS stage only where the block loop takes the items
-    constexpr int kTuneMixed = 5120;
+    constexpr int kTuneMixed = 5120, kTuneSpecMin = 2048;
     const int tile_limit = mixed && P->s32.L > 0 ? kTuneMixed : interp_max_tile(mixed);
     double* F = nullptr;
     int rc = hip_check(hipMalloc(&F, sizeof(double) * n), "alloc tune out");
@@ -434,6 +434,10 @@ int fstat_autotune(fstat_plan_t P, const double* params, int64_t n, int32_t np_u
       for (int ci = 0; ci < (int)(sizeof(chunks) / sizeof(chunks[0])) && !rc; ++ci)
         for (int mi = 0; mi < 3 && !rc; ++mi) {
           if (ex ? chunks[ci] == kTuneMixed : chunks[ci] > tile_limit) continue;
+          // with block spectra a smaller tile only means more nodes, records and workspace
+          // (9216 particles on 7.1M bins: 144 GB at 256 bins, whose release slows the
+          // device's next large allocations by seconds)
+          if (!ex && (mixed ? P->s32.L : P->s64.L) > 0 && chunks[ci] < kTuneSpecMin) continue;
           if (mixed) { P->chunk_mixed = chunks[ci]; P->grid_mult_mixed = mults[mi]; }
           else { P->chunk = chunks[ci]; P->grid_mult_fp64 = mults[mi]; }
           double t_min = 1e300;
