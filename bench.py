@@ -130,14 +130,14 @@ def calibrate(reps=10):
 # bytes written per launch (WRITE_SIZE).
 MAIN_KERNEL = {"fp64": "k_eval_blocks<false> + k_eval_edges<false>",
                "mixed": "k_eval_blocks<true> + k_eval_edges<true>"}
-FLOP_PER_BIN = {"fp64": 13.09, "mixed": 9.65}      # FP64 + FP32
+FLOP_PER_BIN = {"fp64": 13.12, "mixed": 9.62}      # FP64 + FP32
 FLOP32_PER_BIN = {"fp64": 0.01, "mixed": 4.39}      # of which FP32
-VALU_PER_BIN = {"fp64": 11.51, "mixed": 9.38}
-TRAFFIC = {"fp64": (1.1729, 4.985e+07), "mixed": (0.4826, 4.096e+07)}
+VALU_PER_BIN = {"fp64": 11.58, "mixed": 9.33}
+TRAFFIC = {"fp64": (1.1367, 4.979e+07), "mixed": (0.5601, 4.069e+07)}
 # sha256 of the bin-loop kernels' code (fstat_kernels.hip and the two headers
 # it builds on, comments removed) when those counters were taken; the figures
 # are reported as null once it differs.
-COUNTERS_SRC_SHA = "2cb1489dbd2a2bc8bd8b80d8125acc27c85ecb6fb9712abc5060398b3bd502f8"
+COUNTERS_SRC_SHA = "a334ee3107bac21fd4ffd2ed2b08fee7ead18874e29cd55249d2b26c077aba12"
 KERNEL_HEADERS = ("fstat_internal.h", "fstat_kernels.h")
 
 

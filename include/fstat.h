@@ -116,7 +116,9 @@ typedef struct {
                            the noise-weighted norm of each item's template
                            error and the error of its quadrature M-terms)
                            get their largest-error items evaluated again
-                           exactly.  0 = 5e-10; < 0 = never                 */
+                           exactly.  Block spectra are used up to the frequency
+                           where their own error is half of it (none below
+                           8e-12).  0 = 5e-10; < 0 = never                   */
 } fstat_opts;
 
 /* Create a plan: validates the grid (EINVAL on nbins < 1, df <= 0, k_lo < 1,

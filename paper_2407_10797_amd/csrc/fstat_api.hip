@@ -174,6 +174,9 @@ static int make_spectra(fstat_plan_s* P, hipStream_t s) {
   Spectra<float> t32{};
   t64.L = (P->prec & FSTAT_FP64) ? spectra_block(false, g.nbins) : 0;
   t32.L = (P->prec & FSTAT_MIXED) ? spectra_block(true, g.nbins) : 0;
+  t32.fmax = HUGE_VAL;              // the mixed path's phases are FP32
+  t64.fmax = t64.L ? spec_fmax(g, 2 * t64.L, P->refine_budget) : 0.0;
+  if (!((double)g.k_lo * g.df < t64.fmax)) t64.L = 0;
   if ((!t64.L && !t32.L) || !(g.T_obs * g.df <= kSpecMaxSlope)) return FSTAT_OK;
   const bool shared = t64.L == t32.L;
   size_t n64 = 0, n32 = 0;          // values per channel

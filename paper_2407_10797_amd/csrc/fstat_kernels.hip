@@ -31,6 +31,7 @@
 //                   F_hat = mean_l F_l, or -inf / NaN
 #include "fstat_internal.h"
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "fstat_kernels.h"
@@ -1209,12 +1210,14 @@ constexpr double kInterpTolTMixed = 3e-8;
 //
 // With block spectra (sp.L > 0) an item goes to the block loop when over any
 // of its blocks the phase stays within sp.psi radians of a straight line and
-// its slope within half a slot of the spectra's range; otherwise to the
-// per-bin loop.  sup |R'| and sup |R''| are bounded by the coefficients' sums.
+// its slope within half a slot of the spectra's range, and it ends below the
+// spectra's fmax; otherwise to the per-bin loop.  sup |R'| and sup |R''| are
+// bounded by the coefficients' sums.
 struct SpecShape {
   int32_t L, Q, nslots, nblk;
   double psi;
   double hq, smax;      // half a slot of the slope grid, its last slot
+  double fmax;          // see Spectra
 };
 template <bool MIXED, bool TAB>
 __global__ __launch_bounds__(256, TAB ? 2 : 3) void k_interp_nodes(Grid g,
@@ -1522,7 +1525,8 @@ __global__ __launch_bounds__(256, TAB ? 2 : 3) void k_interp_nodes(Grid g,
       if (sp.L > 0) {
         const double half = 0.5 * (double)(sp.L - 1) * alpha;
         const double sl = alpha * d1;
-        blocks = kPi * d2 * half * half <= sp.psi && B - sl >= -sp.hq && B + sl <= sp.smax + sp.hq;
+        blocks = kPi * d2 * half * half <= sp.psi && B - sl >= -sp.hq && B + sl <= sp.smax + sp.hq &&
+                 bin_freq(g, b1 - 1) < sp.fmax;
       }
       const int state = rej ? kRecExact : (blocks ? kRecBlocks : kRecBins);
       int2* ri = reinterpret_cast<int2*>(r + L::tail + 3);
@@ -2430,8 +2434,44 @@ __global__ __launch_bounds__(256, MIXED ? 4 : 3) void k_eval_edges(
 // exactly, which brings the remainder under the budget.  Partitions within a
 // factor kFragile of the pseudo-inverse cut are refined whole (a small error
 // could flip the rank decision).
+//
+// The block loop adds an error of its own to the items it takes: the sixteen-point
+// interpolation, at most kSpecErrFp64 per sample, and the grid rounding, which the
+// spectra take at the slot's slope, up to 2 pi |B - beta_q| e_j / df radians per bin,
+// |B - beta_q| <= 1 / (2 Q), |e_j| half an ulp of f (spectra.hip).  Both multiply the
+// template's two polarisations by one factor 1 + eps_j (to the change of T over a
+// block), so that dA beta = eps A beta whatever beta is: |dA beta| <= max|eps| sqrt(2F)
+// without the conditioning that b carries, and the partition's share is
+//   (kappa + sqrt(2F)) sqrt(2F) max|eps|,
+// at most kSpecGain max|eps| of max(F, 1) (at F = 1).  spec_fmax keeps that within half
+// the budget; the terms above have the rest.  (At 2.5 years and Q = 512 it is
+// 1.4e-11..8.7e-11 from 10 to 100 mHz.  Summed into e instead, with b's conditioning, it
+// would send nearly every item of a 4096 x 64 batch to the exact loop: 2.8 -> 32.7 ms.)
 constexpr double kRefineKappa = 16.0;
 constexpr double kFragile = 1e3;
+constexpr double kSpecErrFp64 = 1.6e-13;   // slope pi / 4, curvature 0.25 rad: 1.5e-13
+constexpr double kSpecGain = 24.63;        // (kappa + sqrt 2) sqrt 2
+
+// 2 pi |B - beta_q| / df at its largest, 0 where every k df is a double (df has `bits`
+// significant bits, k at most 53 - bits)
+static double spec_grid(const Grid& g, int32_t Q) {
+  int e = 0, bits = 0;
+  uint64_t m = (uint64_t)std::ldexp(std::frexp(g.df, &e), 53);
+  while (!(m & 1)) m >>= 1;
+  for (; m; m >>= 1) ++bits;
+  return ((uint64_t)(g.k_lo + g.nbins - 1) >> (53 - bits)) == 0 ? 0.0 : kPi / (Q * g.df);
+}
+
+// The frequency (a power of two: half an ulp of f changes there) up to which the FP64
+// block loop's error stays within half the refinement budget; items that reach above
+// take the per-bin loop, which has each bin's rounding exactly.  Budget 5e-10 at 2.5
+// years: 62.5 mHz with Q = 128, 125 mHz with Q = 256, 250 mHz with Q = 512.
+double spec_fmax(const Grid& g, int32_t Q, double budget) {
+  if (!(budget > 0.0)) return HUGE_VAL;                   // no estimate asked for
+  const double eps = 0.5 * budget / kSpecGain - kSpecErrFp64, gr = spec_grid(g, Q);
+  if (!(eps > 0.0)) return 0.0;
+  return gr > 0.0 ? std::ldexp(1.0, std::ilogb(eps / gr) + 54) : HUGE_VAL;
+}
 
 // Sums of a partition's items [o, o + c): eight lanes, lane k the k-th of the
 // eight terms (an item's partials are one 64-byte line), Neumaier sums in item
@@ -2466,7 +2506,9 @@ __device__ __forceinline__ void partition_sums(const double* __restrict__ partia
 }
 
 // Eight lanes per partition.
-__global__ __launch_bounds__(256) void k_mark(const PartConst* __restrict__ pc, int64_t n,
+__global__ __launch_bounds__(256) void k_mark(Grid g, double grid_term,
+                                              const PartConst* __restrict__ pc, int64_t n,
+                                              const int32_t* __restrict__ bounds,
                                               int32_t stride, const int32_t* __restrict__ cnt,
                                               const int32_t* __restrict__ off,
                                               const double* __restrict__ partials,
@@ -2476,14 +2518,19 @@ __global__ __launch_bounds__(256) void k_mark(const PartConst* __restrict__ pc, 
                                               int32_t* __restrict__ nrefine) {
   const int64_t q = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 3;
   const int k = threadIdx.x & 7, lane = threadIdx.x & 63;
-  int o = 0, c = 0;                            // no items: the group only takes part in the scan
+  int o = 0, c = 0, last = 0;                  // no items: the group only takes part in the scan
   if (q < n * stride) {
     const int64_t p = q / stride;
     const PartConst& P = pc[p];
-    if ((int)(q - p * stride) < P.np && P.status == kStatusOk) { o = off[q]; c = cnt[q]; }
+    const int l = (int)(q - p * stride);
+    if (l < P.np && P.status == kStatusOk) {
+      o = off[q];
+      c = cnt[q];
+      last = bounds[p * (stride + 1) + l + 1];
+    }
   }
   // the items' error terms, every eighth item per lane
-  int ninterp = 0;
+  int ninterp = 0, nblocks = 0;
   double s2 = 0.0, mt = 0.0;
   for (int i = k; i < c; i += 32) {              // four of them under way
     uint8_t f[4];
@@ -2498,6 +2545,7 @@ __global__ __launch_bounds__(256) void k_mark(const PartConst* __restrict__ pc, 
     for (int u = 0; u < 4; ++u)
       if (i + 8 * u < c && f[u] != kItemExact) {
         ++ninterp;
+        nblocks += f[u] == kItemBlocks ? 1 : 0;
         s2 = fma((double)x[u].x, (double)x[u].x, s2);
         mt += (double)x[u].y;
       }
@@ -2505,6 +2553,7 @@ __global__ __launch_bounds__(256) void k_mark(const PartConst* __restrict__ pc, 
 #pragma unroll
   for (int d = 4; d > 0; d >>= 1) {
     ninterp += __shfl_xor(ninterp, d, 8);
+    nblocks += __shfl_xor(nblocks, d, 8);
     s2 += __shfl_xor(s2, d, 8);
     mt += __shfl_xor(mt, d, 8);
   }
@@ -2524,7 +2573,12 @@ __global__ __launch_bounds__(256) void k_mark(const PartConst* __restrict__ pc, 
     const double b = hypot(beta[0], beta[1]) + hypot(beta[2], beta[3]);
     const double kt = 1.4142135623730951 * (kRefineKappa + sqrt(2.0 * fmax(F, 0.0))) * b;
     const double km = 0.5 * b * b;
-    const double tol = budget * fmax(fabs(F), 1.0);
+    double tol = budget * fmax(fabs(F), 1.0);
+    if (nblocks > 0) {
+      const double f = (double)(g.k_lo + last) * g.df, rF = sqrt(2.0 * fmax(F, 0.0));
+      const double eps = fma(grid_term, ldexp(1.0, __builtin_amdgcn_frexp_exp(f) - 54), kSpecErrFp64);
+      tol = fmax(tol - (kRefineKappa + rF) * rF * eps, 0.5 * tol);
+    }
     some = !(kt * sqrt(s2) + km * mt <= tol);
     // refining every item above these leaves at most tol / 2 in each term
     thr_t = 0.5 * tol / (kt * sqrt((double)ninterp));
@@ -3404,9 +3458,9 @@ void launch_eval(bool mixed, bool interp, double refine_budget, const Grid& g,
     const int32_t L = mixed ? s32.L : s64.L;
     if (L > 0 && tl.T % L == 0)
       sp = mixed ? SpecShape{L, s32.Q, s32.nslots, s32.nblk, kSpecPsiMixed, 0.5 / s32.Q,
-                             (double)(s32.nslots - 1) / s32.Q}
+                             (double)(s32.nslots - 1) / s32.Q, s32.fmax}
                  : SpecShape{L, s64.Q, s64.nslots, s64.nblk, kSpecPsiFp64, 0.5 / s64.Q,
-                             (double)(s64.nslots - 1) / s64.Q};
+                             (double)(s64.nslots - 1) / s64.Q, s64.fmax};
     {
       const bool tab = g.orb.coef != nullptr;
       auto nodes = mixed ? (tab ? k_interp_nodes<true, true> : k_interp_nodes<true, false>)
@@ -3465,9 +3519,10 @@ void launch_eval(bool mixed, bool interp, double refine_budget, const Grid& g,
   if (interp && !mixed && refine_budget > 0.0) {
     // the mixed path's bar (1e-4 + 1e-6 cond) already covers the interpolation error
     const int64_t m = (int64_t)n_particles * stride;
-    hipLaunchKernelGGL(k_mark, dim3(nblk(8 * m, 256)), dim3(256), 0, s, ws.pc, n_particles, stride,
-                       ws.cnt, ws.off, ws.partials, ws.xflag, ws.xerr, refine_budget, ws.refine,
-                       ws.nrefine);
+    hipLaunchKernelGGL(k_mark, dim3(nblk(8 * m, 256)), dim3(256), 0, s, g,
+                       s64.L > 0 ? spec_grid(g, s64.Q) : 0.0, ws.pc,
+                       n_particles, ws.bounds, stride, ws.cnt, ws.off, ws.partials, ws.xflag,
+                       ws.xerr, refine_budget, ws.refine, ws.nrefine);
     exact_pass(ws.refine, ws.nrefine);
   }
 }

@@ -14,13 +14,16 @@
 // The grid is f_j = (k_lo + j) df rounded to a double; e_j = exact - rounded.  The slope's
 // phase is taken at the rounded frequency, e^{2 pi i beta_q ((t - c) - e_j / df)} (the second
 // factor to first order: |2 pi beta_q e_j / df| <~ 4e-9), which leaves the grid term of
-// |B - beta_q| <= 1 / (2 Q) alone, below 2e-12 rad at 2.5 years.
+// |B - beta_q| <= 1 / (2 Q) alone: with |e_j| half an ulp of f, up to 3.4e-12 rad at 2.5
+// years, Q = 512 and 62.5-125 mHz, and 2.7e-11 with Q = 64.  spec_fmax (fstat_kernels.hip)
+// keeps the FP64 block loop to frequencies where that is within the refinement budget.
 //
 // Why 16 nodes, Q = 2 L (FP64) and Q = L (FP32): over a half block the remaining slope turns
-// g by at most pi / 4 (Q = 2 L) and the curvature by kSpecPsi64 = 0.25 rad; the Chebyshev
-// coefficients of e^{i (0.785 x + 0.25 x^2)} fall below 1e-13 at degree 16.  With Q = L the
-// slope turns it by pi / 2 and the curvature may reach 1 rad before the sixteenth coefficient
-// passes 1e-8, the mixed path's FP32 resolution.  16 nodes of 8 + 8 bytes (real and
+// g by at most pi / 4 (Q = 2 L) and the curvature by kSpecPsiFp64 = 0.25 rad; the
+// interpolant of e^{i (0.785 x + 0.25 x^2)} then misses a bin by at most 1.5e-13 (rms
+// 1e-13; computed for L = 32 to 256).  With Q = L the slope turns it by pi / 2 and the
+// curvature may reach 1 rad, where the largest error is 1.0e-8 (rms 6e-9), below the mixed
+// path's FP32 resolution.  16 nodes of 8 + 8 bytes (real and
 // imaginary part side by side: one load per lane) are two whole 128-byte lines per
 // (block, slope) row.
 //
