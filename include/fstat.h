@@ -241,8 +241,9 @@ int fstat_waveform(double T_obs, double df, int64_t k_lo, int64_t nbins, const d
  * n particles; np [n] partition counts (device) with part_stride their
  * maximum, or np NULL and np_uniform for all) for work items of 256, 512,
  * 1024, 2048, 2560, 4096, 4608 and 8192 bins (those above the interpolating
- * loop's LDS tile, 2560 bins FP64 and 4608 mixed, for the exact loop only; on
- * the mixed path of a plan with block spectra also 5120) and
+ * loop's LDS tile, 2560 bins FP64 and 4608 mixed, for the exact loop only;
+ * with block spectra of the precision the interpolating loop from 2048 bins
+ * on, on the mixed path up to 5120) and
  * persistent grids of 1, 2, 4 times the resident occupancy, keeps
  * the fastest for the precision selected by flags (FSTAT_EVAL_MIXED) in the
  * plan, and returns it.  With FSTAT_AUTOTUNE_MODE it times the exact per-bin
@@ -252,7 +253,9 @@ int fstat_waveform(double T_obs, double df, int64_t k_lo, int64_t nbins, const d
  * same within the parity bars; FSTAT_EVAL_EXACT tunes the exact loop only).
  * Results are cached in the text file named by $FSTAT_TUNE_CACHE (if set),
  * keyed by GPU architecture, band size, Np class (and whether Np varies),
- * precision and mode; FSTAT_AUTOTUNE_FORCE re-measures.  Requires
+ * channels, block length of the spectra, precision and mode; an entry that
+ * this search would not try is measured again; FSTAT_AUTOTUNE_FORCE
+ * re-measures.  Requires
  * FSTAT_DEVICE_PTRS; waits for completion.  best_ms is -1 when the value came
  * from the cache.                                                          */
 int fstat_autotune(fstat_plan_t plan, const double *params, int64_t n, int32_t np_uniform,

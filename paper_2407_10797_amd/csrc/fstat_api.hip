@@ -327,7 +327,7 @@ int eval_device(fstat_plan_s* P, const double* params, int64_t n, const int32_t*
 }
 
 // ---- autotuner --------------------------------------------------------------
-static std::string tune_key(const fstat_plan_s* P, int32_t np, bool mixed) {
+static std::string tune_key(const fstat_plan_s* P, int32_t np, bool mixed, bool exact) {
   hipDeviceProp_t prop;
   std::string arch = "gpu";
   if (hipGetDeviceProperties(&prop, P->device) == hipSuccess) arch = prop.gcnArchName;
@@ -335,9 +335,14 @@ static std::string tune_key(const fstat_plan_s* P, int32_t np, bool mixed) {
   while (npc < np) npc <<= 1;
   int nbc = 0;
   while ((1ll << nbc) < P->grid.nbins) ++nbc;
-  char buf[256], chs[16] = "";
+  // a plan with block spectra has other candidates and times another loop than one of
+  // the same band class without (97,000 and 24,000 bins lie inside a class, and spectra
+  // depend on T_obs df, the budget and free memory as well): the block length in the key
+  char buf[256], chs[16] = "", blk[16] = "";
   if (P->grid.chan.n > 1) snprintf(chs, sizeof(chs), " ch%d", P->grid.chan.n);
-  snprintf(buf, sizeof(buf), "%s nbins2^%d np%d%s %s", arch.c_str(), nbc, npc, chs,
+  const int32_t L = exact ? 0 : (mixed ? P->s32.L : P->s64.L);
+  if (L > 0) snprintf(blk, sizeof(blk), " L%d", L);
+  snprintf(buf, sizeof(buf), "%s nbins2^%d np%d%s%s %s", arch.c_str(), nbc, npc, chs, blk,
            mixed ? "mixed" : "fp64");
   for (char* c = buf; *c; ++c)
     if (*c == ':') *c = '_';
@@ -389,6 +394,21 @@ static void tune_cache_put(const std::string& key, int chunk, int mult, int ex) 
   fclose(fp);
 }
 
+// The item sizes that the autotuner times (ex: for the exact loop).  Tiles above the
+// per-bin loop's LDS stage only where the block loop takes the items; with block spectra
+// a smaller tile only means more nodes, records and workspace (9216 particles on 7.1M
+// bins: 144 GB at 256 bins, whose release slows the device's next large allocations by
+// seconds).
+constexpr int kTuneMixed = 5120, kTuneSpecMin = 2048;
+static int tile_limit(const fstat_plan_s* P, bool mixed) {
+  return mixed && P->s32.L > 0 ? kTuneMixed : interp_max_tile(mixed);
+}
+static bool tune_candidate(const fstat_plan_s* P, bool mixed, bool ex, int chunk) {
+  if (ex) return chunk != kTuneMixed;
+  return chunk <= tile_limit(P, mixed) &&
+         ((mixed ? P->s32.L : P->s64.L) == 0 || chunk >= kTuneSpecMin);
+}
+
 }  // namespace fstat
 
 extern "C" {
@@ -408,19 +428,17 @@ int fstat_autotune(fstat_plan_t P, const double* params, int64_t n, int32_t np_u
     return set_error(FSTAT_EINVAL, "precision not built into the plan");
   hipStream_t s = (hipStream_t)hip_stream;
   const int32_t stride = np ? part_stride : np_uniform;
-  const std::string key = tune_key(P, stride, mixed) + (np ? " npmix" : "") +
+  const std::string key = tune_key(P, stride, mixed, exact) + (np ? " npmix" : "") +
                           (exact ? " exact" : (mode ? " mode" : ""));
   bool& prefer = mixed ? P->prefer_exact_mixed : P->prefer_exact_fp64;
   int c = 0, m = 0, e = 0;
   double ms_best = -1.0;
-  if (!(flags & FSTAT_AUTOTUNE_FORCE) && tune_cache_get(key, &c, &m, &e) && c >= 64 && m >= 1) {
+  if (!(flags & FSTAT_AUTOTUNE_FORCE) && tune_cache_get(key, &c, &m, &e) && c >= 64 && m >= 1 &&
+      tune_candidate(P, mixed, exact || e != 0, c)) {
     // cached
   } else {
     static const int chunks[] = {256, 512, 1024, 2048, 2560, 4096, 4608, 5120, 8192};
     static const int mults[] = {1, 2, 4};
-    // tiles above the per-bin loop's LDS stage only where the block loop takes the items
-    constexpr int kTuneMixed = 5120, kTuneSpecMin = 2048;
-    const int tile_limit = mixed && P->s32.L > 0 ? kTuneMixed : interp_max_tile(mixed);
     double* F = nullptr;
     int rc = hip_check(hipMalloc(&F, sizeof(double) * n), "alloc tune out");
     hipEvent_t e0, e1;
@@ -436,11 +454,7 @@ int fstat_autotune(fstat_plan_t P, const double* params, int64_t n, int32_t np_u
     for (int ex = exact ? 1 : 0; ex <= ((exact || mode) ? 1 : 0) && !rc; ++ex)
       for (int ci = 0; ci < (int)(sizeof(chunks) / sizeof(chunks[0])) && !rc; ++ci)
         for (int mi = 0; mi < 3 && !rc; ++mi) {
-          if (ex ? chunks[ci] == kTuneMixed : chunks[ci] > tile_limit) continue;
-          // with block spectra a smaller tile only means more nodes, records and workspace
-          // (9216 particles on 7.1M bins: 144 GB at 256 bins, whose release slows the
-          // device's next large allocations by seconds)
-          if (!ex && (mixed ? P->s32.L : P->s64.L) > 0 && chunks[ci] < kTuneSpecMin) continue;
+          if (!tune_candidate(P, mixed, ex != 0, chunks[ci])) continue;
           if (mixed) { P->chunk_mixed = chunks[ci]; P->grid_mult_mixed = mults[mi]; }
           else { P->chunk = chunks[ci]; P->grid_mult_fp64 = mults[mi]; }
           double t_min = 1e300;
