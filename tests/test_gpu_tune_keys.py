@@ -45,7 +45,7 @@ def _points(n=32):
 @pytest.mark.parametrize("mixed, sizes", [(False, (70_001, 120_001)), (True, (20_001, 30_001))])
 @pytest.mark.parametrize("first", [0, 1])
 def test_plans_with_and_without_spectra_keep_their_own_choice(cache, mixed, sizes, first):
-    npart = 8 + first                       # a key of its own (Np classes 8 and 16)
+    npart = 600 + 600 * first         # keys of its own: choices last as long as the process
     prm = _points()
     a, b = _plan(sizes[first]), _plan(sizes[1 - first])
     try:
@@ -65,14 +65,14 @@ def test_entries_outside_the_plans_search_are_measured_again(cache):
     prm = _points()
     plan = _plan(20_001)
     try:
-        plan.autotune(prm, 32, mixed=True, force=True)
+        plan.autotune(prm, 4096, mixed=True, force=True)
         key = cache.read_text().splitlines()[-1].split("|")[0]
         with open(cache, "a") as f:
-            f.write(key.replace("np32", "np64") + "|5120 1 0\n")      # above the per-bin loop's tile
-            f.write(key.replace("np32", "np128") + "|512 2 0\n")
-        c, m, ms = plan.autotune(prm, 64, mixed=True)
+            f.write(key.replace(" np4096 ", " np8192 ") + "|5120 1 0\n")      # above the per-bin loop's tile
+            f.write(key.replace(" np4096 ", " np16384 ") + "|512 2 0\n")
+        c, m, ms = plan.autotune(prm, 8192, mixed=True)
         assert ms > 0 and c <= 4608
-        assert plan.autotune(prm, 128, mixed=True) == (512, 2, -1.0)
-        plan.eval(prm, 64, mixed=True)
+        assert plan.autotune(prm, 16384, mixed=True) == (512, 2, -1.0)
+        plan.eval(prm, 8192, mixed=True)
     finally:
         plan.close()
