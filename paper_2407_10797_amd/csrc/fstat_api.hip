@@ -245,14 +245,24 @@ int eval_blocks(fstat_plan_s* P, bool mixed) {
 }
 
 
+// The precision's tile is the caller's: neither tuned nor the plan's own choice.
+static bool chunk_by_caller(const fstat_plan_s* P, bool mixed) {
+  return P->chunk_given && !(mixed && P->chunk_mixed > 0);
+}
+
+// Largest tile of the interpolating loop: the per-bin loop's LDS stage, and for the
+// plan's own choices kTuneMixed where the block loop takes most items (the others go
+// through the stage in parts).
+constexpr int kTuneMixed = 5120;
+static int tile_limit(const fstat_plan_s* P, bool mixed) {
+  return mixed && P->s32.L > 0 && !chunk_by_caller(P, mixed) ? kTuneMixed : interp_max_tile(mixed);
+}
+
 static int check_chunk(const fstat_plan_s* P, bool mixed, bool exact) {
-  const int chunk = chunk_for(P, mixed);
-  // only a size that the caller asked for: the plan's own choices above the
-  // LDS stage go through it in parts
-  const bool given = P->chunk_given && !(mixed && P->chunk_mixed > 0);
-  if (!exact && given && chunk > interp_max_tile(mixed))
+  const int chunk = chunk_for(P, mixed), most = tile_limit(P, mixed);
+  if (!exact && chunk > most)
     return set_error(FSTAT_EINVAL, "work-item size %d exceeds the LDS tile limit %d (use a smaller "
-                     "chunk or FSTAT_EVAL_EXACT)", chunk, interp_max_tile(mixed));
+                     "chunk or FSTAT_EVAL_EXACT)", chunk, most);
   return FSTAT_OK;
 }
 
@@ -261,9 +271,9 @@ static int check_chunk(const fstat_plan_s* P, bool mixed, bool exact) {
 // partition.
 static Tiling tiling_for(const fstat_plan_s* P, bool mixed, bool exact) {
   const int chunk = chunk_for(P, mixed);
-  const bool given = P->chunk_given && !(mixed && P->chunk_mixed > 0);
   const int32_t L = mixed ? P->s32.L : P->s64.L;
-  return make_tiling(P->grid, chunk, !exact && !given && L > 0 && chunk % L == 0, mixed);
+  return make_tiling(P->grid, chunk,
+                     !exact && !chunk_by_caller(P, mixed) && L > 0 && chunk % L == 0, mixed);
 }
 
 // Enqueue the kernels of one evaluation on workspace `ws` (device pointers).
@@ -394,18 +404,14 @@ static void tune_cache_put(const std::string& key, int chunk, int mult, int ex) 
   fclose(fp);
 }
 
-// The item sizes that the autotuner times (ex: for the exact loop).  Tiles above the
-// per-bin loop's LDS stage only where the block loop takes the items; with block spectra
-// a smaller tile only means more nodes, records and workspace (9216 particles on 7.1M
-// bins: 144 GB at 256 bins, whose release slows the device's next large allocations by
-// seconds).
-constexpr int kTuneMixed = 5120, kTuneSpecMin = 2048;
-static int tile_limit(const fstat_plan_s* P, bool mixed) {
-  return mixed && P->s32.L > 0 ? kTuneMixed : interp_max_tile(mixed);
-}
+// The item sizes that the autotuner times (ex: for the exact loop).  With block spectra
+// a tile below kTuneSpecMin only means more nodes, records and workspace (9216 particles
+// on 7.1M bins: 144 GB at 256 bins, whose release slows the device's next large
+// allocations by seconds).
+constexpr int kTuneSpecMin = 2048;
 static bool tune_candidate(const fstat_plan_s* P, bool mixed, bool ex, int chunk) {
   if (ex) return chunk != kTuneMixed;
-  return chunk <= tile_limit(P, mixed) &&
+  return chunk <= (mixed && P->s32.L > 0 ? kTuneMixed : interp_max_tile(mixed)) &&
          ((mixed ? P->s32.L : P->s64.L) == 0 || chunk >= kTuneSpecMin);
 }
 
