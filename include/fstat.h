@@ -246,7 +246,9 @@ int fstat_waveform(double T_obs, double df, int64_t k_lo, int64_t nbins, const d
  * on, on the mixed path up to 5120) and
  * persistent grids of 1, 2, 4 times the resident occupancy, keeps
  * the fastest for the precision selected by flags (FSTAT_EVAL_MIXED) in the
- * plan, and returns it.  With FSTAT_AUTOTUNE_MODE it times the exact per-bin
+ * plan, and returns it (on a plan that was given a chunk, the size tuned for
+ * FP64 also replaces it on the mixed path, one tile per item, until that is
+ * tuned).  With FSTAT_AUTOTUNE_MODE it times the exact per-bin
  * loop as well and, when that is faster (small batches, where the
  * interpolating loop's node evaluations are a latency chain), makes the
  * plan's later evaluations of that precision use it (the statistic is the

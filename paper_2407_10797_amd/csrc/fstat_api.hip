@@ -245,9 +245,10 @@ int eval_blocks(fstat_plan_s* P, bool mixed) {
 }
 
 
-// The precision's tile is the caller's: neither tuned nor the plan's own choice.
+// The precision's tile is the caller's: neither tuned nor the plan's own choice.  (A
+// size tuned for FP64 serves the mixed path until that is tuned, as the caller's did.)
 static bool chunk_by_caller(const fstat_plan_s* P, bool mixed) {
-  return P->chunk_given && !(mixed && P->chunk_mixed > 0);
+  return P->chunk_given && !(mixed ? P->chunk_mixed > 0 : P->chunk_tuned);
 }
 
 // Largest tile of the interpolating loop: the per-bin loop's LDS stage, and for the
@@ -452,8 +453,8 @@ int fstat_autotune(fstat_plan_t P, const double* params, int64_t n, int32_t np_u
     if (!rc) rc = hip_check(hipEventCreate(&e1), "event");
     const int save_c = P->chunk, save_cm = P->chunk_mixed;
     const int save_m = mixed ? P->grid_mult_mixed : P->grid_mult_fp64;
-    const bool save_p = prefer, save_g = P->chunk_given;
-    P->chunk_given = false;
+    const bool save_p = prefer, save_t = P->chunk_tuned;
+    if (!mixed) P->chunk_tuned = true;
     prefer = false;     // each candidate below runs the loop it names
     // interpolating loop (unless exact is requested), then the exact loop
     // (when requested, or when the mode is tuned as well)
@@ -481,7 +482,7 @@ int fstat_autotune(fstat_plan_t P, const double* params, int64_t n, int32_t np_u
     P->chunk = save_c; P->chunk_mixed = save_cm;
     if (mixed) P->grid_mult_mixed = save_m; else P->grid_mult_fp64 = save_m;
     prefer = save_p;
-    P->chunk_given = save_g;
+    P->chunk_tuned = save_t;
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (F) (void)hipFree(F);
@@ -489,7 +490,7 @@ int fstat_autotune(fstat_plan_t P, const double* params, int64_t n, int32_t np_u
     tune_cache_put(key, c, m, e);
   }
   if (mixed) { P->chunk_mixed = c; P->grid_mult_mixed = m; }
-  else { P->chunk = c; P->grid_mult_fp64 = m; P->chunk_given = false; }
+  else { P->chunk = c; P->grid_mult_fp64 = m; P->chunk_tuned = true; }
   if (!exact) prefer = mode && e != 0;
   if (best_chunk) *best_chunk = c;
   if (best_mult) *best_mult = m;

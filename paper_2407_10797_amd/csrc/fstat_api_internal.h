@@ -21,7 +21,8 @@ struct fstat_plan_s {
   int num_cu = 0;
   int prec = 0;
   int chunk = 2048;                 // bins per work item (both precisions unless tuned)
-  bool chunk_given = false;         // chunk comes from the caller's options
+  bool chunk_given = false;         // the caller's options gave a chunk
+  bool chunk_tuned = false;         // chunk comes from an FP64 autotuning
   int chunk_mixed = 0;              // tuned value for the mixed path (0: use chunk)
   double refine_budget = 5e-10;    // see fstat_opts.refine_budget
   int grid_mult_fp64 = 1, grid_mult_mixed = 1;   // persistent-grid multiplier

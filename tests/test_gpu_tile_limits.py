@@ -1,6 +1,7 @@
 """Work-item sizes above the interpolating loop's tile (2560 bins FP64, 4608
 mixed) that a plan got from tuning the exact loop are refused by that loop, on
-plans with and without block spectra."""
+plans with and without block spectra; and a caller's item size stays one tile
+per item on the mixed path when only FP64 is tuned."""
 import os
 
 import numpy as np
@@ -62,3 +63,23 @@ def test_exact_loop_sizes_are_refused_by_the_interpolating_loop(cache, nbins, mi
         np.testing.assert_allclose(F.cpu().numpy(), ref.cpu().numpy(), rtol=1e-5 if mixed else 1e-9)
     finally:
         plan.close()
+
+
+def test_callers_tile_on_the_mixed_path_after_fp64_tuning(cache):
+    prm = _points()
+    plan, own = _plan(800_001, chunk=1024), None
+    try:
+        c = plan.autotune(prm, 4, force=True)[0]
+        plan.eval(prm, 4, mixed=True)
+        items = plan.interp_stats()[0]
+        own = _plan(800_001, chunk=c)
+        own.eval(prm, 4, mixed=True)
+        print(f"[limits] FP64 tuned to {c} bins: {items} mixed items", flush=True)
+        assert items == own.interp_stats()[0]
+        plan.autotune(prm, 4, mixed=True, force=True)     # the mixed path's own choice
+        plan.eval(prm, 4, mixed=True)
+        assert plan.interp_stats()[0] != items or c >= 5120
+    finally:
+        plan.close()
+        if own is not None:
+            own.close()
