@@ -511,8 +511,10 @@ def main():
             r = time_path(plan, prm, args.np, args.steps, args.warmup, mixed, sur)
             items, rejected, refined, mix = plan.interp_stats(bin_mix=True)
             bmix, rmix = bin_mix_dict(mixed, mix)
+            # sixteen lanes' work per item: all from the block spectra (up to 64 bin by bin)
+            blocks = sum(mix[7:13]) <= 17 * (items - rejected)
             extra.update(work_items=items, exact_items=rejected, refined_items=refined,
-                         bin_mix=bmix, run_mix=rmix)
+                         block_loop=blocks, bin_mix=bmix, run_mix=rmix)
             if sur:
                 extra["used"], extra["fallback"] = plan.surrogate_stats()
         except fstat.FstatError as e:
@@ -524,11 +526,12 @@ def main():
         bins = r["bins_per_launch"]
         # FLOPs that the bin sums execute per launch (counted): their algorithm's
         # own, samples per block and not bins
+        counted = same_src and blocks       # the counted kernels did this launch
         f32 = FLOP32_PER_BIN[kind] * bins
         f64 = FLOP_PER_BIN[kind] * bins - f32
         step_secs = r["seconds"] / args.steps
         roof = dict(bound="alu", unit="TFLOP/s", flop_source="counters")
-        if same_src:
+        if counted:
             peak = floor_peak(f64, f32, PEAK_VALU_TFLOPS, PEAK_F32_TFLOPS)
             achieved = (f64 + f32) / secs / 1e12
             roof.update(achieved=achieved, peak=round(peak, 1), frac=achieved / peak,
@@ -544,17 +547,17 @@ def main():
         roof["per_bin_loop_flop_per_launch"] = sum(alg_flops(kind, mix))
         # the counted figures belong to the kernel sources they were counted on
         rd, wr = TRAFFIC[kind]
-        traffic = rd * bins + wr if same_src else None
+        traffic = rd * bins + wr if counted else None
         roof["traffic"] = traffic
         variants[name] = dict(templates_per_s=tps, ms_per_step=1e3 * r["seconds"] / args.steps,
                               stage_ms=r["kernel_ms"], main_kernel=MAIN_KERNEL[kind],
                               main_kernel_ms=r["main_ms"], bins_per_launch=bins,
                               bin_templates_per_s=bins / (r["kernel_ms"] * 1e-3),
-                              executed_flop_per_bin=FLOP_PER_BIN[kind] if same_src else None,
+                              executed_flop_per_bin=FLOP_PER_BIN[kind] if counted else None,
                               # issue slots: unpacked FP32 issues at the FP64 rate (measured
                               # by the calibration leg), so every VALU instruction counts once
                               valu_issue_frac=VALU_PER_BIN[kind] * bins / secs / PEAK_LANE_INSTR
-                              if same_src else None,
+                              if counted else None,
                               hbm_GBps=traffic / secs / 1e9 if traffic else None,
                               roofline=roof, **extra)
         _log(f"{name}: {tps:.1f} templates/s, bin-loop stage {r['kernel_ms']:.2f} ms, main kernel "

@@ -167,7 +167,13 @@ static int scratch_init(int dev) {
 }
 
 // Block spectra of the plan's data.  They only speed the evaluation up: where
-// the device has no room for them the per-bin loop takes every item.
+// the device has no room for them the per-bin loop takes every item, and
+// fstat_last_error says so after the plan's creation.
+static int no_room(size_t need, size_t free_b) {
+  (void)set_error(FSTAT_OK, "no block spectra: %.3f GB needed, at most a quarter of %.3f GB free "
+                  "taken; evaluations sum bin by bin", need * 1e-9, free_b * 1e-9);
+  return FSTAT_OK;
+}
 static int make_spectra(fstat_plan_s* P, hipStream_t s) {
   const Grid& g = P->grid;
   Spectra<double> t64{};
@@ -196,15 +202,19 @@ static int make_spectra(fstat_plan_s* P, hipStream_t s) {
   const size_t nch = (size_t)g.chan.n;
   // at most a quarter of the free memory, so that a plan does not crowd out its caller
   size_t free_b = 0, total_b = 0;
-  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) { (void)hipGetLastError(); return FSTAT_OK; }
-  if (nch * (n64 * sizeof(double) + n32 * sizeof(float)) > free_b / 4) return FSTAT_OK;
+  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
+    (void)hipGetLastError();
+    free_b = 0;
+  }
+  const size_t need = nch * (n64 * sizeof(double) + n32 * sizeof(float));
+  if (need > free_b / 4) return no_room(need, free_b);
   bool have = true;
   if (n64) have = hipMalloc((void**)&t64.S, nch * n64 * sizeof(double)) == hipSuccess;
   if (have && n32) have = hipMalloc((void**)&t32.S, nch * n32 * sizeof(float)) == hipSuccess;
   if (!have) {
     (void)hipGetLastError();
     if (t64.S) (void)hipFree(t64.S);
-    return FSTAT_OK;
+    return no_room(need, free_b);
   }
   P->s64 = t64;                     // the plan owns them from here on
   P->s32 = t32;

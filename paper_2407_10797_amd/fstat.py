@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 
 import numpy as np
 
@@ -415,6 +416,9 @@ class Plan:
         opts = fstat_opts(int(precision), FSTAT_DEVICE_PTRS | (FSTAT_PROFILE if profile else 0),
                           int(chunk), 0, float(refine_budget))
         self.handle = fstat_plan_create(desc, opts, _stream())
+        note = fstat_last_error()
+        if note:                        # created, but without block spectra
+            warnings.warn(note, RuntimeWarning, stacklevel=2)
         torch.cuda.current_stream().synchronize()
 
     def eval(self, params, np_parts=1, part_stride: int | None = None, mixed: bool = False,
