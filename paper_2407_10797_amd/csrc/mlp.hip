@@ -388,18 +388,16 @@ __device__ __forceinline__ V block_sum(const float* __restrict__ v, int B, V* re
   return red[0];
 }
 
-// dz4 = dy w5 * SiLU'(z4) (bf16, and FP32 with DZ) for 64 columns and
+// dz4 = dy w5 * SiLU'(z4) (bf16) for 64 columns and
 // the rows of slice blockIdx.y, with the slice's column sums of dy SiLU(z4) (dW5)
 // and of dz4 (db4) in the order of k_colred.  Two blocks past the slices sum dy
 // (db5) and the squared errors (the batch's mean loss, where loss is given).
 // Batch 4096: 4.2 us; the six launches that this was took 43 us, 15.6 of them a
 // single block's serial sum over the slices (now in k_adam, beside its other sums).
-template <bool DZ>
 __global__ __launch_bounds__(256) void k_out_back(const float* __restrict__ z4, int B, int slices,
                                                   const float* __restrict__ w5,
                                                   const float* __restrict__ dy,
                                                   const float* __restrict__ sq,
-                                                  float* __restrict__ dz,
                                                   uint16_t* __restrict__ dzb,
                                                   float* __restrict__ part5,
                                                   float* __restrict__ part4,
@@ -429,7 +427,6 @@ __global__ __launch_bounds__(256) void k_out_back(const float* __restrict__ z4, 
     const float z = z4[at], dm = dy[m];
     a5 = fmaf(silu(z), dm, a5);
     const float d = dm * w * dsilu(z);
-    if (DZ) dz[at] = d;
     dzb[at] = f2bf(d);
     {
 #pragma clang fp contract(off)
@@ -805,9 +802,9 @@ void Mlp::backward(const float* x, int B, double* loss, hipStream_t s) {
   parts_slices = sl;
   parts_ks = ks;
   // dz4; dW5[k] = sum_m dy[m] SiLU(z4[m][k]), db4; db5 = sum_m dy[m]
-  hipLaunchKernelGGL((fused ? k_out_back<false> : k_out_back<true>), dim3(kHid / 64, sl + 1),
-                     dim3(256), 0, s, z[3], B, sl, params + mlp_off_w(4), dy, sq, dz,
-                     dzb + 2 * BH, red, red + set, grad + mlp_off_b(4), loss);
+  hipLaunchKernelGGL(k_out_back, dim3(kHid / 64, sl + 1), dim3(256), 0, s, z[3], B, sl,
+                     params + mlp_off_w(4), dy, sq, dzb + 2 * BH, red, red + set,
+                     grad + mlp_off_b(4), loss);
   for (int l = 3; l >= 1; --l) {
     // dH_{l-1} = dZ_l W_l, dz_{l-1} = dH_{l-1} SiLU'(z_{l-1}); the column sums
     // give db_{l-1}, or dW1 and db1
