@@ -32,6 +32,7 @@
 // 3.3 ms mixed; the largest partition error against the exact loop is unchanged
 // (2.6e-12, 2.1e-11, 2.3e-10 at Np = 1, 64, 256).
 #include <cmath>
+#include <type_traits>
 
 #include "fstat_kernels.h"
 
@@ -98,13 +99,13 @@ void spectra_weights(int32_t L, double* out) {
 // for the whole wavefront: scalar loads).  Bins are taken in mirrored pairs t = c +- (p + 1/2):
 // l_m(-x) = l_{15-m}(x), so the sums and differences of a pair serve two nodes each, 16 FMAs
 // per bin instead of 32.  Bound by FP64 issue: about 27 instructions per bin and slope.
-template <bool D64, bool D32>
+template <typename T>
 __global__ __launch_bounds__(64) void k_spectra(Grid g, const double* __restrict__ wr,
                                                  const double* __restrict__ wi, int L, int Q,
-                                                 int nslots, int n32, int nblk, int q0,
+                                                 int nslots, int nblk, int q0,
                                                  const double* __restrict__ lag,
-                                                 double* __restrict__ s64,
-                                                 float* __restrict__ s32) {
+                                                 T* __restrict__ S) {
+  typedef typename std::conditional<sizeof(T) == 8, double2, float2>::type T2;
   const int q = q0 >= 0 ? q0 : blockIdx.y * blockDim.x + threadIdx.x;
   const int b = q0 >= 0 ? blockIdx.x * blockDim.x + threadIdx.x : blockIdx.x;
   if (q >= nslots || b >= nblk) return;
@@ -142,25 +143,11 @@ __global__ __launch_bounds__(64) void k_spectra(Grid g, const double* __restrict
     ei = fma(er, zi, ei * zr);
     er = nr;
   }
-  if constexpr (D64) {
-    double2* o = reinterpret_cast<double2*>(s64) + ((int64_t)b * nslots + q) * kSpecNodes;
+  T2* o = reinterpret_cast<T2*>(S) + ((int64_t)b * nslots + q) * kSpecNodes;
 #pragma unroll
-    for (int m = 0; m < kHalf; ++m) {
-      o[m] = double2{Er[m] + Or[m], Ei[m] + Oi[m]};
-      o[kSpecNodes - 1 - m] = double2{Er[m] - Or[m], Ei[m] - Oi[m]};
-    }
-  }
-  if constexpr (D32) {
-    // with both tables the FP32 one keeps every second slope (Q = L beside Q = 2 L)
-    const int q32 = D64 ? q >> 1 : q;
-    if (!D64 || ((q & 1) == 0 && q32 < n32)) {
-      float2* o = reinterpret_cast<float2*>(s32) + ((int64_t)b * n32 + q32) * kSpecNodes;
-#pragma unroll
-      for (int m = 0; m < kHalf; ++m) {
-        o[m] = float2{(float)(Er[m] + Or[m]), (float)(Ei[m] + Oi[m])};
-        o[kSpecNodes - 1 - m] = float2{(float)(Er[m] - Or[m]), (float)(Ei[m] - Oi[m])};
-      }
-    }
+  for (int m = 0; m < kHalf; ++m) {
+    o[m] = T2{(T)(Er[m] + Or[m]), (T)(Ei[m] + Oi[m])};
+    o[kSpecNodes - 1 - m] = T2{(T)(Er[m] - Or[m]), (T)(Ei[m] - Oi[m])};
   }
 }
 
@@ -180,6 +167,7 @@ constexpr int kFftQ = 512;
 constexpr int kFftNodes = 8;              // nodes per work group: half a row
 constexpr int kFftThreads = kFftQ / 8 * kFftNodes;
 constexpr int kFftGroups = 512;           // a multiple of 16: pairs of groups on one XCD
+static_assert(kSpecMaxSlope * kFftQ + 1.5 < kFftQ + 64, "a thread has one slope past the cycle");
 
 struct Cplx {
   double r, i;
@@ -314,31 +302,36 @@ __global__ __launch_bounds__(kFftThreads) void k_spectra_fft(Grid g, const doubl
   }
 }
 
+template <typename T>
+static void launch_direct(const Grid& g, const double* wr, const double* wi, const double* lag,
+                          const Spectra<T>& t, T* S, hipStream_t s) {
+  // slopes in whole wavefronts per block, then the few left over (the last one of Q + 1)
+  // with the blocks across the lanes
+  const int bs = 64, whole = t.nslots / bs;
+  if (whole > 0)
+    hipLaunchKernelGGL(k_spectra<T>, dim3(t.nblk, whole), dim3(bs), 0, s, g, wr, wi, t.L, t.Q,
+                       t.nslots, t.nblk, -1, lag, S);
+  for (int q = whole * bs; q < t.nslots; ++q)
+    hipLaunchKernelGGL(k_spectra<T>, dim3((t.nblk + bs - 1) / bs), dim3(bs), 0, s, g, wr, wi, t.L,
+                       t.Q, t.nslots, t.nblk, q, lag, S);
+}
+
+// With both tables their blocks are of 256 bins (spectra_block), which the transforms take.
 void launch_spectra(const Grid& g, const double* wr, const double* wi, const double* lag,
                     const Spectra<double>& t64, const Spectra<float>& t32, double* s64, float* s32,
                     hipStream_t s) {
-  const int L = s64 ? t64.L : t32.L, Q = s64 ? t64.Q : t32.Q;
-  const int ns = s64 ? t64.nslots : t32.nslots, nblk = s64 ? t64.nblk : t32.nblk;
-  if (s64 && Q == kFftQ && L == kFftQ / 2 && ns <= Q + 64) {
+  if (!s64) {
+    launch_direct(g, wr, wi, lag, t32, s32, s);
+  } else if (t64.Q == kFftQ && t64.L == kFftQ / 2) {
     auto fft = s32 ? k_spectra_fft<true> : k_spectra_fft<false>;
     const size_t lds = sizeof(double2) * (kFftQ * kFftNodes + 2 * kFftQ);
     (void)hipFuncSetAttribute((const void*)fft, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)lds);
     hipLaunchKernelGGL(fft, dim3(kFftGroups), dim3(kFftThreads), lds, s, g, wr, wi,
-                       ns, t32.nslots, nblk, lag, s64, s32);
-    return;
+                       t64.nslots, t32.nslots, t64.nblk, lag, s64, s32);
+  } else {
+    launch_direct(g, wr, wi, lag, t64, s64, s);
   }
-  auto kern = s64 ? (s32 ? k_spectra<true, true> : k_spectra<true, false>)
-                  : k_spectra<false, true>;
-  // slopes in whole wavefronts per block, then the few left over (the last one of Q + 1)
-  // with the blocks across the lanes
-  const int bs = 64, whole = ns / bs;
-  if (whole > 0)
-    hipLaunchKernelGGL(kern, dim3(nblk, whole), dim3(bs), 0, s, g, wr, wi, L, Q, ns, t32.nslots,
-                       nblk, -1, lag, s64, s32);
-  for (int q = whole * bs; q < ns; ++q)
-    hipLaunchKernelGGL(kern, dim3((nblk + bs - 1) / bs), dim3(bs), 0, s, g, wr, wi, L, Q, ns,
-                       t32.nslots, nblk, q, lag, s64, s32);
 }
 
 }  // namespace fstat
