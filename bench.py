@@ -130,14 +130,14 @@ def calibrate(reps=10):
 # bytes written per launch (WRITE_SIZE).
 MAIN_KERNEL = {"fp64": "k_eval_blocks<false> + k_eval_edges<false>",
                "mixed": "k_eval_blocks<true> + k_eval_edges<true>"}
-FLOP_PER_BIN = {"fp64": 13.12, "mixed": 9.62}      # FP64 + FP32
+FLOP_PER_BIN = {"fp64": 13.12, "mixed": 9.65}      # FP64 + FP32
 FLOP32_PER_BIN = {"fp64": 0.01, "mixed": 4.39}      # of which FP32
-VALU_PER_BIN = {"fp64": 11.58, "mixed": 9.33}
-TRAFFIC = {"fp64": (1.1367, 4.979e+07), "mixed": (0.5601, 4.069e+07)}
+VALU_PER_BIN = {"fp64": 11.58, "mixed": 9.39}
+TRAFFIC = {"fp64": (1.1369, 4.978e+07), "mixed": (0.4819, 4.096e+07)}
 # sha256 of the bin-loop kernels' code (fstat_kernels.hip and the two headers
 # it builds on, comments removed) when those counters were taken; the figures
 # are reported as null once it differs.
-COUNTERS_SRC_SHA = "a334ee3107bac21fd4ffd2ed2b08fee7ead18874e29cd55249d2b26c077aba12"
+COUNTERS_SRC_SHA = "92b05a366bf17200ad4f99e579b9f8155b0e8aa24e3ae07fcaf939938e12143f"
 KERNEL_HEADERS = ("fstat_internal.h", "fstat_kernels.h")
 
 

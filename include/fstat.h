@@ -132,7 +132,9 @@ typedef struct {
  * 512 bytes per bin and channel for FP64 and 128 for mixed (3.6 + 0.9 GB at
  * 7.1 million bins), if that is at most a quarter of the free device memory;
  * otherwise every bin is evaluated (the same statistic in other roundings, in
- * about three times the time) and fstat_last_error says so.  The caller keeps
+ * about three times the time) and fstat_last_error says so.  Laying them out
+ * is 0.1 ms of the call at 180,000 bins, 0.4 at 500,000 and 1 to 2 from 1.7
+ * million on; a precision that is not in the mask has none.  The caller keeps
  * ownership of `data`; it may be freed after this call returns.            */
 int fstat_plan_create(fstat_plan_t *plan, const fstat_data_desc *data, const fstat_opts *opts,
                       void *hip_stream);

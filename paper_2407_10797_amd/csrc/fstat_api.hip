@@ -166,15 +166,15 @@ static int scratch_init(int dev) {
   return FSTAT_OK;
 }
 
-// Block spectra of the plan's data.  They only speed the evaluation up: where
-// the device has no room for them the per-bin loop takes every item, and
-// fstat_last_error says so after the plan's creation.
+// Block spectra of the plan's data: their shapes and memory, then their values.  They
+// only speed the evaluation up: where the device has no room for them the per-bin loop
+// takes every item, and fstat_last_error says so after the plan's creation.
 static int no_room(size_t need, size_t free_b) {
   (void)set_error(FSTAT_OK, "no block spectra: %.3f GB needed, at most a quarter of %.3f GB free "
                   "taken; evaluations sum bin by bin", need * 1e-9, free_b * 1e-9);
   return FSTAT_OK;
 }
-static int make_spectra(fstat_plan_s* P, hipStream_t s) {
+static int alloc_spectra(fstat_plan_s* P) {
   const Grid& g = P->grid;
   Spectra<double> t64{};
   Spectra<float> t32{};
@@ -190,14 +190,14 @@ static int make_spectra(fstat_plan_s* P, hipStream_t s) {
     t32.Q = t32.L;
     t32.nslots = spectra_slots(g, t32.Q);
     t32.nblk = (int32_t)(g.nbins / t32.L);
-    n32 = (size_t)t32.nblk * (size_t)t32.nslots * 2 * kSpecNodes;
+    n32 = t32.values();
   }
   if (t64.L) {
     t64.Q = 2 * t64.L;
     t64.nslots = spectra_slots(g, t64.Q);
     if (shared) t64.nslots = std::max(t64.nslots, 2 * t32.nslots - 1);
     t64.nblk = (int32_t)(g.nbins / t64.L);
-    n64 = (size_t)t64.nblk * (size_t)t64.nslots * 2 * kSpecNodes;
+    n64 = t64.values();
   }
   const size_t nch = (size_t)g.chan.n;
   // at most a quarter of the free memory, so that a plan does not crowd out its caller
@@ -218,29 +218,28 @@ static int make_spectra(fstat_plan_s* P, hipStream_t s) {
   }
   P->s64 = t64;                     // the plan owns them from here on
   P->s32 = t32;
-  double* lag = nullptr;
-  int rc = dev_alloc(&lag, 2 * 128 * kSpecNodes, "alloc spectra weights");
-  std::vector<double> h(2 * 128 * kSpecNodes, 0.0);
-  if (t64.L) spectra_weights(t64.L, h.data());
-  if (t32.L) spectra_weights(t32.L, h.data() + 128 * kSpecNodes);
-  if (!rc) rc = hip_check(hipMemcpyAsync(lag, h.data(), h.size() * sizeof(double),
-                                         hipMemcpyHostToDevice, s), "copy spectra weights");
-  for (size_t c = 0; c < nch && !rc; ++c) {
+  return FSTAT_OK;
+}
+static int fill_spectra(fstat_plan_s* P, hipStream_t s) {
+  const Grid& g = P->grid;
+  const Spectra<double>& t64 = P->s64;
+  const Spectra<float>& t32 = P->s32;
+  if (!t64.L && !t32.L) return FSTAT_OK;
+  int rc = FSTAT_OK;
+  for (size_t c = 0; c < (size_t)g.chan.n && !rc; ++c) {
     const double* wr = P->b64.wr + c * (size_t)g.nbins;
     const double* wi = P->b64.wi + c * (size_t)g.nbins;
-    double* o64 = t64.L ? t64.S + c * n64 : nullptr;
-    float* o32 = t32.L ? t32.S + c * n32 : nullptr;
-    if (shared) {
-      launch_spectra(g, wr, wi, lag, t64, t32, o64, o32, s);
+    double* o64 = t64.L ? t64.S + c * t64.values() : nullptr;
+    float* o32 = t32.L ? t32.S + c * t32.values() : nullptr;
+    if (t64.L == t32.L) {
+      launch_spectra(g, wr, wi, t64, t32, o64, o32, s);
     } else {
-      if (o64) launch_spectra(g, wr, wi, lag, t64, t32, o64, nullptr, s);
-      if (o32) launch_spectra(g, wr, wi, lag + 128 * kSpecNodes, t64, t32, nullptr, o32, s);
+      if (o64) launch_spectra(g, wr, wi, t64, t32, o64, nullptr, s);
+      if (o32) launch_spectra(g, wr, wi, t64, t32, nullptr, o32, s);
     }
     rc = hip_check(hipGetLastError(), "block spectra launch");
   }
-  if (!rc) rc = hip_check(hipStreamSynchronize(s), "block spectra");
-  dev_free(lag);
-  return rc;
+  return rc;                        // under way on s
 }
 
 int eval_blocks(fstat_plan_s* P, bool mixed) {
@@ -585,6 +584,7 @@ int fstat_plan_create(fstat_plan_t* out, const fstat_data_desc* d, const fstat_o
     rc = dev_alloc(&P->bin_counter, 1, "alloc counter");
     if (!rc) rc = hip_check(hipMemsetAsync(P->bin_counter, 0, sizeof(unsigned long long), s), "memset");
   }
+  if (!rc) rc = alloc_spectra(P);
   const double* ddata = d->data;
   const double* dpsd = d->psd;
   if (!rc && !dev) {
@@ -634,16 +634,15 @@ int fstat_plan_create(fstat_plan_t* out, const fstat_data_desc* d, const fstat_o
     }
     rc = hip_check(hipMemcpyAsync(P->ubad, bad.data(), sizeof(int32_t) * bad.size(),
                                   hipMemcpyHostToDevice, s), "copy u model flags");
+    // after the copies: a copy of pageable memory behind running kernels waits for them
+    // in a way that took up to 2 ms
+    if (!rc) rc = fill_spectra(P, s);
     if (!rc) rc = hip_check(hipStreamSynchronize(s), "plan prep");
   }
   dev_free(dd);
   dev_free(dp);
   dev_free(ubsum);
   if (rc) {
-    fstat_plan_destroy(P);
-    return rc;
-  }
-  if ((rc = make_spectra(P, s))) {
     fstat_plan_destroy(P);
     return rc;
   }

@@ -111,6 +111,8 @@ struct Spectra {
   int32_t nslots = 0;    // slopes kept: 0 .. T_obs df Q
   int32_t nblk = 0;      // whole blocks per channel
   double fmax = 0.0;     // items that reach this frequency take the per-bin loop
+  // values per channel
+  size_t values() const { return (size_t)nblk * (size_t)nslots * 2 * kSpecNodes; }
 };
 // Default tile of a plan with spectra, and how far a partition's items may be
 // widened: as long as the signal's time in an item stays below kWidenTime and its
@@ -141,10 +143,10 @@ constexpr double kSpecMaxSlope = 1.001;   // largest T_obs df [cycles per bin] w
 int spectra_block(bool mixed, int64_t nbins);
 int spectra_slots(const Grid& g, int32_t Q);
 double spec_fmax(const Grid& g, int32_t Q, double budget);   // FP64: Spectra::fmax
-void spectra_weights(int32_t L, double* out);   // [L / 2][kSpecNodes], host
+int spectra_tables_init();              // the weights of all block sizes, once per device
 // Spectra of one channel (w at wr, wi) into s64 and/or s32; with both they share L and
 // t64 has the slopes of t32 at its even places.
-void launch_spectra(const Grid& g, const double* wr, const double* wi, const double* lag,
+void launch_spectra(const Grid& g, const double* wr, const double* wi,
                     const Spectra<double>& t64, const Spectra<float>& t32, double* s64, float* s32,
                     hipStream_t s);
 

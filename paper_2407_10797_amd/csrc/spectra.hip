@@ -59,10 +59,16 @@ int spectra_slots(const Grid& g, int32_t Q) {
   return (int)std::floor(g.T_obs * g.df * (double)Q + 0.5) + 1;
 }
 
+// The weights of every block size: constants of the node positions, so that a plan neither
+// forms nor uploads them (0.1 ms of a plan of 180,001 bins).  Block size L from row
+// lag_row(L) on: 16 + 32 + 64 + 128 rows.
+__constant__ double c_lag[240 * kSpecNodes];
+constexpr int lag_row(int L) { return L / 2 - 16; }
+
 // Half sums and differences of the Lagrange polynomials of mirrored nodes at the bins of the
 // block's right half: [pair p][0..7] (l_m + l_{15-m}) / 2, [8..15] (l_m - l_{15-m}) / 2 at
 // bin c + p + 1/2 (long double on the host; nodes x_m = cos(pi (m + 1/2) / 16), x = y / c).
-void spectra_weights(int32_t L, double* out) {
+static void spectra_weights(int32_t L, double* out) {
   const long double pi = 3.141592653589793238462643383279502884L;
   const int M = kSpecNodes;
   long double xm[kSpecNodes];
@@ -95,6 +101,12 @@ void spectra_weights(int32_t L, double* out) {
   }
 }
 
+int spectra_tables_init() {
+  double h[240 * kSpecNodes];
+  for (int L = 32; L <= 256; L *= 2) spectra_weights(L, h + lag_row(L) * kSpecNodes);
+  return hipMemcpyToSymbol(HIP_SYMBOL(c_lag), h, sizeof(h)) == hipSuccess ? 0 : -1;
+}
+
 // One thread per slope of a block (the block index, w and the Lagrange weights are the same
 // for the whole wavefront: scalar loads).  Bins are taken in mirrored pairs t = c +- (p + 1/2):
 // l_m(-x) = l_{15-m}(x), so the sums and differences of a pair serve two nodes each, 16 FMAs
@@ -103,7 +115,6 @@ template <typename T>
 __global__ __launch_bounds__(64) void k_spectra(Grid g, const double* __restrict__ wr,
                                                  const double* __restrict__ wi, int L, int Q,
                                                  int nslots, int nblk, int q0,
-                                                 const double* __restrict__ lag,
                                                  T* __restrict__ S) {
   typedef typename std::conditional<sizeof(T) == 8, double2, float2>::type T2;
   const int q = q0 >= 0 ? q0 : blockIdx.y * blockDim.x + threadIdx.x;
@@ -119,6 +130,7 @@ __global__ __launch_bounds__(64) void k_spectra(Grid g, const double* __restrict
 #pragma unroll
   for (int m = 0; m < kHalf; ++m) Er[m] = Ei[m] = Or[m] = Oi[m] = 0.0;
   const int half = L >> 1;
+  const double* lag = c_lag + lag_row(L) * kSpecNodes;
   for (int p = 0; p < half; ++p) {
     const int64_t jr = j0 + half + p, jl = j0 + half - 1 - p;
     const double dr = (double)(g.k_lo + jr), dl = (double)(g.k_lo + jl);
@@ -238,7 +250,6 @@ template <bool D32>
 __global__ __launch_bounds__(kFftThreads) void k_spectra_fft(Grid g, const double* __restrict__ wr,
                                                              const double* __restrict__ wi,
                                                              int nslots, int n32, int nblk,
-                                                             const double* __restrict__ lag,
                                                              double* __restrict__ s64,
                                                              float* __restrict__ s32) {
   extern __shared__ double2 s_fft[];
@@ -254,6 +265,7 @@ __global__ __launch_bounds__(kFftThreads) void k_spectra_fft(Grid g, const doubl
     sincospi((double)k / (double)kFftQ, &s, &c);
     root[k] = double2{c, s};
   }
+  const double* lag = c_lag + lag_row(L) * kSpecNodes;
   // l_m at bins 64 a + j: the half sums and differences at the bin's mirrored pair
   double lm[4];
 #pragma unroll
@@ -303,34 +315,34 @@ __global__ __launch_bounds__(kFftThreads) void k_spectra_fft(Grid g, const doubl
 }
 
 template <typename T>
-static void launch_direct(const Grid& g, const double* wr, const double* wi, const double* lag,
+static void launch_direct(const Grid& g, const double* wr, const double* wi,
                           const Spectra<T>& t, T* S, hipStream_t s) {
   // slopes in whole wavefronts per block, then the few left over (the last one of Q + 1)
   // with the blocks across the lanes
   const int bs = 64, whole = t.nslots / bs;
   if (whole > 0)
     hipLaunchKernelGGL(k_spectra<T>, dim3(t.nblk, whole), dim3(bs), 0, s, g, wr, wi, t.L, t.Q,
-                       t.nslots, t.nblk, -1, lag, S);
+                       t.nslots, t.nblk, -1, S);
   for (int q = whole * bs; q < t.nslots; ++q)
     hipLaunchKernelGGL(k_spectra<T>, dim3((t.nblk + bs - 1) / bs), dim3(bs), 0, s, g, wr, wi, t.L,
-                       t.Q, t.nslots, t.nblk, q, lag, S);
+                       t.Q, t.nslots, t.nblk, q, S);
 }
 
 // With both tables their blocks are of 256 bins (spectra_block), which the transforms take.
-void launch_spectra(const Grid& g, const double* wr, const double* wi, const double* lag,
+void launch_spectra(const Grid& g, const double* wr, const double* wi,
                     const Spectra<double>& t64, const Spectra<float>& t32, double* s64, float* s32,
                     hipStream_t s) {
   if (!s64) {
-    launch_direct(g, wr, wi, lag, t32, s32, s);
+    launch_direct(g, wr, wi, t32, s32, s);
   } else if (t64.Q == kFftQ && t64.L == kFftQ / 2) {
     auto fft = s32 ? k_spectra_fft<true> : k_spectra_fft<false>;
     const size_t lds = sizeof(double2) * (kFftQ * kFftNodes + 2 * kFftQ);
     (void)hipFuncSetAttribute((const void*)fft, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)lds);
     hipLaunchKernelGGL(fft, dim3(kFftGroups), dim3(kFftThreads), lds, s, g, wr, wi,
-                       t64.nslots, t32.nslots, t64.nblk, lag, s64, s32);
+                       t64.nslots, t32.nslots, t64.nblk, s64, s32);
   } else {
-    launch_direct(g, wr, wi, lag, t64, s64, s);
+    launch_direct(g, wr, wi, t64, s64, s);
   }
 }
 
