@@ -1,14 +1,39 @@
-"""A plan has its block spectra, and one made while the device is nearly full has
-none, says so, and gives the same statistic bin by bin (5e-10 relative FP64,
-1e-4 mixed, the block loop's bars)."""
+"""Which loop takes the items: plans of the block loop's grids have their block
+spectra (an item is sixteen lanes' work there, up to 64 in the per-bin loop), item
+sizes that are no multiple of a block rule them out, and a plan made while the
+device is nearly full has none, says so, and gives the same statistic bin by bin
+(5e-10 relative FP64, 1e-4 mixed, the block loop's bars)."""
 import warnings
 
 import numpy as np
 import pytest
 
 from paper_2407_10797_amd import synth as S
+from tests.test_gpu_blocks import GRIDS, _case
 
 pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("chunk", [0, 256, 1000])
+@pytest.mark.parametrize("name", list(GRIDS))
+def test_block_loop_takes_the_items(name, chunk):
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    from paper_2407_10797_amd import fstat
+    g, pts = _case(name)
+    psd = S.psd_tdix(g.freqs())
+    plan = fstat.Plan(S.noise(psd, g.df, 9200), psd, g.T_obs, g.df, g.k_lo, chunk=chunk)
+    try:
+        for mixed in (False, True):
+            plan.eval(torch.from_numpy(pts), 1, mixed=mixed)
+            items, rej, _, mix = plan.interp_stats(bin_mix=True)
+            runs = sum(mix[7:13]) / (items - rej)
+            print(f"[loops] {name} chunk={chunk} mixed={mixed}: {runs:.1f} runs per item", flush=True)
+            # the last particle's short items may be the per-bin loop's
+            assert runs > 40.0 if chunk == 1000 else 15.9 < runs < 24.0
+    finally:
+        plan.close()
 
 
 def test_plan_without_room_for_spectra():
