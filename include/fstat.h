@@ -126,9 +126,9 @@ typedef struct {
  * PSD to device memory the plan owns, and precomputes the per-bin factors
  * that do not depend on the template (the noise weighting 1/S_n, the f^{-7/6}
  * amplitude of App. A, the bin width factor 4 df of Eq. inner_product, and the
- * template-independent part of the TDI-X transfer).  For data sets of about
- * 100,000 bins and more with T_obs df <= 1 it also lays out the data's block
- * spectra, from which the evaluations take the N-terms of smooth templates:
+ * template-independent part of the TDI-X transfer).  For data sets of 97,000
+ * bins and more (mixed path: 24,000) with T_obs df <= 1 it also lays out the
+ * data's block spectra, from which the evaluations take the N-terms of smooth templates:
  * 512 bytes per bin and channel for FP64 and 128 for mixed (3.6 + 0.9 GB at
  * 7.1 million bins), if that is at most a quarter of the free device memory;
  * otherwise every bin is evaluated (the same statistic in other roundings, in
@@ -176,7 +176,7 @@ int fstat_eval(fstat_plan_t plan, const double *params, int64_t n, const int32_t
  *   flags    FSTAT_EVAL_MIXED and/or FSTAT_EVAL_EXACT (FSTAT_DEVICE_PTRS is
  *            implied)
  * The scratch holds n x (ceil(nbins / chunk) x channels + part_stride) work
- * items at about 565 bytes each (chunk: the plan's work-item size); with the
+ * items at about 550 bytes each (chunk: the plan's work-item size); with the
  * default 2048-bin items that is e.g. 320 particles at Np = 256 on 20,972
  * bins, or 16,384 particles at Np = 1; larger calls fail with EINVAL and a
  * message giving the bytes needed.

@@ -242,8 +242,9 @@ __host__ __device__ __forceinline__ void phase_and_tf(const PartConst& P, double
 // mantissa bits pick c, log(m / c) by six terms in r = m / c - 1, |r| <= 2^-8
 // (remainder 2e-18).  log c has 40 fractional bits and ln 2 is split, so that
 // their sum is exact, and each c is one whose reciprocal rounds to less than
-// 2e-18: what is left is the last rounding, 0.5 ulp as the library's log, in 17
-// operations for its ~70.
+// 2e-18: what is left is the last rounding and ~1e-17, 0.5 ulp as the library's log
+// where |log x| is of order one and more (x = Mc f is 5e-7 to 3e-5 in the searches; near
+// x = 1 the terms cancel and only the absolute error stays), in 17 operations for its ~70.
 constexpr int kLogTab = 128;
 __device__ __forceinline__ double log_tab(double x, const double2* lt) {
   const int hi = __double2hiint(x);
